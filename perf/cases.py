@@ -94,9 +94,9 @@ def _exponents(cols, ld, lo, hi, gen):
     return out.view(torch.float32)
 
 
-def prepare(case, seed):
-    M, N, K, pad, mode = case["M"], case["N"], case["K"], case["pad"], _MODES[case["mode"]]
-    trans_a, trans_b = _OPS[case["trans"][0]], _OPS[case["trans"][1]]
+def _inputs(case, seed):
+    """A, B and, for an update, the C it starts from, as the program stores them"""
+    M, N, K, pad = case["M"], case["N"], case["K"], case["pad"]
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
 
@@ -105,14 +105,22 @@ def prepare(case, seed):
             return _uniform(cols, ld, gen)
         return _exponents(cols, ld, *(window if case["inputs"] == "window" else wide), gen)
 
-    a_rows, a_cols = (M, K) if trans_a == ec.OP_N else (K, M)
-    b_rows, b_cols = (K, N) if trans_b == ec.OP_N else (N, K)
+    a_rows, a_cols = (M, K) if case["trans"][0] == "N" else (K, M)
+    b_rows, b_cols = (K, N) if case["trans"][1] == "N" else (N, K)
+    A = matrix(a_cols, a_rows + pad, (-15, 15), (-100, 100))
+    B = matrix(b_cols, b_rows + pad, (-15, 15), (-15, 14))
+    return A, B, _uniform(N, M + pad, gen) if case["beta"] != 0.0 else None
+
+
+def prepare(case, seed):
+    M, N, K, pad, mode = case["M"], case["N"], case["K"], case["pad"], _MODES[case["mode"]]
+    trans_a, trans_b = _OPS[case["trans"][0]], _OPS[case["trans"][1]]
+    A, B, C_in = _inputs(case, seed)
     s = {"case": case, "M": M, "N": N, "K": K, "mode": mode, "trans_a": trans_a, "trans_b": trans_b,
-         "lda": a_rows + pad, "ldb": b_rows + pad, "ldc": M + pad,
-         "A": matrix(a_cols, a_rows + pad, (-15, 15), (-100, 100)), "B": matrix(b_cols, b_rows + pad, (-15, 15), (-15, 14)),
+         "lda": A.shape[1], "ldb": B.shape[1], "ldc": M + pad, "A": A, "B": B,
          "C": torch.zeros((N, M + pad), dtype=torch.float32, device="cuda")}
-    if case["beta"] != 0.0:
-        s["C_in"] = _uniform(N, M + pad, gen)
+    if C_in is not None:
+        s["C_in"] = C_in
     handle = ec.Handle()
     handle.set_stream(torch.cuda.current_stream().cuda_stream)
     nbytes = max(256, handle.workspace_size(trans_a, trans_b, M, N, K, mode))
@@ -153,3 +161,25 @@ def tolerance(case):
     # Measured against a product in 64 bits: 1.2e-7 at K = 256 up to 8.2e-7 at K = 16384 (the FP32 sum of the matrix
     # unit, growing with the square root of the depth it runs over), 5.8e-7 for 65536 deep in slices.  Four times that.
     return {"rel": 4.0 * (1.2e-7 + 5.5e-9 * math.sqrt(min(case["K"], 16384)))}
+
+
+def exact(case, seed):
+    """The same product in 64 bits, rounded nowhere, laid out as `run` returns it"""
+    M, N, pad = case["M"], case["N"], case["pad"]
+    A, B, C_in = _inputs(case, seed)
+
+    C_in = None if C_in is None else C_in[:, :M]
+
+    def logical(X, trans):      # (cols, ld) as stored -> op(X) as a row-major matrix
+        X = X[:, :X.shape[1] - pad]
+        return X.t() if trans == "N" else X
+
+    A, B = logical(A, case["trans"][0]), logical(B, case["trans"][1]).double()
+    out = torch.empty((N, M), dtype=torch.float64, device="cuda")
+    step = max(1, (1 << 27) // case["K"])     # rows of A at a time
+    for at in range(0, M, step):
+        rows = case["alpha"] * (A[at:at + step].double() @ B)
+        if C_in is not None:
+            rows += case["beta"] * C_in[:, at:at + step].t().double()
+        out[:, at:at + step] = rows.t()
+    return out
