@@ -1115,9 +1115,13 @@ struct EventLease {
 //   3. if undecided: the per-row / per-column scaling exponents of both operands from step 1's exponents (largest
 //      binade of every row of op(A) and column of op(B) to 2^14), the FP16 pair split of the scaled operands with the
 //      same statistics, and the second choice: kChoiceFp16Scaled if that fits, else kChoiceBf16
+//      (small products, which one-launch kernels make from the FP32 operands: steps 1 to 3 by measure_rows_kernel)
 //   4. the BF16 three-term split of both operands (if kChoiceBf16), over the FP16 parts, which are no longer needed then
 //   5. the FP16 product, the FP16 product that undoes the scaling vectors, the BF16 product: one of them runs
 enum AutoChoice { kChoiceFp16 = 0, kChoiceBf16 = 1, kChoiceFp16Scaled = 2, kChoiceUndecided = 3 };
+// Deepest product that is measured by rows (measure_rows_kernel): a block walks whole rows, 1024 k per round of loads,
+// twice, and its rows' number of blocks does not grow with the depth, while the measuring splits' does.
+constexpr int64_t kMeasureMaxDepth = 4096;
 constexpr int kAutoScaleTarget = 14;  // where the scaled candidate puts the largest binade of every row and column
 
 ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t transB, int64_t M, int64_t N, int64_t K, float alpha,
@@ -1180,45 +1184,64 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
     if (!tc.start || !tc.split_done || !tc.product_done) return fail(h, ECGEMM_ERR_HIP, "ecgemm_sgemm: hipEventCreate failed");
     ECGEMM_HIP(h, hipEventRecord(tc.start, h->stream));
   }
-  if (try_scaled) {
-    // the first split also finds every row's largest exponent (on the operands as the caller passed them), so that
-    // the scaled candidate needs no pass over A and B of its own for them
-    st = launch_row_scales(h, rows_a, rows_b, nullptr, 0, kRowScaleClear);
-    if (st != ECGEMM_OK) return st;
-    fp16_a.row_max = scales_a;
-    fp16_b.row_max = scales_b;
-  }
-  st = launch_split(h, ECGEMM_MODE_FP16_SPLIT, fp16_a, &fp16_b, true);
-  if (st != ECGEMM_OK) return st;
-  // (operands with few rows: the first choice also turns the rows' exponents into factors, which saves a launch)
-  const bool finish_with_choice = try_scaled && M + N <= 4096;
-  const RowScaleJob no_rows{};
-  hipLaunchKernelGGL(choose_mode_kernel, dim3(1), dim3(1024), 0, h->stream, stats_a, fp16_a.blocks, (double)M, stats_b,
-                     fp16_b.blocks, (double)N, kAutoTolerance, kAutoMinTerms, choice, (int)kChoiceFp16,
-                     (int)(try_scaled ? kChoiceUndecided : kChoiceBf16), (const int*)nullptr, 0,
-                     finish_with_choice ? rows_a : no_rows, finish_with_choice ? rows_b : no_rows);
-  ECGEMM_HIP(h, hipGetLastError());
-  h->auto_choice = choice;
-  if (try_scaled) {
-    // the exponents are found on the operands as the caller passed them; the handle's global pre-scaling, a common
-    // factor of every row, comes on top in the split and is undone with the product's output scale
-    if (!finish_with_choice) {
-      st = launch_row_scales(h, rows_a, rows_b, choice, kChoiceUndecided, kRowScaleFinish);
-      if (st != ECGEMM_OK) return st;
-    }
-    st = launch_split(h, ECGEMM_MODE_FP16_SPLIT, scaled_a, &scaled_b, true);
-    if (st != ECGEMM_OK) return st;
-    hipLaunchKernelGGL(choose_mode_kernel, dim3(1), dim3(1024), 0, h->stream, stats_a, scaled_a.blocks, (double)M, stats_b,
-                       scaled_b.blocks, (double)N, kAutoTolerance, kAutoMinTerms, choice, (int)kChoiceFp16Scaled,
-                       (int)kChoiceBf16, (const int*)choice, (int)kChoiceUndecided, no_rows, no_rows);
-    ECGEMM_HIP(h, hipGetLastError());
-  }
   // Every candidate runs the way ecgemm_sgemm would run it in that mode, so that the result is that call's bit for
-  // bit: a small product as one launch on the FP32 operands (the measuring splits above still write their packed
-  // parts, which nothing reads then), the others with the product kernels on the packed operands.
+  // bit: a small product as one launch on the FP32 operands, the others with the product kernels on the packed operands.
   const Plan one_fp16 = make_plan(M, N, K, ECGEMM_MODE_FP16_SPLIT, h->shape, kOneLaunchSliced);
   const Plan one_bf16 = make_plan(M, N, K, ECGEMM_MODE_BF16_FULL, h->shape, kOneLaunchSliced);
   const bool fp16_one_launch = one_fp16.shape && one_fp16.shape->fused, bf16_one_launch = one_bf16.shape && one_bf16.shape->fused;
+  h->auto_choice = choice;
+  if (fp16_one_launch && bf16_one_launch && try_scaled && K <= kMeasureMaxDepth) {
+    // Nothing reads packed operands: both FP16 candidates are measured in one launch that writes none, the choice is
+    // another (steps 1 to 3 in two launches instead of five).  The blocks' sums lie where the packed operands would.
+    const unsigned blocks_a = (unsigned)((M + kMeasureRows - 1) / kMeasureRows), blocks_b = (unsigned)((N + kMeasureRows - 1) / kMeasureRows);
+    if (kMeasureSums * sizeof(double) * ((size_t)blocks_a + blocks_b) > ap.packed_bytes)
+      return fail(h, ECGEMM_ERR_HIP, "ecgemm_sgemm: internal error, no room for the row statistics");
+    double* sums_a = reinterpret_cast<double*>(ws);
+    double* sums_b = sums_a + kMeasureSums * (size_t)blocks_a;
+    auto job_of = [K](const RowScaleJob& rows, int log2_prescale, double* sums) {
+      return MeasureJob{rows.src, rows.k_contiguous ? rows.ld : 1, rows.k_contiguous ? 1 : rows.ld, rows.rows, K,
+                        std::ldexp(1.0f, log2_prescale), rows.target, rows.scale, sums};
+    };
+    hipLaunchKernelGGL(measure_rows_kernel, dim3(blocks_a + blocks_b), dim3(kMeasureThreads), 0, h->stream,
+                       job_of(rows_a, h->log2_scale_a, sums_a), job_of(rows_b, h->log2_scale_b, sums_b), blocks_a, blocks_b);
+    ECGEMM_HIP(h, hipGetLastError());
+    hipLaunchKernelGGL(choose_from_rows_kernel, dim3(1), dim3(256), 0, h->stream, sums_a, blocks_a, (double)M, sums_b, blocks_b,
+                       (double)N, kAutoTolerance, kAutoMinTerms, choice, (int)kChoiceFp16, (int)kChoiceFp16Scaled, (int)kChoiceBf16);
+    ECGEMM_HIP(h, hipGetLastError());
+  } else {
+    if (try_scaled) {
+      // the first split also finds every row's largest exponent (on the operands as the caller passed them), so that
+      // the scaled candidate needs no pass over A and B of its own for them
+      st = launch_row_scales(h, rows_a, rows_b, nullptr, 0, kRowScaleClear);
+      if (st != ECGEMM_OK) return st;
+      fp16_a.row_max = scales_a;
+      fp16_b.row_max = scales_b;
+    }
+    st = launch_split(h, ECGEMM_MODE_FP16_SPLIT, fp16_a, &fp16_b, true);
+    if (st != ECGEMM_OK) return st;
+    // (operands with few rows: the first choice also turns the rows' exponents into factors, which saves a launch)
+    const bool finish_with_choice = try_scaled && M + N <= 4096;
+    const RowScaleJob no_rows{};
+    hipLaunchKernelGGL(choose_mode_kernel, dim3(1), dim3(1024), 0, h->stream, stats_a, fp16_a.blocks, (double)M, stats_b,
+                       fp16_b.blocks, (double)N, kAutoTolerance, kAutoMinTerms, choice, (int)kChoiceFp16,
+                       (int)(try_scaled ? kChoiceUndecided : kChoiceBf16), (const int*)nullptr, 0,
+                       finish_with_choice ? rows_a : no_rows, finish_with_choice ? rows_b : no_rows);
+    ECGEMM_HIP(h, hipGetLastError());
+    if (try_scaled) {
+      // the exponents are found on the operands as the caller passed them; the handle's global pre-scaling, a common
+      // factor of every row, comes on top in the split and is undone with the product's output scale
+      if (!finish_with_choice) {
+        st = launch_row_scales(h, rows_a, rows_b, choice, kChoiceUndecided, kRowScaleFinish);
+        if (st != ECGEMM_OK) return st;
+      }
+      st = launch_split(h, ECGEMM_MODE_FP16_SPLIT, scaled_a, &scaled_b, true);
+      if (st != ECGEMM_OK) return st;
+      hipLaunchKernelGGL(choose_mode_kernel, dim3(1), dim3(1024), 0, h->stream, stats_a, scaled_a.blocks, (double)M, stats_b,
+                         scaled_b.blocks, (double)N, kAutoTolerance, kAutoMinTerms, choice, (int)kChoiceFp16Scaled,
+                         (int)kChoiceBf16, (const int*)choice, (int)kChoiceUndecided, no_rows, no_rows);
+      ECGEMM_HIP(h, hipGetLastError());
+    }
+  }
   if (!bf16_one_launch) {
     st = launch_split(h, ECGEMM_MODE_BF16_FULL, bf16_a, &bf16_b);
     if (st != ECGEMM_OK) return st;

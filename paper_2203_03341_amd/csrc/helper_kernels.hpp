@@ -166,6 +166,16 @@ __global__ void __launch_bounds__(256, 1) mfma_rate_kernel(const unsigned short*
   sink[(int64_t)blockIdx.x * 256 + threadIdx.x] = s;
 }
 
+// The criterion of the automatic mode choice (see choose_mode_kernel) on the sums (err2, norm2, abs1) of A and of B.
+__device__ __forceinline__ bool choice_fits(const double* a, double rows_a, const double* b, double rows_b, double tolerance2,
+                                            double min_terms) {
+  const bool represented = a[0] <= tolerance2 * a[1] && b[0] <= tolerance2 * b[1];
+  // (sum |x|)^2 >= min_terms rows sum x^2, for either operand; an all-zero operand has nothing to lose
+  const bool spread = a[2] * a[2] >= min_terms * rows_a * a[1] || b[2] * b[2] >= min_terms * rows_b * b[1] ||
+                      a[1] == 0.0 || b[1] == 0.0;
+  return represented && spread;
+}
+
 // Automatic mode choice: from the blocks' statistics of both operands, *choice = if_fits or if_not.  It fits if
 //   * the FP16 pair represents both operands as they were split to within `tolerance`, relative, in the Frobenius
 //     norm, and
@@ -222,17 +232,163 @@ __global__ void __launch_bounds__(1024) choose_mode_kernel(const double* __restr
   if (threadIdx.x == 0) {
     const double* a = partial[0];      // err2, norm2, abs1 of A
     const double* b = partial[0] + kS;  // ... of B
-    const double t2 = tolerance * tolerance;
-    const bool represented = a[0] <= t2 * a[1] && b[0] <= t2 * b[1];
-    // (sum |x|)^2 >= min_terms rows sum x^2, for either operand; an all-zero operand has nothing to lose
-    const bool spread = a[2] * a[2] >= min_terms * rows_a * a[1] || b[2] * b[2] >= min_terms * rows_b * b[1] ||
-                        a[1] == 0.0 || b[1] == 0.0;
-    chosen = (represented && spread) ? if_fits : if_not;
+    chosen = choice_fits(a, rows_a, b, rows_b, tolerance * tolerance, min_terms) ? if_fits : if_not;
     *choice = chosen;
   }
   __syncthreads();
   if (chosen == if_not)
     for (int64_t i = threadIdx.x; i < finish_a.rows + finish_b.rows; i += kThreads) finish_row_scale(finish_a, finish_b, i);
+}
+
+// Automatic mode choice for products whose every candidate is a one-launch kernel: nothing reads packed operands then,
+// so this kernel only measures, both candidates of the FP16 mode in one pass.  A block owns kMeasureRows whole rows
+// of op(A) or op(B)^T (blocks 0 .. blocks_a - 1: A), so that it knows their largest exponents, and with them the
+// scaled candidate, without another launch.  It leaves the rows' scaling exponents and six sums (MeasureSums).
+// What bounds it is latency (a launch, one trip to memory, 40 vector instructions per element); the values of the
+// first 1024 k stay in registers between the two uses, deeper rows are read twice, the second time from the caches.
+// The rows of a block share cache lines with its neighbours' when r is contiguous: xcd_run_position.  Automatic mode,
+// 1024^3: 28.1 us a call against 33.9 with clearing, two measuring splits and two choices, five launches, before the
+// two products.
+constexpr int kMeasureRows = 8, kMeasureThreads = 64 * kMeasureRows;
+constexpr int kMeasureSums = 6;  // per block: err2, norm2, abs1 as they are (see SplitStats), then with the rows scaled
+struct MeasureJob {
+  const float* src;             // X(r, k) = src[r * row_stride + k * k_stride]
+  int64_t row_stride, k_stride;  // one of them is 1
+  int64_t rows, depth;
+  float prescale;               // the handle's power of two
+  int target;                   // where the scaled candidate puts the largest binade of a row (before prescale)
+  int* scale;                   // out: `rows` scaling exponents
+  double* sums;                 // out: kMeasureSums per block
+};
+
+// v - (v16 + dv16 2^-11) for finite v, every step exact where Splitter does not saturate; dv16 is cut at
+// +-65504 2^-11 as there.  (A value that is not finite shows in the sum of squares.)
+__device__ __forceinline__ float fp16_pair_loss(float v) {
+  const _Float16 hi = (_Float16)__builtin_amdgcn_fmed3f(v, -65504.0f, 65504.0f);
+  const float residual = v - (float)hi;
+  const _Float16 lo = (_Float16)(__builtin_amdgcn_fmed3f(residual, -0x1.ffcp+4f, 0x1.ffcp+4f) * 2048.0f);
+  return __builtin_fmaf((float)lo, -0x1p-11f, residual);
+}
+
+__global__ void __launch_bounds__(kMeasureThreads) measure_rows_kernel(const MeasureJob a, const MeasureJob b, unsigned blocks_a,
+                                                                       unsigned blocks_b) {
+  constexpr int kNone = -0x7fffffff - 1, kPerThread = 16, kChunk = 64 * kPerThread;
+  __shared__ int row_max[kMeasureRows];
+  __shared__ double partial[kMeasureRows][kMeasureSums];
+  const bool second = blockIdx.x >= blocks_a;  // block-uniform
+  const MeasureJob& job = second ? b : a;
+  const unsigned block = second ? xcd_run_position(blockIdx.x - blocks_a, blocks_b) : xcd_run_position(blockIdx.x, blocks_a);
+  const int t = threadIdx.x, wave = t >> 6;
+  // lanes along whichever index is contiguous; 64 threads per row, 64 apart in k, either way
+  const bool k_contiguous = job.k_stride == 1;
+  const int row = k_contiguous ? wave : t % kMeasureRows, k_first = k_contiguous ? (t & 63) : t / kMeasureRows;
+  const int64_t r = (int64_t)block * kMeasureRows + row, depth = job.depth;
+  const bool exists = r < job.rows;
+  const float* src = job.src + (exists ? r : 0) * job.row_stride;
+  auto fetch = [&](int64_t k0, float (&v)[kPerThread]) {
+#pragma unroll
+    for (int u = 0; u < kPerThread; ++u) {
+      const int64_t k = k0 + k_first + 64 * u;
+      v[u] = (exists && k < depth) ? src[k * job.k_stride] : 0.0f;
+    }
+  };
+  if (t < kMeasureRows) row_max[t] = kNone;
+  __syncthreads();
+  float kept[kPerThread];
+  int hi = kNone;
+  fetch(0, kept);
+#pragma unroll
+  for (int u = 0; u < kPerThread; ++u) hi = max(hi, finite_exponent(kept[u]));
+  for (int64_t k0 = kChunk; k0 < depth; k0 += kChunk) {
+    float v[kPerThread];
+    fetch(k0, v);
+#pragma unroll
+    for (int u = 0; u < kPerThread; ++u) hi = max(hi, finite_exponent(v[u]));
+  }
+#pragma unroll
+  for (int d = 32; d >= kMeasureRows; d >>= 1) hi = max(hi, __shfl_xor(hi, d, 64));
+  if (k_contiguous) {
+#pragma unroll
+    for (int d = kMeasureRows / 2; d >= 1; d >>= 1) hi = max(hi, __shfl_xor(hi, d, 64));
+  }
+  if ((t & 63) < (k_contiguous ? 1 : kMeasureRows)) atomicMax(&row_max[row], hi);
+  __syncthreads();
+  const int largest = row_max[row];
+  int e = largest == kNone ? 0 : job.target - largest;  // as finish_row_scale
+  e = e < -126 ? -126 : e > 126 ? 126 : e;
+  if (k_first == 0 && exists) job.scale[r] = e;
+
+  const float scaled = job.prescale * row_scale_factor(e);
+  double sums[kMeasureSums] = {};
+  auto add_value = [&](float x, double* to) {
+    const double x64 = (double)x, lost = (double)fp16_pair_loss(x);
+    to[0] += lost * lost;
+    to[1] += x64 * x64;
+    to[2] += __builtin_fabs(x64);
+  };
+  auto add = [&](const float (&v)[kPerThread]) {
+#pragma unroll
+    for (int u = 0; u < kPerThread; ++u) {
+      add_value(v[u] * job.prescale, sums);
+      add_value(v[u] * scaled, sums + kStatsPerBlock);
+    }
+  };
+  add(kept);
+  for (int64_t k0 = kChunk; k0 < depth; k0 += kChunk) {
+    float v[kPerThread];
+    fetch(k0, v);
+    add(v);
+  }
+  // an infinity or a NaN among the values (nothing else makes a sum of squares overflow 64 bits) is not represented
+  if (!(sums[1] <= 1.7976931348623157e308)) sums[0] = __builtin_nan("");
+  if (!(sums[kStatsPerBlock + 1] <= 1.7976931348623157e308)) sums[kStatsPerBlock] = __builtin_nan("");
+#pragma unroll
+  for (int q = 0; q < kMeasureSums; ++q) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) sums[q] += __shfl_xor(sums[q], d, 64);
+    if ((t & 63) == 0) partial[wave][q] = sums[q];
+  }
+  __syncthreads();
+  if (t < kMeasureSums) {
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < kMeasureRows; ++w) sum += partial[w][t];
+    job.sums[kMeasureSums * (size_t)block + t] = sum;
+  }
+}
+
+// The choice from what measure_rows_kernel left, by the criteria of choose_mode_kernel for either candidate: *choice =
+// if_fits, else if_fits_scaled, else if_not.  One block; every sum in a fixed order.
+__global__ void __launch_bounds__(256) choose_from_rows_kernel(const double* __restrict__ sums_a, unsigned blocks_a, double rows_a,
+                                                               const double* __restrict__ sums_b, unsigned blocks_b, double rows_b,
+                                                               double tolerance, double min_terms, int* __restrict__ choice,
+                                                               int if_fits, int if_fits_scaled, int if_not) {
+  __shared__ double partial[4][kMeasureSums];
+  const int t = threadIdx.x, wave = t >> 6;
+  const bool second = t >= 128;  // two waves per operand
+  const double* from = second ? sums_b : sums_a;
+  const unsigned blocks = second ? blocks_b : blocks_a;
+  double sums[kMeasureSums] = {};
+#pragma unroll 2
+  for (unsigned i = t & 127; i < blocks; i += 128)
+#pragma unroll
+    for (int q = 0; q < kMeasureSums; ++q) sums[q] += from[kMeasureSums * (size_t)i + q];
+#pragma unroll
+  for (int q = 0; q < kMeasureSums; ++q) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) sums[q] += __shfl_xor(sums[q], d, 64);
+    if ((t & 63) == 0) partial[wave][q] = sums[q];
+  }
+  __syncthreads();
+  if (t != 0) return;
+  const double t2 = tolerance * tolerance;
+  auto fits = [&](int at) {
+    double a[kStatsPerBlock], b[kStatsPerBlock];
+#pragma unroll
+    for (int q = 0; q < kStatsPerBlock; ++q) a[q] = partial[0][at + q] + partial[1][at + q], b[q] = partial[2][at + q] + partial[3][at + q];
+    return choice_fits(a, rows_a, b, rows_b, t2, min_terms);
+  };
+  *choice = fits(0) ? if_fits : fits(kStatsPerBlock) ? if_fits_scaled : if_not;
 }
 
 }  // namespace ecgemm

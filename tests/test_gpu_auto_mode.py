@@ -347,3 +347,35 @@ def test_one_captured_graph_takes_either_branch_depending_on_the_data():
         assert np.array_equal(got.view(np.uint32)[~np.isnan(got)], want.view(np.uint32)[~np.isnan(want)]), which
     del graph
     h.destroy()
+
+
+@pytest.mark.parametrize("K", [1, 63, 65, 1024, 1025, 2049])
+@pytest.mark.parametrize("M,N", [(1, 9), (8, 16), (7, 65), (129, 40)])
+def test_measuring_by_rows_at_its_edges(M, N, K):
+    """The choice of small products is measured by blocks of eight whole rows, 1024 k at a time: rows and depths around
+    those sizes in every storage order, each of the three outcomes, and an infinity or a NaN in the last element.  The
+    inputs sit far from the thresholds, as above, so the choice has to equal the oracle's."""
+    import paper_2203_03341_amd as ec
+    h = ec.Handle()
+    name = {(ec.MODE_FP16_SPLIT, False): "fp16", (ec.MODE_FP16_SPLIT, True): "fp16 scaled", (ec.MODE_BF16_FULL, False): "bf16"}
+    spread = (-110, 14)
+    for i, (transA, transB) in enumerate(("NN", "NT", "TN", "TT")):
+        for dist_a, dist_b in (("urand", "urand"), (TYPE3, TYPE1), (TYPE1, TYPE4), (spread, spread)):
+            A, B, C = _problem(transA, transB, M, N, K, dist_a, dist_b, K + i, i % 2)
+            for last in (None, np.inf, np.nan):
+                if last is not None and dist_a != "urand":
+                    continue
+                opA, opB = gemm.logical(transA, A, M, K), gemm.logical(transB, B, K, N)
+                if last is not None:
+                    A = A.copy(order="F")  # the last element of op(A)'s last row
+                    A[(M, K)[transA == "T"] - 1, (K, M)[transA == "T"] - 1] = last
+                want = "bf16" if last is not None else split.automatic_choice(opA, opB)
+                got = _run(h, h.sgemm, transA, transB, M, N, K, 1.0, A, B, 0.0, C, ec.MODE_AUTO)
+                chosen = h.auto_choice()
+                assert name[chosen] == want, (transA, transB, M, N, K, dist_a, dist_b, last, chosen)
+                if want == "fp16 scaled":
+                    direct, _, _ = _run_scaled(h, transA, transB, M, N, K, 1.0, A, B, 0.0, C)
+                else:
+                    direct = _run(h, h.sgemm, transA, transB, M, N, K, 1.0, A, B, 0.0, C, chosen[0])
+                assert np.array_equal(got.view(np.uint32), direct.view(np.uint32)), (transA, transB, M, N, K, dist_a, dist_b, last)
+    h.destroy()
