@@ -345,6 +345,18 @@ struct FusedOperand {
     }
   }
 
+  // The same for the last chunk where the depth ends inside it: k beyond the depth counts as zero, which the short split
+  // takes like any ordinary value (the general one cost as much as three whole chunks: 300 x 200 x 77 in BF16 mode,
+  // both operands transposed, takes 7.04 us against 7.36).
+  template <bool GENERAL>
+  __device__ __forceinline__ void deposit_last(const float (&x)[V], int c, char* region) const {
+    const int left = (int)(K - (int64_t)c * 64) - k_here;  // values of each row that lie inside the depth, from this thread's first on
+    float v[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = e % PER_ROW < left ? x[e] : 0.0f;
+    deposit_whole<GENERAL>(v, c, region);
+  }
+
   __device__ __forceinline__ void write(const unsigned (&words)[V / 2][NP], char* region) const {
     char* base = region + lds_offset[0];
     typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
@@ -459,8 +471,8 @@ __global__ void __launch_bounds__(fused_threads(TILE), 1) fused_kernel(const Fus
         });
       }
       // The last chunks, whose successors in the ring do not exist or are not whole: the same split for those that
-      // lie inside the depth, the general one for the last if it does not, and the general fetch for what is left to
-      // request.  (Every condition here is the same for the whole block, and every chunk still has its one barrier.)
+      // lie inside the depth, the same with zeros behind the depth for the last if it does not, and the general fetch
+      // for what is left to request.  (Every condition here is the same for the whole block, and every chunk still has its one barrier.)
       while (c0 < chunks) {
         static_for<kFusedRing>([&](auto r_c) {
           constexpr int r = decltype(r_c)::value;
@@ -471,8 +483,8 @@ __global__ void __launch_bounds__(fused_threads(TILE), 1) fused_kernel(const Fus
               a.template deposit_whole<GENERAL>(xa[r], c, stage);
               b.template deposit_whole<GENERAL>(xb[r], c, stage + REGION_BYTES);
             } else {
-              a.deposit(xa[r], c, stage);
-              b.deposit(xb[r], c, stage + REGION_BYTES);
+              a.template deposit_last<GENERAL>(xa[r], c, stage);
+              b.template deposit_last<GENERAL>(xb[r], c, stage + REGION_BYTES);
             }
             if (c + kFusedRing < chunks) a.fetch(xa[r], c + kFusedRing), b.fetch(xb[r], c + kFusedRing);
             __syncthreads();

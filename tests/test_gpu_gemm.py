@@ -569,6 +569,25 @@ def test_one_launch_shape_splits_like_the_split_kernels(mode, transA, transB, pa
 
 
 @pytest.mark.parametrize("mode", ["fp16", "bf16"])
+@pytest.mark.parametrize("K", [1, 63, 65, 68, 127, 129, 212])
+@pytest.mark.parametrize("transA,transB,pad", [("N", "N", 0), ("T", "N", 0), ("T", "T", 1), ("N", "T", 1)])
+def test_a_last_chunk_that_is_not_whole_splits_like_the_split_kernels(mode, K, transA, transB, pad):
+    """The one-launch shapes take a last chunk of fewer than 64 k by the short split, with zeros behind the depth, and
+    by the general one if it holds a value beyond the format's range: ordinary values, then such values in the last k
+    only.  Same terms in the same order in every shape, so the bits are those of the split-first shape."""
+    M, N = 70, 45
+    for awkward in (False, True):
+        A, B = _inputs(M, N, K, transA, transB, "urand", 17 + K, pad)
+        if awkward:
+            opA, opB = gemm.logical(transA, A, M, K), gemm.logical(transB, B, K, N)   # views: writes go to A and B
+            opA[3, K - 1], opA[M - 1, K - 1], opB[K - 1, 5], opB[K - 1, N - 1] = 70000.0, -np.inf, 3.39e38, 1e-41
+            opA[33, K - 1] = np.nan
+        outs = [_gpu_sgemm(transA, transB, M, N, K, 1.0, A, B, 0.0, None, mode, shape=sh)[:M, :N] for sh in ("x2", "fused", "fused32")]
+        for out in outs[1:]:
+            assert np.array_equal(outs[0].view(np.uint32), out.view(np.uint32)), awkward
+
+
+@pytest.mark.parametrize("mode", ["fp16", "bf16"])
 def test_one_launch_shape_with_leading_dimensions_beyond_32_bit_offsets(mode):
     """The loop that covers the bulk of the depth addresses a chunk's values with 32-bit offsets from the chunk's
     first value, which holds up to leading dimensions of 2^23; beyond, the kernel takes its general loop.  Operands
