@@ -70,60 +70,6 @@ struct FusedParams {
   int gate_value, gate_value_scaled;
 };
 
-// The split for values that need no care, two at a time (the two 16-bit results of a part share a register: out[q]
-// holds part q of v0 in its low half and of v1 in its high half).  It has none of Splitter's clamps and masks; on a
-// value whose high part comes out finite both give the same bits: the high part is then at most the largest finite
-// number of the format whether or not the value was clamped to it first, the residuals are at most half a unit of
-// its last place, far inside the range of the low parts, and nothing is masked.  A value that Splitter treats
-// differently (beyond the format's range, where it saturates; infinite; NaN) shows as a high part that is infinite or
-// NaN, which high_parts_finite() finds on the packed registers.
-typedef float fused_float2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 fused_half2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 fused_bf16x2_t __attribute__((ext_vector_type(2)));
-typedef unsigned short fused_ushort2_t __attribute__((ext_vector_type(2)));
-template <int KIND>
-struct FastSplit {
-  static constexpr int kParts = parts_of_split(KIND);
-  // `scaled0`, `scaled1`: the same two values times 2^11 (used by kSplitFp16Scaled only), so that the scaled residual
-  // is one fused multiply-add on the packed high part: hi * -2^11 + v * 2^11 = (v - hi) * 2^11, exact like the
-  // two-step form (v * 2^11 overflows only for values whose high part is not finite, which do not end up here).
-  __device__ static __forceinline__ void split2(float v0, float v1, float scaled0, float scaled1, unsigned (&out)[kParts]) {
-    if constexpr (!split_is_bf16(KIND)) {
-      const fused_half2_t hi = __builtin_convertvector(fused_float2_t{v0, v1}, fused_half2_t);
-      out[0] = __builtin_bit_cast(unsigned, hi);
-      if constexpr (KIND == kSplitFp16Scaled) {
-        // (each rounded to FP16 by itself: the multiply-add then delivers its result as one half of the register)
-        const fused_half2_t lo = {(_Float16)__builtin_fmaf((float)hi[0], -2048.0f, scaled0), (_Float16)__builtin_fmaf((float)hi[1], -2048.0f, scaled1)};
-        out[1] = __builtin_bit_cast(unsigned, lo);
-      } else if constexpr (kParts == 2) {
-        const fused_float2_t residual = {v0 - (float)hi[0], v1 - (float)hi[1]};  // exact
-        out[1] = __builtin_bit_cast(unsigned, __builtin_convertvector(residual, fused_half2_t));
-      }
-    } else {
-      const fused_bf16x2_t b0 = __builtin_convertvector(fused_float2_t{v0, v1}, fused_bf16x2_t);
-      out[0] = __builtin_bit_cast(unsigned, b0);
-      if constexpr (kParts == 3) {
-        const fused_float2_t r1 = {v0 - (float)b0[0], v1 - (float)b0[1]};
-        const fused_bf16x2_t b1 = __builtin_convertvector(r1, fused_bf16x2_t);
-        const fused_float2_t r2 = {r1[0] - (float)b1[0], r1[1] - (float)b1[1]};
-        out[1] = __builtin_bit_cast(unsigned, b1);
-        out[2] = __builtin_bit_cast(unsigned, __builtin_convertvector(r2, fused_bf16x2_t));
-      }
-    }
-  }
-  // true if none of the 2 W high parts in `words[..][0]` is infinite or NaN
-  template <int W>
-  __device__ static __forceinline__ bool high_parts_finite(const unsigned (&words)[W][kParts]) {
-    const unsigned magnitude = 0x7fff7fffu;
-    fused_ushort2_t most = {0, 0};
-#pragma unroll
-    for (int e = 0; e < W; ++e)
-      most = __builtin_elementwise_max(most, __builtin_bit_cast(fused_ushort2_t, words[e][0] & magnitude));
-    const unsigned short exponent_all_ones = split_is_bf16(KIND) ? 0x7f80 : 0x7c00;
-    return most[0] < exponent_all_ones && most[1] < exponent_all_ones;
-  }
-};
-
 // Where element (row, k) of a chunk lies in an operand's region of LDS, part 0 (bytes): fragment order, [row / 32]
 // [k step][part] blocks of 1 KiB, each two halves (k % 16 / 8) of 32 rows x 16 bytes, except that the rows of a half
 // are rotated by 2 (k step) + half places.  A fragment read takes a whole half either way.  The rotation is for
