@@ -411,6 +411,13 @@ ecgemm_status_t hip_fail(ecgemm_handle_t h, hipError_t e, const char* where) {
     if (e_ != hipSuccess) return hip_fail((h), e_, #call);    \
   } while (0)
 
+// Aligned operands with k contiguous, from this many blocks of four tiles on (four per unit): fewer and longer blocks
+// with four times the loads in flight.  Below, single tiles, which spread a small operand over the chip.  Whole calls
+// with single / four tiles, against the same reference: 4096^3 365.5 / 363.8 us (its two splits also fit one launch
+// then), 1024 x 1024 x 65536 0.994 / 0.987 of it; the automatic mode at 8192^3 reads a quarter of the statistics (its
+// two choices 20 / 11 us each).
+constexpr int64_t kSplitDeepBlocks = 1024;
+
 // X = op(src) is rows x depth.  op == N: X(r, k) = src[r + k * ld]; op == T: X(r, k) = src[k + r * ld].
 ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, int64_t depth, const float* src, int64_t ld,
                                void* packed, int log2_prescale, const int* row_log2_scale, SplitJob* job) {
@@ -431,12 +438,18 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
   job->gate = nullptr;
   job->gate_value = 0;
   job->row_max = nullptr;
+  job->k_tiles = 1;
   job->variant = k_contiguous ? (vec ? kSplitKContiguousVec : kSplitKContiguous) : (vec ? kSplitRContiguousWide : kSplitRContiguous);
   // blocks are 64 rows x 32 k, except 256 x 32 (wide) and 64 x 64 (k contiguous, unaligned)
   switch (job->variant) {
     case kSplitRContiguousWide: job->fast_tiles = (unsigned)(Rp / 256), job->blocks = (unsigned)(blocks64 / 4); break;
     case kSplitRContiguous: job->fast_tiles = (unsigned)(Rp / 64), job->blocks = (unsigned)blocks64; break;
-    case kSplitKContiguousVec: job->fast_tiles = (unsigned)(Kp / 32), job->blocks = (unsigned)blocks64; break;
+    case kSplitKContiguousVec:
+      // (four tiles a block where that still leaves every unit several blocks)
+      job->k_tiles = blocks64 / kSplitDeepTiles >= kSplitDeepBlocks ? kSplitDeepTiles : 1;
+      job->fast_tiles = (unsigned)((Kp + 32 * job->k_tiles - 1) / (32 * job->k_tiles));
+      job->blocks = (unsigned)(job->fast_tiles * (Rp / 64));
+      break;
     default: job->fast_tiles = (unsigned)((Kp + 63) / 64), job->blocks = (unsigned)((Kp + 63) / 64 * (Rp / 64)); break;
   }
   return ECGEMM_OK;

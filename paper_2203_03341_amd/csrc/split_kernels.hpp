@@ -231,6 +231,8 @@ __device__ __forceinline__ void store_fragment_row(unsigned short* __restrict__ 
   for (int p = 0; p < NP; ++p) *reinterpret_cast<ushort8_t*>(chunk + p * kChunkElems) = parts[p];
 }
 
+constexpr int kSplitDeepTiles = 4;
+
 // One operand to split: X = op(src), rows x depth, into `packed`.
 struct SplitJob {
   const float* src;
@@ -242,6 +244,7 @@ struct SplitJob {
   unsigned fast_tiles;        // tiles along the direction in which the blocks are numbered first
   unsigned blocks;
   int variant;                // SplitVariant
+  int k_tiles;                // kSplitKContiguousVec: 64 x 32 tiles per block, 1 or kSplitDeepTiles
   // Automatic mode choice only, else null: block b leaves its SplitStats at stats[kStatsPerBlock b ...]
   double* stats;
   // Automatic mode choice only, else null: the kernel does nothing unless *gate == gate_value
@@ -272,30 +275,51 @@ enum SplitVariant { kSplitKContiguousVec = 0, kSplitKContiguous = 1, kSplitRCont
 
 // Source with k contiguous, X(r, k) = src[k + r * ld], base and leading dimension multiples of 16 bytes.  One block:
 // 64 rows x 32 k, 256 threads, thread t handles row t / 4 and the 8 values starting at k = 8 * (t % 4), two 16-byte
-// loads.  Blocks are numbered with the k tile fastest.
-template <int KIND, bool STATS = false>
-__device__ __forceinline__ void split_block_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats = nullptr) {
+// loads; or job.k_tiles = kSplitDeepTiles such tiles next to each other in k, whose loads are all requested before the
+// first is split.  Blocks are numbered with k fastest.
+template <int KIND, int TILES, bool STATS = false>
+__device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats) {
   const int t = threadIdx.x;
   const int64_t r = (int64_t)(block / job.fast_tiles) * 64 + (t >> 2);
-  const int64_t k = (int64_t)(block % job.fast_tiles) * 32 + (t & 3) * 8;
+  const int64_t k0 = (int64_t)(block % job.fast_tiles) * (32 * TILES) + (t & 3) * 8;
   float prescale = job.prescale;
   if (job.row_log2_scale != nullptr && r < job.rows) prescale *= row_scale_factor(job.row_log2_scale[r]);
   const float* src = job.src;
-  float v[8];
-  if (r < job.rows && k + 8 <= job.depth) {
-    const float4 lo = *reinterpret_cast<const float4*>(src + r * job.ld + k);
-    const float4 hi = *reinterpret_cast<const float4*>(src + r * job.ld + k + 4);
-    v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
-    v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
-  } else {
+  float v[TILES][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (r < job.rows && k + e < job.depth) ? src[r * job.ld + k + e] : 0.0f;
+  for (int s = 0; s < TILES; ++s) {
+    const int64_t k = k0 + 32 * s;
+    if (r < job.rows && k + 8 <= job.depth) {
+      const float4 lo = *reinterpret_cast<const float4*>(src + r * job.ld + k);
+      const float4 hi = *reinterpret_cast<const float4*>(src + r * job.ld + k + 4);
+      v[s][0] = lo.x; v[s][1] = lo.y; v[s][2] = lo.z; v[s][3] = lo.w;
+      v[s][4] = hi.x; v[s][5] = hi.y; v[s][6] = hi.z; v[s][7] = hi.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[s][e] = (r < job.rows && k + e < job.depth) ? src[r * job.ld + k + e] : 0.0f;
+    }
   }
-  if constexpr (STATS)
-    if (job.row_max != nullptr) publish_row_exponent_of_4_lanes(job.row_max, r, r < job.rows, finite_exponent8(v));
+  if constexpr (STATS) {
+    if (job.row_max != nullptr) {
+      int hi = -0x7fffffff - 1;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] *= prescale;
-  store_fragment_row<KIND, STATS>(job.packed, job.k_steps_total, r, k, v, stats);
+      for (int s = 0; s < TILES; ++s) hi = max(hi, finite_exponent8(v[s]));
+      publish_row_exponent_of_4_lanes(job.row_max, r, r < job.rows, hi);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < TILES; ++s) {
+    const int64_t k = k0 + 32 * s;
+    if (TILES > 1 && k >= job.k_steps_total * 16) break;  // (the padded depth is a multiple of 32: the same for the block)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[s][e] *= prescale;
+    store_fragment_row<KIND, STATS>(job.packed, job.k_steps_total, r, k, v[s], stats);
+  }
+}
+template <int KIND, bool STATS = false>
+__device__ __forceinline__ void split_block_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats = nullptr) {
+  if (job.k_tiles == kSplitDeepTiles) split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, STATS>(job, block, stats);
+  else split_tiles_k_contiguous_vec<KIND, 1, STATS>(job, block, stats);
 }
 
 // Source with k contiguous, any alignment (rows that do not start on 16 bytes: lda = 5003).  One block: 64 rows x

@@ -135,3 +135,15 @@ def test_split_of_a_large_operand(mode_bf16):
         store = si.exp_rand(sr, sc, -30, 20, 9, si.ID_B)
         got = _run(op, store, rows, depth, mode_bf16)
         assert np.array_equal(got, _expected(op, store, rows, depth, mode_bf16))
+
+
+@pytest.mark.parametrize("mode_bf16", [False, True])
+@pytest.mark.parametrize("rows,depth", [(2048, 4064), (2048, 4096), (2048, 4100), (2040, 4148), (64, 131100)])
+def test_split_of_large_operands_with_the_depth_contiguous(mode_bf16, rows, depth):
+    """Aligned operands with k contiguous are split four 64 x 32 tiles a block from 1024 such blocks on: one depth below
+    that, depths of whole blocks and of one, two and four tiles in the last, a ragged one among them, rows that end
+    inside a block; a few values beyond the formats' range.  Bit for bit."""
+    store = si.exp_rand(depth, rows, -30, 20, 10, si.ID_B)
+    store[depth - 1, rows - 1], store[depth // 2, 3], store[5, rows // 2] = np.inf, 3.39e38, -70000.0
+    got = _run("T", store, rows, depth, mode_bf16)
+    assert np.array_equal(got, _expected("T", store, rows, depth, mode_bf16))
