@@ -293,7 +293,7 @@ struct FusedOperand {
 
   // The same for the last chunk where the depth ends inside it: k beyond the depth counts as zero, which the short split
   // takes like any ordinary value (the general one cost as much as three whole chunks: 300 x 200 x 77 in BF16 mode,
-  // both operands transposed, takes 7.04 us against 7.36).
+  // both operands transposed, takes 6.95 us against 7.36).
   template <bool GENERAL>
   __device__ __forceinline__ void deposit_last(const float (&x)[V], int c, char* region) const {
     const int left = (int)(K - (int64_t)c * 64) - k_here;  // values of each row that lie inside the depth, from this thread's first on
@@ -339,16 +339,12 @@ struct FusedOperand {
 constexpr int kFusedSliceChunks = 8;  // chunks of 64 per slice of the depth (see the multiplying waves)
 __host__ __device__ constexpr int fused_threads(int tile) { return 64 * (kFusedSplitWaves + (tile / 32) * (tile / 32)); }
 
+// Bytes of LDS of a block: two buffers of a chunk of both operands.
+__host__ __device__ constexpr int fused_lds_bytes(int method, int tile) { return 2 * 2 * (tile / 32) * 4 * parts_of_split(split_kind_of(method)) * 1024; }
+
+// One block (see the top of this file), on `lds`, fused_lds_bytes(METHOD, TILE) of it.
 template <int METHOD, int LAYOUT_A, int LAYOUT_B, int TILE>
-__global__ void __launch_bounds__(fused_threads(TILE), 1) fused_kernel(const FusedParams params) {
-  FusedParams p = params;
-  if (p.gate != nullptr) {  // the same for every thread of the grid, and before any barrier
-    const int choice = *p.gate;
-    if (choice == p.gate_value)
-      p.row_log2_scale = p.col_log2_scale = nullptr;
-    else if (choice != p.gate_value_scaled)
-      return;
-  }
+__device__ __forceinline__ void fused_block(FusedParams p, char* lds) {
   constexpr int KIND = split_kind_of(METHOD);
   constexpr bool BF16 = split_is_bf16(KIND);
   constexpr int NP = parts_of_split(KIND), PRODUCTS = products_of(METHOD);
@@ -358,7 +354,7 @@ __global__ void __launch_bounds__(fused_threads(TILE), 1) fused_kernel(const Fus
   constexpr int V = OperandA::V;
   constexpr int REGION_BYTES = OperandA::REGION_BYTES, STAGE_BYTES = 2 * REGION_BYTES;
   typedef typename Mfma<BF16 ? kElemBf16 : kElemFp16>::frag_t frag_t;
-  __shared__ __attribute__((aligned(1024))) char lds[2 * STAGE_BYTES];
+  static_assert(2 * STAGE_BYTES == fused_lds_bytes(METHOD, TILE), "LDS of a block");
 
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -425,7 +421,7 @@ __global__ void __launch_bounds__(fused_threads(TILE), 1) fused_kernel(const Fus
           const int c = c0 + r;
           if (c < chunks) {
             char* stage = lds + (r & 1) * STAGE_BYTES;
-            if (c < whole_chunks) {
+            if (__builtin_expect(c < whole_chunks, 1)) {
               a.template deposit_whole<GENERAL>(xa[r], c, stage);
               b.template deposit_whole<GENERAL>(xb[r], c, stage + REGION_BYTES);
             } else {
@@ -581,6 +577,35 @@ __global__ void __launch_bounds__(fused_threads(TILE), 1) fused_kernel(const Fus
       store_result(dst, (p.beta == 0.0f) ? p.alpha * c : scaled_sum(p.alpha, c, p.beta, *dst));
     }
   }
+}
+
+template <int METHOD, int LAYOUT_A, int LAYOUT_B, int TILE>
+__global__ void __launch_bounds__(fused_threads(TILE), 1) fused_kernel(const FusedParams params) {
+  FusedParams p = params;
+  if (p.gate != nullptr) {  // the same for every thread of the grid, and before any barrier
+    const int choice = *p.gate;
+    if (choice == p.gate_value)
+      p.row_log2_scale = p.col_log2_scale = nullptr;
+    else if (choice != p.gate_value_scaled)
+      return;
+  }
+  __shared__ __attribute__((aligned(1024))) char lds[fused_lds_bytes(METHOD, TILE)];
+  fused_block<METHOD, LAYOUT_A, LAYOUT_B, TILE>(p, lds);
+}
+
+// Automatic mode choice, where both modes' plans have the same tiles and slices: all three candidates in one launch,
+// the word at p.gate (always one of the three values) says which this is.  What it saves is a launch that would
+// return at once, and a second one for the reduction of plans in slices.
+template <int LAYOUT_A, int LAYOUT_B, int TILE>
+__global__ void __launch_bounds__(fused_threads(TILE), 1) fused_auto_kernel(const FusedParams params) {
+  FusedParams p = params;
+  const int choice = *p.gate;
+  if (choice != p.gate_value_scaled) p.row_log2_scale = p.col_log2_scale = nullptr;
+  __shared__ __attribute__((aligned(1024))) char lds[fused_lds_bytes(kMethodBf16Full, TILE)];
+  if (choice == p.gate_value || choice == p.gate_value_scaled)
+    fused_block<kMethodFp16Split, LAYOUT_A, LAYOUT_B, TILE>(p, lds);
+  else
+    fused_block<kMethodBf16Full, LAYOUT_A, LAYOUT_B, TILE>(p, lds);
 }
 
 }  // namespace ecgemm

@@ -57,6 +57,11 @@ typedef ProductConfig<kMethodFp32, 256, 128, 128, 64, 2, 3, 1> Fp32Config;
 #else
 #define ECGEMM_FUSED_GROUP extern
 #endif
+#ifdef ECGEMM_INSTANTIATE_FUSED_AUTO
+#define ECGEMM_FUSED_AUTO_GROUP
+#else
+#define ECGEMM_FUSED_AUTO_GROUP extern
+#endif
 #ifdef ECGEMM_INSTANTIATE_SPLIT
 #define ECGEMM_SPLIT_GROUP
 #else
@@ -99,6 +104,16 @@ ECGEMM_COMPARE_B_GROUP template __global__ void product_kernel<Fp32Config, false
   ECGEMM_FUSED_KERNELS_OF(METHOD, kFusedDepthVec, 32)
 ECGEMM_FUSED_KERNELS_OF_METHOD(kMethodFp16Split)
 ECGEMM_FUSED_KERNELS_OF_METHOD(kMethodBf16Full)
+#define ECGEMM_FUSED_AUTO_KERNELS_OF(LAYOUT_A, TILE)                                                                    \
+  ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<LAYOUT_A, kFusedRows, TILE>(const FusedParams);   \
+  ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<LAYOUT_A, kFusedDepth, TILE>(const FusedParams);  \
+  ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<LAYOUT_A, kFusedDepthVec, TILE>(const FusedParams);
+ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedRows, 64)
+ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepth, 64)
+ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepthVec, 64)
+ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedRows, 32)
+ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepth, 32)
+ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepthVec, 32)
 
 #define ECGEMM_SPLIT_KERNELS_OF(KIND)                                                                     \
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitKContiguousVec, false>(const SplitJob);   \
