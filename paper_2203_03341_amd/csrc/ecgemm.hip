@@ -425,6 +425,12 @@ ecgemm_status_t hip_fail(ecgemm_handle_t h, hipError_t e, const char* where) {
 // two choices 20 / 11 us each).
 constexpr int64_t kSplitDeepBlocks = 1024;
 
+// Operands from 256 MiB on, the size of the memory-side cache, are read past it (see load_source4).  Whole calls with
+// ordinary / non-temporal loads of the source: 1024 x 1024 x 65536 (two operands of 256 MiB) 524 / 512.5 us, but
+// 4096^3 (64 MiB) 356 / 360 us and 2048^3 57.5 / 61 us, whose operands a program's next read finds in the cache.  The
+// measuring splits, which read an operand twice, keep ordinary loads (8192^3: level).
+constexpr int64_t kSplitStreamedElems = 1ll << 26;
+
 // X = op(src) is rows x depth.  op == N: X(r, k) = src[r + k * ld]; op == T: X(r, k) = src[k + r * ld].
 ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, int64_t depth, const float* src, int64_t ld,
                                void* packed, int log2_prescale, const int* row_log2_scale, SplitJob* job) {
@@ -446,6 +452,7 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
   job->gate_value = 0;
   job->row_max = nullptr;
   job->k_tiles = 1;
+  job->streamed = rows * depth >= kSplitStreamedElems;
   job->variant = k_contiguous ? (vec ? kSplitKContiguousVec : kSplitKContiguous) : (vec ? kSplitRContiguousWide : kSplitRContiguous);
   // blocks are 64 rows x 32 k, except 256 x 32 (wide) and 64 x 64 (k contiguous, unaligned)
   switch (job->variant) {

@@ -244,6 +244,7 @@ struct SplitJob {
   unsigned fast_tiles;        // tiles along the direction in which the blocks are numbered first
   unsigned blocks;
   int variant;                // SplitVariant
+  bool streamed;              // 16-byte loads of the source are non-temporal (operands larger than the memory-side cache)
   int k_tiles;                // kSplitKContiguousVec: 64 x 32 tiles per block, 1 or kSplitDeepTiles
   // Automatic mode choice only, else null: block b leaves its SplitStats at stats[kStatsPerBlock b ...]
   double* stats;
@@ -273,11 +274,21 @@ __device__ __forceinline__ void store_block_stats(const SplitStats& mine, double
 }
 enum SplitVariant { kSplitKContiguousVec = 0, kSplitKContiguous = 1, kSplitRContiguous = 2, kSplitRContiguousWide = 3 };
 
+// Four values of the source.  STREAMED: non-temporal, so that an operand that is too large to be found in the
+// memory-side cache by anyone later does not push out of it what was just packed.
+template <bool STREAMED>
+__device__ __forceinline__ float4 load_source4(const float* from) {
+  typedef float vec4_t __attribute__((ext_vector_type(4)));
+  const vec4_t* at = reinterpret_cast<const vec4_t*>(from);
+  const vec4_t x = STREAMED ? __builtin_nontemporal_load(at) : *at;
+  return make_float4(x[0], x[1], x[2], x[3]);
+}
+
 // Source with k contiguous, X(r, k) = src[k + r * ld], base and leading dimension multiples of 16 bytes.  One block:
 // 64 rows x 32 k, 256 threads, thread t handles row t / 4 and the 8 values starting at k = 8 * (t % 4), two 16-byte
 // loads; or job.k_tiles = kSplitDeepTiles such tiles next to each other in k, whose loads are all requested before the
 // first is split.  Blocks are numbered with k fastest.
-template <int KIND, int TILES, bool STATS = false>
+template <int KIND, int TILES, bool STREAMED, bool STATS>
 __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats) {
   const int t = threadIdx.x;
   const int64_t r = (int64_t)(block / job.fast_tiles) * 64 + (t >> 2);
@@ -290,8 +301,7 @@ __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job
   for (int s = 0; s < TILES; ++s) {
     const int64_t k = k0 + 32 * s;
     if (r < job.rows && k + 8 <= job.depth) {
-      const float4 lo = *reinterpret_cast<const float4*>(src + r * job.ld + k);
-      const float4 hi = *reinterpret_cast<const float4*>(src + r * job.ld + k + 4);
+      const float4 lo = load_source4<STREAMED>(src + r * job.ld + k), hi = load_source4<STREAMED>(src + r * job.ld + k + 4);
       v[s][0] = lo.x; v[s][1] = lo.y; v[s][2] = lo.z; v[s][3] = lo.w;
       v[s][4] = hi.x; v[s][5] = hi.y; v[s][6] = hi.z; v[s][7] = hi.w;
     } else {
@@ -318,8 +328,17 @@ __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job
 }
 template <int KIND, bool STATS = false>
 __device__ __forceinline__ void split_block_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats = nullptr) {
-  if (job.k_tiles == kSplitDeepTiles) split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, STATS>(job, block, stats);
-  else split_tiles_k_contiguous_vec<KIND, 1, STATS>(job, block, stats);
+  if (job.k_tiles != kSplitDeepTiles) {
+    split_tiles_k_contiguous_vec<KIND, 1, false, STATS>(job, block, stats);
+  } else {
+    if constexpr (!STATS) {
+      if (job.streamed) {  // (large operands only: they always have blocks of this size)
+        split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, true, STATS>(job, block, stats);
+        return;
+      }
+    }
+    split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, false, STATS>(job, block, stats);
+  }
 }
 
 // Source with k contiguous, any alignment (rows that do not start on 16 bytes: lda = 5003).  One block: 64 rows x
@@ -385,8 +404,8 @@ __device__ __forceinline__ void split_block_r_contiguous(const SplitJob& job, un
 // 32 KiB of LDS (`tile`).  A wave reads one k line of 256 rows per instruction (1 KiB runs, 16 bytes per lane); after
 // the barrier thread t owns row t and picks its 8-value groups out of LDS along k (lanes on consecutive words: no bank
 // conflicts).  5.4 TB/s at 16384^2 against 3.9 TB/s for the 64-row kernel above.
-template <int KIND, bool STATS = false>
-__device__ __forceinline__ void split_block_r_contiguous_wide(const SplitJob& job, unsigned block, float* tile, SplitStats* stats = nullptr) {
+template <bool STREAMED>
+__device__ __forceinline__ void stage_r_contiguous_wide(const SplitJob& job, unsigned block, float* tile) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t r0 = (int64_t)(block % job.fast_tiles) * 256, k0 = (int64_t)(block / job.fast_tiles) * 32;
   const float* src = job.src;
@@ -397,7 +416,7 @@ __device__ __forceinline__ void split_block_r_contiguous_wide(const SplitJob& jo
     float4 x = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (k < job.depth) {
       if (r + 4 <= job.rows) {
-        x = *reinterpret_cast<const float4*>(src + r + k * job.ld);
+        x = load_source4<STREAMED>(src + r + k * job.ld);
       } else {
         if (r + 0 < job.rows) x.x = src[r + 0 + k * job.ld];
         if (r + 1 < job.rows) x.y = src[r + 1 + k * job.ld];
@@ -406,6 +425,13 @@ __device__ __forceinline__ void split_block_r_contiguous_wide(const SplitJob& jo
     }
     *reinterpret_cast<float4*>(&tile[kk * 256 + 4 * lane]) = x;
   }
+}
+template <int KIND, bool STATS = false>
+__device__ __forceinline__ void split_block_r_contiguous_wide(const SplitJob& job, unsigned block, float* tile, SplitStats* stats = nullptr) {
+  const int t = threadIdx.x;
+  const int64_t r0 = (int64_t)(block % job.fast_tiles) * 256, k0 = (int64_t)(block / job.fast_tiles) * 32;
+  if (!STATS && job.streamed) stage_r_contiguous_wide<true>(job, block, tile);
+  else stage_r_contiguous_wide<false>(job, block, tile);
   __syncthreads();
   float prescale = job.prescale;
   if (job.row_log2_scale != nullptr && r0 + t < job.rows) prescale *= row_scale_factor(job.row_log2_scale[r0 + t]);

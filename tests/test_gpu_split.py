@@ -147,3 +147,31 @@ def test_split_of_large_operands_with_the_depth_contiguous(mode_bf16, rows, dept
     store[depth - 1, rows - 1], store[depth // 2, 3], store[5, rows // 2] = np.inf, 3.39e38, -70000.0
     got = _run("T", store, rows, depth, mode_bf16)
     assert np.array_equal(got, _expected("T", store, rows, depth, mode_bf16))
+
+
+@pytest.mark.parametrize("mode_bf16", [False, True])
+@pytest.mark.parametrize("op", ["N", "T"])
+def test_split_of_operands_read_past_the_cache(op, mode_bf16):
+    """Aligned operands of 2^26 elements and more are read with non-temporal loads.  Row blocks are packed one after the
+    other, so the packed operand is the packed halves of its rows end to end, each of them split with ordinary loads
+    (which the tests above compare with the oracle)."""
+    import torch
+    import paper_2203_03341_amd as ec
+    rows, depth = 512, (1 << 17) + 4
+    mode = ec.MODE_BF16_FULL if mode_bf16 else ec.MODE_FP16_SPLIT
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    src = torch.randn((depth, rows) if op == "N" else (rows, depth), generator=gen, device="cuda")
+    h = ec.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+
+    def packed(first, count):
+        out = torch.empty(ec.split_size(count, depth, mode), dtype=torch.uint8, device="cuda")
+        part = src[:, first:] if op == "N" else src[first:]
+        h.split(ec.OP_N if op == "N" else ec.OP_T, count, depth, part, src.shape[1], mode, out)
+        return out
+
+    whole, halves = packed(0, rows), [packed(0, 256), packed(256, 256)]
+    torch.cuda.synchronize()
+    assert torch.equal(whole, torch.cat(halves))
+    h.destroy()
