@@ -1149,8 +1149,20 @@ struct EventLease {
 //   5. the FP16 product, the FP16 product that undoes the scaling vectors, the BF16 product: one of them runs
 enum AutoChoice { kChoiceFp16 = 0, kChoiceBf16 = 1, kChoiceFp16Scaled = 2, kChoiceUndecided = 3 };
 // Deepest product that is measured by rows (measure_rows_kernel): a block walks whole rows, 1024 k per round of loads,
-// twice, and its rows' number of blocks does not grow with the depth, while the measuring splits' does.
+// twice, and its rows' number of blocks does not grow with the depth, while the measuring splits' does.  Calls by rows /
+// by measuring splits, us: at 4096 deep 64 x 64 28.4 / 28.8, 256 x 256 32.9 / 30.9, 512 x 512 39.2 / 38.4, and where the
+// scaled candidate is needed, which costs the splits a second pass, 30.8 / 39.5, 37.0 / 42.9, 43.1 / 54.2; at 6144 deep
+// 33.8 / 29.6, 40.2 / 33.9, 51.4 / 49.0, and 36.3 / 42.8, 43.9 / 47.7, 54.8 / 64.7.
 constexpr int64_t kMeasureMaxDepth = 4096;
+// Rows per block of measure_rows_kernel.  Eight keep a small product's launch as wide as it gets.  From more than 256
+// such blocks on the chip is filled either way, and a block takes as many rows as leave all of its threads values (at
+// most 16 each): fewer blocks, fewer sums in 64 bits to add across lanes, and fewer sums for the choice.  Calls with
+// eight rows / with this rule, us: 16384 x 64 x 64 31.9 / 17.2, 8192 x 64 x 256 25.4 / 18.9, 16384 x 64 x 512 41.1 /
+// 32.2, 4096 x 256 x 64 18.6 / 15.2; more rows where few are: 1024 x 1024 x 128 15.5 / 16.7, 256 x 256 x 64 13.1 / 13.9.
+int measure_rows_per_block(int64_t M, int64_t N, int64_t K) {
+  if (M + N <= 2048) return 8;
+  return K <= 128 ? 64 : K <= 256 ? 32 : K <= 512 ? 16 : 8;
+}
 constexpr int kAutoScaleTarget = 14;  // where the scaled candidate puts the largest binade of every row and column
 
 ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t transB, int64_t M, int64_t N, int64_t K, float alpha,
@@ -1222,7 +1234,8 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
   if (fp16_one_launch && bf16_one_launch && try_scaled && K <= kMeasureMaxDepth) {
     // Nothing reads packed operands: both FP16 candidates are measured in one launch that writes none, the choice is
     // another (steps 1 to 3 in two launches instead of five).  The blocks' sums lie where the packed operands would.
-    const unsigned blocks_a = (unsigned)((M + kMeasureRows - 1) / kMeasureRows), blocks_b = (unsigned)((N + kMeasureRows - 1) / kMeasureRows);
+    const int rows_per_block = measure_rows_per_block(M, N, K);
+    const unsigned blocks_a = (unsigned)((M + rows_per_block - 1) / rows_per_block), blocks_b = (unsigned)((N + rows_per_block - 1) / rows_per_block);
     if (kMeasureSums * sizeof(double) * ((size_t)blocks_a + blocks_b) > ap.packed_bytes)
       return fail(h, ECGEMM_ERR_HIP, "ecgemm_sgemm: internal error, no room for the row statistics");
     double* sums_a = reinterpret_cast<double*>(ws);
@@ -1231,7 +1244,11 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
       return MeasureJob{rows.src, rows.k_contiguous ? rows.ld : 1, rows.k_contiguous ? 1 : rows.ld, rows.rows, K,
                         std::ldexp(1.0f, log2_prescale), rows.target, rows.scale, sums};
     };
-    hipLaunchKernelGGL(measure_rows_kernel, dim3(blocks_a + blocks_b), dim3(kMeasureThreads), 0, h->stream,
+    auto* measure = rows_per_block == 64   ? measure_rows_kernel<64>
+                    : rows_per_block == 32 ? measure_rows_kernel<32>
+                    : rows_per_block == 16 ? measure_rows_kernel<16>
+                                           : measure_rows_kernel<8>;
+    hipLaunchKernelGGL(measure, dim3(blocks_a + blocks_b), dim3(kMeasureThreads), 0, h->stream,
                        job_of(rows_a, h->log2_scale_a, sums_a), job_of(rows_b, h->log2_scale_b, sums_b), blocks_a, blocks_b);
     ECGEMM_HIP(h, hipGetLastError());
     hipLaunchKernelGGL(choose_from_rows_kernel, dim3(1), dim3(256), 0, h->stream, sums_a, blocks_a, (double)M, sums_b, blocks_b,

@@ -241,15 +241,15 @@ __global__ void __launch_bounds__(1024) choose_mode_kernel(const double* __restr
 }
 
 // Automatic mode choice for products whose every candidate is a one-launch kernel: nothing reads packed operands then,
-// so this kernel only measures, both candidates of the FP16 mode in one pass.  A block owns kMeasureRows whole rows
-// of op(A) or op(B)^T (blocks 0 .. blocks_a - 1: A), so that it knows their largest exponents, and with them the
-// scaled candidate, without another launch.  It leaves the rows' scaling exponents and six sums (MeasureSums).
+// so this kernel only measures, both candidates of the FP16 mode in one pass.  A block owns ROWS whole rows of op(A) or
+// op(B)^T (blocks 0 .. blocks_a - 1: A), so that it knows their largest exponents, and with them the scaled candidate,
+// without another launch.  It leaves the rows' scaling exponents and kMeasureSums sums.
 // What bounds it is latency (a launch, one trip to memory, 40 vector instructions per element); the values of the
-// first 1024 k stay in registers between the two uses, deeper rows are read twice, the second time from the caches.
+// first round stay in registers between the two uses, deeper rows are read twice, the second time from the caches.
 // The rows of a block share cache lines with its neighbours' when r is contiguous: xcd_run_position.  Automatic mode,
-// 1024^3: 28.1 us a call against 33.9 with clearing, two measuring splits and two choices, five launches, before the
-// two products.
-constexpr int kMeasureRows = 8, kMeasureThreads = 64 * kMeasureRows;
+// whole calls: 1024^3 25.2 us against 34.1 with clearing, two measuring splits and two choices, five launches, before
+// the products; 16384 x 64 x 64 17.2 against 32.
+constexpr int kMeasureThreads = 512;
 constexpr int kMeasureSums = 6;  // per block: err2, norm2, abs1 as they are (see SplitStats), then with the rows scaled
 struct MeasureJob {
   const float* src;             // X(r, k) = src[r * row_stride + k * k_stride]
@@ -270,29 +270,43 @@ __device__ __forceinline__ float fp16_pair_loss(float v) {
   return __builtin_fmaf((float)lo, -0x1p-11f, residual);
 }
 
+template <int ROWS>
 __global__ void __launch_bounds__(kMeasureThreads) measure_rows_kernel(const MeasureJob a, const MeasureJob b, unsigned blocks_a,
                                                                        unsigned blocks_b) {
-  constexpr int kNone = -0x7fffffff - 1, kPerThread = 16, kChunk = 64 * kPerThread;
-  __shared__ int row_max[kMeasureRows];
-  __shared__ double partial[kMeasureRows][kMeasureSums];
+  // kLanes threads per row, each with kPerThread values kLanes apart in k, kChunk values of a row at a time
+  constexpr int kNone = -0x7fffffff - 1, kPerThread = 16, kLanes = kMeasureThreads / ROWS, kChunk = kLanes * kPerThread;
+  static_assert(kLanes <= 64, "the threads of a row lie in one wave where k is contiguous");
+  __shared__ int row_max[ROWS];
+  __shared__ double partial[kMeasureThreads / 64][kMeasureSums];
   const bool second = blockIdx.x >= blocks_a;  // block-uniform
   const MeasureJob& job = second ? b : a;
   const unsigned block = second ? xcd_run_position(blockIdx.x - blocks_a, blocks_b) : xcd_run_position(blockIdx.x, blocks_a);
   const int t = threadIdx.x, wave = t >> 6;
-  // lanes along whichever index is contiguous; 64 threads per row, 64 apart in k, either way
+  // lanes along whichever index is contiguous
   const bool k_contiguous = job.k_stride == 1;
-  const int row = k_contiguous ? wave : t % kMeasureRows, k_first = k_contiguous ? (t & 63) : t / kMeasureRows;
-  const int64_t r = (int64_t)block * kMeasureRows + row, depth = job.depth;
+  const int row = k_contiguous ? t / kLanes : t % ROWS, k_first = k_contiguous ? t % kLanes : t / ROWS;
+  const int64_t r = (int64_t)block * ROWS + row, depth = job.depth;
   const bool exists = r < job.rows;
   const float* src = job.src + (exists ? r : 0) * job.row_stride;
+  // (a round that lies inside the depth without a condition; in the last one, what lies behind the depth for the whole
+  // block costs nothing)
   auto fetch = [&](int64_t k0, float (&v)[kPerThread]) {
+    const float* from = src + (k0 + k_first) * job.k_stride;
+    if (k0 + kChunk <= depth) {  // the same for the block
 #pragma unroll
-    for (int u = 0; u < kPerThread; ++u) {
-      const int64_t k = k0 + k_first + 64 * u;
-      v[u] = (exists && k < depth) ? src[k * job.k_stride] : 0.0f;
+      for (int u = 0; u < kPerThread; ++u) v[u] = from[(int64_t)(kLanes * u) * job.k_stride];
+#pragma unroll
+      for (int u = 0; u < kPerThread; ++u) v[u] = exists ? v[u] : 0.0f;
+    } else {
+#pragma unroll
+      for (int u = 0; u < kPerThread; ++u) {
+        v[u] = 0.0f;
+        if (k0 + kLanes * u < depth)  // the same for the block
+          if (exists && k0 + kLanes * u + k_first < depth) v[u] = from[(int64_t)(kLanes * u) * job.k_stride];
+      }
     }
   };
-  if (t < kMeasureRows) row_max[t] = kNone;
+  if (t < ROWS) row_max[t] = kNone;
   __syncthreads();
   float kept[kPerThread];
   int hi = kNone;
@@ -306,12 +320,9 @@ __global__ void __launch_bounds__(kMeasureThreads) measure_rows_kernel(const Mea
     for (int u = 0; u < kPerThread; ++u) hi = max(hi, finite_exponent(v[u]));
   }
 #pragma unroll
-  for (int d = 32; d >= kMeasureRows; d >>= 1) hi = max(hi, __shfl_xor(hi, d, 64));
-  if (k_contiguous) {
-#pragma unroll
-    for (int d = kMeasureRows / 2; d >= 1; d >>= 1) hi = max(hi, __shfl_xor(hi, d, 64));
-  }
-  if ((t & 63) < (k_contiguous ? 1 : kMeasureRows)) atomicMax(&row_max[row], hi);
+  for (int d = 32; d >= 1; d >>= 1)
+    if (k_contiguous ? d < kLanes : d >= ROWS) hi = max(hi, __shfl_xor(hi, d, 64));
+  if (k_contiguous ? k_first == 0 : (t & 63) < ROWS) atomicMax(&row_max[row], hi);
   __syncthreads();
   const int largest = row_max[row];
   int e = largest == kNone ? 0 : job.target - largest;  // as finish_row_scale
@@ -326,18 +337,20 @@ __global__ void __launch_bounds__(kMeasureThreads) measure_rows_kernel(const Mea
     to[1] += x64 * x64;
     to[2] += __builtin_fabs(x64);
   };
-  auto add = [&](const float (&v)[kPerThread]) {
+  auto add = [&](int64_t k0, const float (&v)[kPerThread]) {
+    const bool whole = k0 + kChunk <= depth;  // the same for the block
 #pragma unroll
     for (int u = 0; u < kPerThread; ++u) {
+      if (!whole && k0 + kLanes * u >= depth) break;  // only zeros from here on
       add_value(v[u] * job.prescale, sums);
       add_value(v[u] * scaled, sums + kStatsPerBlock);
     }
   };
-  add(kept);
+  add(0, kept);
   for (int64_t k0 = kChunk; k0 < depth; k0 += kChunk) {
     float v[kPerThread];
     fetch(k0, v);
-    add(v);
+    add(k0, v);
   }
   // an infinity or a NaN among the values (nothing else makes a sum of squares overflow 64 bits) is not represented
   if (!(sums[1] <= 1.7976931348623157e308)) sums[0] = __builtin_nan("");
@@ -352,7 +365,7 @@ __global__ void __launch_bounds__(kMeasureThreads) measure_rows_kernel(const Mea
   if (t < kMeasureSums) {
     double sum = 0.0;
 #pragma unroll
-    for (int w = 0; w < kMeasureRows; ++w) sum += partial[w][t];
+    for (int w = 0; w < kMeasureThreads / 64; ++w) sum += partial[w][t];
     job.sums[kMeasureSums * (size_t)block + t] = sum;
   }
 }

@@ -379,3 +379,64 @@ def test_measuring_by_rows_at_its_edges(M, N, K):
                     direct = _run(h, h.sgemm, transA, transB, M, N, K, 1.0, A, B, 0.0, C, chosen[0])
                 assert np.array_equal(got.view(np.uint32), direct.view(np.uint32)), (transA, transB, M, N, K, dist_a, dist_b, last)
     h.destroy()
+
+
+def _one_launch_in_both_modes(h, M, N, K):
+    import paper_2203_03341_amd as ec
+    return all(h.plan_info(M, N, K, mode)["shape"] >= ec.SHAPE_64x64_FUSED for mode in (ec.MODE_FP16_SPLIT, ec.MODE_BF16_FULL))
+
+
+@pytest.mark.parametrize("M,N,K", [(2048, 1, 1), (2111, 40, 63), (4096, 33, 128), (40, 2111, 129), (2049, 65, 256), (3000, 30, 257),
+                                   (2100, 64, 512), (2100, 64, 513)])
+def test_measuring_by_rows_of_many_rows(M, N, K):
+    """Operands of more than 2048 rows together are measured by 64, 32, 16 or 8 rows a block, by depth (up to 128, 256,
+    512, beyond): both sides of each depth, rows that end inside a block, every storage order, each of the outcomes."""
+    import paper_2203_03341_amd as ec
+    h = ec.Handle()
+    assert M + N > 2048 and _one_launch_in_both_modes(h, M, N, K)
+    name = {(ec.MODE_FP16_SPLIT, False): "fp16", (ec.MODE_FP16_SPLIT, True): "fp16 scaled", (ec.MODE_BF16_FULL, False): "bf16"}
+    for i, (transA, transB) in enumerate(("NN", "NT", "TN", "TT")):
+        for dist_a, dist_b, last in (("urand", "urand", None), (TYPE3, TYPE1, None), (TYPE1, TYPE4, None), ("urand", "urand", np.inf),
+                                     ("urand", "urand", np.nan)):
+            A, B, C = _problem(transA, transB, M, N, K, dist_a, dist_b, K + i, i % 2)
+            opA, opB = gemm.logical(transA, A, M, K), gemm.logical(transB, B, K, N)
+            if last is not None:
+                opA[M - 1, K - 1] = last  # a view: the write goes to A
+            want = "bf16" if last is not None else split.automatic_choice(opA, opB)
+            got = _run(h, h.sgemm, transA, transB, M, N, K, 1.0, A, B, 0.0, C, ec.MODE_AUTO)
+            chosen = h.auto_choice()
+            assert name[chosen] == want, (transA, transB, dist_a, dist_b, last, chosen)
+            if want == "fp16 scaled":
+                direct, _, _ = _run_scaled(h, transA, transB, M, N, K, 1.0, A, B, 0.0, C)
+            else:
+                direct = _run(h, h.sgemm, transA, transB, M, N, K, 1.0, A, B, 0.0, C, chosen[0])
+            assert np.array_equal(got.view(np.uint32), direct.view(np.uint32)), (transA, transB, dist_a, dist_b, last)
+    h.destroy()
+
+
+def test_measuring_costs_what_there_is_to_measure():
+    """A wide shallow product, one block of the product kernel per compute unit, against the smallest one: the launches
+    are the same and a million values are next to nothing, so measuring them must not show either (17 against 14 us;
+    39 with blocks that worked on 1024 k of every row whatever the depth)."""
+    import torch
+    import paper_2203_03341_amd as ec
+    h = ec.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+
+    def best_us(M, N, K):
+        assert _one_launch_in_both_modes(h, M, N, K)
+        A, B, C = (torch.rand(n, device="cuda") for n in (M * K, K * N, M * N))
+        calls = 200
+        def timed():
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(calls):
+                h.sgemm(ec.OP_N, ec.OP_N, M, N, K, 1.0, A, M, B, K, 0.0, C, M, ec.MODE_AUTO)
+            stop.record()
+            torch.cuda.synchronize()
+            return start.elapsed_time(stop) * 1e3 / calls
+        return min(timed() for _ in range(6))
+
+    best_us(64, 64, 64)
+    assert best_us(16384, 64, 64) < 1.8 * best_us(64, 64, 64)
+    h.destroy()
