@@ -418,17 +418,34 @@ ecgemm_status_t hip_fail(ecgemm_handle_t h, hipError_t e, const char* where) {
     if (e_ != hipSuccess) return hip_fail((h), e_, #call);    \
   } while (0)
 
-// Aligned operands with k contiguous, from this many blocks of four tiles on (four per unit): fewer and longer blocks
-// with four times the loads in flight.  Below, single tiles, which spread a small operand over the chip.  Whole calls
-// with single / four tiles, against the same reference: 4096^3 365.5 / 363.8 us (its two splits also fit one launch
-// then), 1024 x 1024 x 65536 0.994 / 0.987 of it; the automatic mode at 8192^3 reads a quarter of the statistics (its
-// two choices 20 / 11 us each).
-constexpr int64_t kSplitDeepBlocks = 1024;
+// Aligned operands with k contiguous: one 64 x 32 tile a block, or four (kSplitKContiguousVecDeep), fewer and longer
+// blocks with four times the loads in flight and twice the registers.  Four from 2^12 tiles on (2^23 elements, four
+// blocks of four per unit); below, single tiles, which spread a small operand over the chip.  Whole calls with single /
+// four tiles, us:
+//   * the measuring split, which leaves the choice sums per block to add up: automatic mode, 2048 x 2048 x 4096 135 / 125,
+//     8192^3 2607 / 2552 (its two choices 20 / 11 each)
+//   * two operands in one launch, whose 32 KiB of LDS leave fewer waves: FP16 8192 x 512 x 1024 41.9 / 39.2, 4096 x 512 x
+//     4096 73.5 / 74.5, 2048 x 2048 x 4096 102.0 / 103.5, 1024 x 1024 x 32768 264 / 259; BF16 512 x 8192 x 1024
+//     57.3 / 53.7; plain FP16 2048 x 2048 x 4096 57.0 / 55.1
+//   * one operand by itself: BF16 2048 x 8192 26.6 / 26.1 (the split alone), plain FP16 2048 x 4096 9.2 / 8.4; from 2^14
+//     tiles on it is the other way round until the loads go past the cache (below): 4096 x 8192 in FP16 40.4 / 42.8, in
+//     BF16 64.6 / 69.9
+//   * the same for FP32, which has nothing to convert: single throughout (2048 x 4096 11.6 / 12.9, 4096 x 8192 40.2 / 42.0)
+constexpr unsigned kSplitDeepFrom = 1 << 12, kSplitDeepAloneBelow = 1 << 14;  // in tiles
+void use_deep_blocks(SplitJob* job) {
+  const unsigned row_blocks = job->blocks / job->fast_tiles;
+  job->variant = kSplitKContiguousVecDeep;
+  job->fast_tiles = (job->fast_tiles + kSplitDeepTiles - 1) / kSplitDeepTiles;
+  job->blocks = job->fast_tiles * row_blocks;
+}
+bool large_k_contiguous(const SplitJob& job) { return job.variant == kSplitKContiguousVec && job.blocks >= kSplitDeepFrom; }
 
 // Operands from 256 MiB on, the size of the memory-side cache, are read past it (see load_source4).  Whole calls with
 // ordinary / non-temporal loads of the source: 1024 x 1024 x 65536 (two operands of 256 MiB) 524 / 512.5 us, but
 // 4096^3 (64 MiB) 356 / 360 us and 2048^3 57.5 / 61 us, whose operands a program's next read finds in the cache.  The
-// measuring splits, which read an operand twice, keep ordinary loads (8192^3: level).
+// measuring splits, which read an operand twice, keep ordinary loads (8192^3: level).  Two operands of 128 MiB, which
+// overflow the cache together: with k contiguous 4096 x 4096 x 8192 in FP16 mode 667 / 663, in BF16 mode 1144 / 1152,
+// 1024 x 1024 x 32768 253 / 254 and 392 / 399; with the rows contiguous 680 / 670 and 264 / 259.5.
 constexpr int64_t kSplitStreamedElems = 1ll << 26;
 
 // X = op(src) is rows x depth.  op == N: X(r, k) = src[r + k * ld]; op == T: X(r, k) = src[k + r * ld].
@@ -451,7 +468,6 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
   job->gate = nullptr;
   job->gate_value = 0;
   job->row_max = nullptr;
-  job->k_tiles = 1;
   job->streamed = rows * depth >= kSplitStreamedElems;
   job->variant = k_contiguous ? (vec ? kSplitKContiguousVec : kSplitKContiguous) : (vec ? kSplitRContiguousWide : kSplitRContiguous);
   // blocks are 64 rows x 32 k, except 256 x 32 (wide) and 64 x 64 (k contiguous, unaligned)
@@ -459,10 +475,8 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
     case kSplitRContiguousWide: job->fast_tiles = (unsigned)(Rp / 256), job->blocks = (unsigned)(blocks64 / 4); break;
     case kSplitRContiguous: job->fast_tiles = (unsigned)(Rp / 64), job->blocks = (unsigned)blocks64; break;
     case kSplitKContiguousVec:
-      // (four tiles a block where that still leaves every unit several blocks)
-      job->k_tiles = blocks64 / kSplitDeepTiles >= kSplitDeepBlocks ? kSplitDeepTiles : 1;
-      job->fast_tiles = (unsigned)((Kp + 32 * job->k_tiles - 1) / (32 * job->k_tiles));
-      job->blocks = (unsigned)(job->fast_tiles * (Rp / 64));
+      job->fast_tiles = (unsigned)(Kp / 32), job->blocks = (unsigned)blocks64;
+      if (job->streamed) use_deep_blocks(job);
       break;
     default: job->fast_tiles = (unsigned)((Kp + 63) / 64), job->blocks = (unsigned)((Kp + 63) / 64 * (Rp / 64)); break;
   }
@@ -476,17 +490,34 @@ void launch_split_job(hipStream_t stream, const SplitJob& job) {
     case kSplitRContiguousWide: hipLaunchKernelGGL((split_kernel<KIND, kSplitRContiguousWide, STATS>), grid, block, 0, stream, job); break;
     case kSplitRContiguous: hipLaunchKernelGGL((split_kernel<KIND, kSplitRContiguous, STATS>), grid, block, 0, stream, job); break;
     case kSplitKContiguousVec: hipLaunchKernelGGL((split_kernel<KIND, kSplitKContiguousVec, STATS>), grid, block, 0, stream, job); break;
+    case kSplitKContiguousVecDeep: hipLaunchKernelGGL((split_kernel<KIND, kSplitKContiguousVecDeep, STATS>), grid, block, 0, stream, job); break;
     default: hipLaunchKernelGGL((split_kernel<KIND, kSplitKContiguous, STATS>), grid, block, 0, stream, job); break;
   }
 }
 
+// (the measuring jobs' blocks are fixed by sgemm_auto: their statistics are counted by block)
 template <int KIND, bool STATS = false>
 void launch_split_kind(hipStream_t stream, const SplitJob& a, const SplitJob* b) {
-  if (b != nullptr && (uint64_t)a.blocks + b->blocks <= 8192) {  // small pairs go out as one launch
-    hipLaunchKernelGGL((split_pair_kernel<KIND, STATS>), dim3(a.blocks + b->blocks), dim3(256), 0, stream, a, *b);
-  } else {
-    launch_split_job<KIND, STATS>(stream, a);
-    if (b) launch_split_job<KIND, STATS>(stream, *b);
+  if (b != nullptr) {
+    SplitJob first = a, second = *b;
+    if (!STATS && large_k_contiguous(first)) use_deep_blocks(&first);
+    if (!STATS && large_k_contiguous(second)) use_deep_blocks(&second);
+    // one launch up to 2^26 elements in the aligned variants' large blocks (a quarter of that in small ones): in one /
+    // two launches 1024 x 1024 x 16384 136 / 139 us a call, 2048 x 2048 x 16384 391 / 406
+    if ((uint64_t)first.blocks + second.blocks <= 8192) {
+      const dim3 grid(first.blocks + second.blocks), block(256);
+      if (first.variant == kSplitKContiguousVecDeep || second.variant == kSplitKContiguousVecDeep)
+        hipLaunchKernelGGL((split_pair_kernel<KIND, true, STATS>), grid, block, 0, stream, first, second);
+      else
+        hipLaunchKernelGGL((split_pair_kernel<KIND, false, STATS>), grid, block, 0, stream, first, second);
+      return;
+    }
+  }
+  for (const SplitJob* given : {&a, b}) {
+    if (given == nullptr) break;
+    SplitJob job = *given;
+    if (!STATS && KIND != kSplitFp32 && large_k_contiguous(job) && job.blocks < kSplitDeepAloneBelow) use_deep_blocks(&job);
+    launch_split_job<KIND, STATS>(stream, job);
   }
 }
 
@@ -1201,6 +1232,9 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
   if (st != ECGEMM_OK) return st;
   st = make_split_job(h, op_b, N, K, B, ldb, ws + ap.bf16.a_bytes, h->log2_scale_b, nullptr, &bf16_b);
   if (st != ECGEMM_OK) return st;
+  // (the BF16 split too: where it is not wanted, its blocks return at once, and the fewer there are the better)
+  for (SplitJob* job : {&fp16_a, &fp16_b, &bf16_a, &bf16_b})
+    if (large_k_contiguous(*job)) use_deep_blocks(job);
   if (kStatsPerBlock * sizeof(double) * fp16_a.blocks > ap.stats_a_bytes ||
       kStatsPerBlock * sizeof(double) * fp16_b.blocks > ap.stats_b_bytes)
     return fail(h, ECGEMM_ERR_HIP, "ecgemm_sgemm: internal error, statistics array too small");

@@ -120,7 +120,9 @@ ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepthVec, 32)
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitKContiguous, false>(const SplitJob);      \
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitRContiguous, false>(const SplitJob);      \
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitRContiguousWide, false>(const SplitJob);  \
-  ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<KIND, false>(const SplitJob, const SplitJob);
+  ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitKContiguousVecDeep, false>(const SplitJob); \
+  ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<KIND, false, false>(const SplitJob, const SplitJob); \
+  ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<KIND, true, false>(const SplitJob, const SplitJob);
 ECGEMM_SPLIT_KERNELS_OF(kSplitFp16Scaled)
 ECGEMM_SPLIT_KERNELS_OF(kSplitBf16x3)
 ECGEMM_SPLIT_KERNELS_OF(kSplitFp16Unscaled)
@@ -133,6 +135,8 @@ ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSpli
 ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitKContiguous, true>(const SplitJob);
 ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitRContiguous, true>(const SplitJob);
 ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitRContiguousWide, true>(const SplitJob);
-ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<kSplitFp16Scaled, true>(const SplitJob, const SplitJob);
+ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitKContiguousVecDeep, true>(const SplitJob);
+ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<kSplitFp16Scaled, false, true>(const SplitJob, const SplitJob);
+ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<kSplitFp16Scaled, true, true>(const SplitJob, const SplitJob);
 
 }  // namespace ecgemm

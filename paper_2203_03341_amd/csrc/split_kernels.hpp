@@ -245,7 +245,6 @@ struct SplitJob {
   unsigned blocks;
   int variant;                // SplitVariant
   bool streamed;              // 16-byte loads of the source are non-temporal (operands larger than the memory-side cache)
-  int k_tiles;                // kSplitKContiguousVec: 64 x 32 tiles per block, 1 or kSplitDeepTiles
   // Automatic mode choice only, else null: block b leaves its SplitStats at stats[kStatsPerBlock b ...]
   double* stats;
   // Automatic mode choice only, else null: the kernel does nothing unless *gate == gate_value
@@ -272,7 +271,7 @@ __device__ __forceinline__ void store_block_stats(const SplitStats& mine, double
   if (threadIdx.x < kStatsPerBlock)
     out[threadIdx.x] = (scratch12[threadIdx.x] + scratch12[3 + threadIdx.x]) + (scratch12[6 + threadIdx.x] + scratch12[9 + threadIdx.x]);
 }
-enum SplitVariant { kSplitKContiguousVec = 0, kSplitKContiguous = 1, kSplitRContiguous = 2, kSplitRContiguousWide = 3 };
+enum SplitVariant { kSplitKContiguousVec = 0, kSplitKContiguous = 1, kSplitRContiguous = 2, kSplitRContiguousWide = 3, kSplitKContiguousVecDeep = 4 };
 
 // Four values of the source.  STREAMED: non-temporal, so that an operand that is too large to be found in the
 // memory-side cache by anyone later does not push out of it what was just packed.
@@ -286,8 +285,8 @@ __device__ __forceinline__ float4 load_source4(const float* from) {
 
 // Source with k contiguous, X(r, k) = src[k + r * ld], base and leading dimension multiples of 16 bytes.  One block:
 // 64 rows x 32 k, 256 threads, thread t handles row t / 4 and the 8 values starting at k = 8 * (t % 4), two 16-byte
-// loads; or job.k_tiles = kSplitDeepTiles such tiles next to each other in k, whose loads are all requested before the
-// first is split.  Blocks are numbered with k fastest.
+// loads; or TILES such tiles next to each other in k, whose loads are all requested before the first is split.  Blocks
+// are numbered with k fastest.
 template <int KIND, int TILES, bool STREAMED, bool STATS>
 __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats) {
   const int t = threadIdx.x;
@@ -326,19 +325,15 @@ __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job
     store_fragment_row<KIND, STATS>(job.packed, job.k_steps_total, r, k, v[s], stats);
   }
 }
+// (kernels of their own for one and for four tiles: four take 57 to 81 registers, one 20 to 33)
 template <int KIND, bool STATS = false>
 __device__ __forceinline__ void split_block_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats = nullptr) {
-  if (job.k_tiles != kSplitDeepTiles) {
-    split_tiles_k_contiguous_vec<KIND, 1, false, STATS>(job, block, stats);
-  } else {
-    if constexpr (!STATS) {
-      if (job.streamed) {  // (large operands only: they always have blocks of this size)
-        split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, true, STATS>(job, block, stats);
-        return;
-      }
-    }
-    split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, false, STATS>(job, block, stats);
-  }
+  split_tiles_k_contiguous_vec<KIND, 1, false, STATS>(job, block, stats);
+}
+template <int KIND, bool STATS = false>
+__device__ __forceinline__ void split_block_k_contiguous_vec_deep(const SplitJob& job, unsigned block, SplitStats* stats = nullptr) {
+  if (!STATS && job.streamed) split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, !STATS, STATS>(job, block, stats);
+  else split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, false, STATS>(job, block, stats);
 }
 
 // Source with k contiguous, any alignment (rows that do not start on 16 bytes: lda = 5003).  One block: 64 rows x
@@ -468,7 +463,7 @@ __device__ __forceinline__ bool gate_open(const int* gate, int gate_value) {
 }
 
 // One operand per launch; VARIANT is fixed at compile time so that only the kernels that stage through LDS hold any.
-// STATS (automatic mode choice): block b also leaves its SplitStats at job.stats[2 b], [2 b + 1].
+// STATS (automatic mode choice): block b also leaves its SplitStats at job.stats[kStatsPerBlock b ...].
 template <int KIND, int VARIANT, bool STATS = false>
 __global__ void __launch_bounds__(256) split_kernel(const SplitJob job) {
   if (!gate_open(job.gate, job.gate_value)) return;
@@ -480,6 +475,8 @@ __global__ void __launch_bounds__(256) split_kernel(const SplitJob job) {
     split_block_r_contiguous<KIND, STATS>(job, blockIdx.x, &stats);
   } else if constexpr (VARIANT == kSplitKContiguousVec) {
     split_block_k_contiguous_vec<KIND, STATS>(job, blockIdx.x, &stats);
+  } else if constexpr (VARIANT == kSplitKContiguousVecDeep) {
+    split_block_k_contiguous_vec_deep<KIND, STATS>(job, blockIdx.x, &stats);
   } else {
     __shared__ float tile[64 * 65];
     split_block_k_contiguous_staged<KIND, STATS>(job, xcd_run_position(blockIdx.x, job.blocks), tile, &stats);
@@ -491,9 +488,9 @@ __global__ void __launch_bounds__(256) split_kernel(const SplitJob job) {
   }
 }
 
-// Both operands of a product in one launch, for small operands where a launch costs more than the work: blocks
-// 0 .. a.blocks - 1 split A, the rest split B.
-template <int KIND, bool STATS = false>
+// Both operands of a product in one launch, for operands up to a size at which the second launch no longer shows: blocks
+// 0 .. a.blocks - 1 split A, the rest split B.  DEEP: kSplitKContiguousVecDeep may be among the variants.
+template <int KIND, bool DEEP, bool STATS = false>
 __global__ void __launch_bounds__(256) split_pair_kernel(const SplitJob a, const SplitJob b) {
   if (!gate_open(a.gate, a.gate_value)) return;
   __shared__ float tile[32 * 256];
@@ -501,11 +498,18 @@ __global__ void __launch_bounds__(256) split_pair_kernel(const SplitJob a, const
   const SplitJob& job = second ? b : a;
   const unsigned block = second ? blockIdx.x - a.blocks : blockIdx.x;
   SplitStats stats;
-  switch (job.variant) {
-    case kSplitRContiguousWide: split_block_r_contiguous_wide<KIND, STATS>(job, block, tile, &stats); break;
-    case kSplitRContiguous: split_block_r_contiguous<KIND, STATS>(job, block, &stats); break;
-    case kSplitKContiguousVec: split_block_k_contiguous_vec<KIND, STATS>(job, block, &stats); break;
-    default: split_block_k_contiguous_staged<KIND, STATS>(job, xcd_run_position(block, job.blocks), tile, &stats); break;
+  // (The order of the branches moves the measuring instance, whose code is larger than the instruction cache: automatic
+  // mode, 1024 x 1024 x 16384 NN, wide beside deep, 163.4 us in this order, 164 to 168 in five others.)
+  if (job.variant == kSplitRContiguous) {
+    split_block_r_contiguous<KIND, STATS>(job, block, &stats);
+  } else if (job.variant == kSplitKContiguous) {
+    split_block_k_contiguous_staged<KIND, STATS>(job, xcd_run_position(block, job.blocks), tile, &stats);
+  } else if (job.variant == kSplitKContiguousVec) {
+    split_block_k_contiguous_vec<KIND, STATS>(job, block, &stats);
+  } else if (DEEP && job.variant == kSplitKContiguousVecDeep) {
+    split_block_k_contiguous_vec_deep<KIND, STATS>(job, block, &stats);
+  } else {
+    split_block_r_contiguous_wide<KIND, STATS>(job, block, tile, &stats);
   }
   if constexpr (STATS) {
     __shared__ double sums[12];

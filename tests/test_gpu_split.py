@@ -175,3 +175,36 @@ def test_split_of_operands_read_past_the_cache(op, mode_bf16):
     torch.cuda.synchronize()
     assert torch.equal(whole, torch.cat(halves))
     h.destroy()
+
+
+@pytest.mark.parametrize("mode", ["fp16", "bf16", "plain", "fp32"])
+@pytest.mark.parametrize("transA,transB,M,N,K", [("T", "N", 8192, 300, 1028), ("T", "N", 2100, 2200, 4132), ("N", "N", 300, 2048, 4128),
+                                                 ("T", "T", 2048, 520, 4100), ("T", "N", 2048, 130, 4064), ("T", "N", 8200, 2048, 4096)])
+def test_both_operands_in_one_launch_or_two(mode, transA, transB, M, N, K):
+    """ecgemm_sgemm splits both operands in one launch while they are small enough, each in blocks of its own variant
+    (aligned with k contiguous: of one tile or of four, by size), and ecgemm_split one operand at a time: one of each,
+    two of four tiles, one beside the staged variant, depths that end inside a block of four, one pair beyond one launch.
+    The product of the operands split one by one has the same bits."""
+    import torch
+    import paper_2203_03341_amd as ec
+    mode = {"fp16": ec.MODE_FP16_SPLIT, "bf16": ec.MODE_BF16_FULL, "plain": ec.MODE_FP16_PLAIN, "fp32": ec.MODE_FP32_MFMA}[mode]
+    ops = {"N": ec.OP_N, "T": ec.OP_T}
+    h = ec.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+    if mode in (ec.MODE_FP16_SPLIT, ec.MODE_BF16_FULL):
+        h.set_shape(ec.SHAPE_128x128_X2)     # (never as one launch on the FP32 operands)
+    lda, ldb = M if transA == "N" else K, K if transB == "N" else N
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    A, B = torch.randn(M * K, generator=gen, device="cuda"), torch.randn(K * N, generator=gen, device="cuda")
+    whole, parts = torch.full((N, M), float("nan"), device="cuda"), torch.full((N, M), float("nan"), device="cuda")
+    h.sgemm(ops[transA], ops[transB], M, N, K, 1.0, A, lda, B, ldb, 0.0, whole, M, mode)
+    packed_a = torch.empty(ec.split_size(M, K, mode), dtype=torch.uint8, device="cuda")
+    packed_b = torch.empty(ec.split_size(N, K, mode), dtype=torch.uint8, device="cuda")
+    h.split(ops[transA], M, K, A, lda, mode, packed_a)
+    h.split(ec.OP_T if transB == "N" else ec.OP_N, N, K, B, ldb, mode, packed_b)
+    h.product(M, N, K, 1.0, packed_a, packed_b, 0.0, parts, M, mode)
+    torch.cuda.synchronize()
+    assert not bool(torch.isnan(whole).any())
+    assert torch.equal(whole, parts)
+    h.destroy()
