@@ -386,6 +386,28 @@ def _one_launch_in_both_modes(h, M, N, K):
     return all(h.plan_info(M, N, K, mode)["shape"] >= ec.SHAPE_64x64_FUSED for mode in (ec.MODE_FP16_SPLIT, ec.MODE_BF16_FULL))
 
 
+def _check_choice_and_bits(h, transA, transB, M, N, K, dist_a, dist_b, seed, pad, last=None):
+    """The choice against the oracle's and the result bit for bit against the direct calls'; `last`: the last element of
+    op(A)'s last row, which leaves only the full-range mode if it is an infinity or a NaN."""
+    import paper_2203_03341_amd as ec
+    name = {(ec.MODE_FP16_SPLIT, False): "fp16", (ec.MODE_FP16_SPLIT, True): "fp16 scaled", (ec.MODE_BF16_FULL, False): "bf16"}
+    A, B, C = _problem(transA, transB, M, N, K, dist_a, dist_b, seed, pad)
+    opA, opB = gemm.logical(transA, A, M, K), gemm.logical(transB, B, K, N)
+    if last is not None:
+        opA[M - 1, K - 1] = last  # a view: the write goes to A
+    want = "bf16" if last is not None else split.automatic_choice(opA, opB)
+    got = _run(h, h.sgemm, transA, transB, M, N, K, 1.0, A, B, 0.0, C, ec.MODE_AUTO)
+    chosen = h.auto_choice()
+    assert name[chosen] == want, (transA, transB, dist_a, dist_b, last, chosen)
+    if want == "fp16 scaled":
+        direct, sa, sb = _run_scaled(h, transA, transB, M, N, K, 1.0, A, B, 0.0, C)
+        assert np.array_equal(sa, split.row_scale_exponents(opA)) and np.array_equal(sb, split.row_scale_exponents(opB.T))
+    else:
+        direct = _run(h, h.sgemm, transA, transB, M, N, K, 1.0, A, B, 0.0, C, chosen[0])
+    assert np.array_equal(got.view(np.uint32), direct.view(np.uint32)), (transA, transB, dist_a, dist_b, last)
+    return want
+
+
 @pytest.mark.parametrize("M,N,K", [(2048, 1, 1), (2111, 40, 63), (4096, 33, 128), (40, 2111, 129), (2049, 65, 256), (3000, 30, 257),
                                    (2100, 64, 512), (2100, 64, 513)])
 def test_measuring_by_rows_of_many_rows(M, N, K):
@@ -394,23 +416,10 @@ def test_measuring_by_rows_of_many_rows(M, N, K):
     import paper_2203_03341_amd as ec
     h = ec.Handle()
     assert M + N > 2048 and _one_launch_in_both_modes(h, M, N, K)
-    name = {(ec.MODE_FP16_SPLIT, False): "fp16", (ec.MODE_FP16_SPLIT, True): "fp16 scaled", (ec.MODE_BF16_FULL, False): "bf16"}
     for i, (transA, transB) in enumerate(("NN", "NT", "TN", "TT")):
         for dist_a, dist_b, last in (("urand", "urand", None), (TYPE3, TYPE1, None), (TYPE1, TYPE4, None), ("urand", "urand", np.inf),
                                      ("urand", "urand", np.nan)):
-            A, B, C = _problem(transA, transB, M, N, K, dist_a, dist_b, K + i, i % 2)
-            opA, opB = gemm.logical(transA, A, M, K), gemm.logical(transB, B, K, N)
-            if last is not None:
-                opA[M - 1, K - 1] = last  # a view: the write goes to A
-            want = "bf16" if last is not None else split.automatic_choice(opA, opB)
-            got = _run(h, h.sgemm, transA, transB, M, N, K, 1.0, A, B, 0.0, C, ec.MODE_AUTO)
-            chosen = h.auto_choice()
-            assert name[chosen] == want, (transA, transB, dist_a, dist_b, last, chosen)
-            if want == "fp16 scaled":
-                direct, _, _ = _run_scaled(h, transA, transB, M, N, K, 1.0, A, B, 0.0, C)
-            else:
-                direct = _run(h, h.sgemm, transA, transB, M, N, K, 1.0, A, B, 0.0, C, chosen[0])
-            assert np.array_equal(got.view(np.uint32), direct.view(np.uint32)), (transA, transB, dist_a, dist_b, last)
+            _check_choice_and_bits(h, transA, transB, M, N, K, dist_a, dist_b, K + i, i % 2, last)
     h.destroy()
 
 
@@ -439,4 +448,35 @@ def test_measuring_costs_what_there_is_to_measure():
 
     best_us(64, 64, 64)
     assert best_us(16384, 64, 64) < 1.8 * best_us(64, 64, 64)
+    h.destroy()
+
+
+@pytest.mark.parametrize("transA,transB,pad", [("N", "N", 0), ("T", "T", 0), ("N", "T", 0), ("T", "N", 0), ("N", "T", 1), ("T", "N", 3)])
+def test_measuring_splits_of_every_variant(transA, transB, pad):
+    """Products that need packed operands are measured by their splits: every variant of the split kernel (both storage
+    orders, aligned and not), each of the outcomes, an infinity and a NaN in the last element."""
+    import paper_2203_03341_amd as ec
+    h = ec.Handle()
+    M, N, K = 1060, 1044, 196
+    assert h.plan_info(M, N, K, ec.MODE_FP16_SPLIT)["shape"] < ec.SHAPE_64x64_FUSED
+    chosen = [_check_choice_and_bits(h, transA, transB, M, N, K, dist_a, dist_b, 31 + i, pad, last)
+              for i, (dist_a, dist_b, last) in enumerate((("urand", "urand", None), (TYPE3, TYPE3, None), (TYPE4, TYPE1, None), (TYPE1, TYPE3, None),
+                                                          ("urand", "urand", np.inf), ("urand", "urand", np.nan)))]
+    assert chosen == ["fp16", "fp16 scaled", "fp16 scaled", "fp16 scaled", "bf16", "bf16"]
+    h.destroy()
+
+
+@pytest.mark.parametrize("transA,transB,M,N,K,pad", [("T", "N", 2048, 1000, 4132, 0), ("T", "N", 1000, 2050, 4128, 0),
+                                                     ("T", "N", 2048, 2048, 4100, 0), ("N", "T", 4100, 90, 4100, 1)])
+def test_measuring_splits_of_large_operands(transA, transB, M, N, K, pad):
+    """Aligned operands with k contiguous are measured in blocks of four 64 x 32 tiles from 4096 such tiles on: beside an
+    operand in single tiles on either side, and both; one and two tiles in the last block of a row; then an unaligned
+    operand with r contiguous that is too large to share a launch."""
+    import paper_2203_03341_amd as ec
+    h = ec.Handle()
+    tiles = lambda rows: (rows + 255) // 256 * 4 * ((K + 31) // 32)
+    assert max(tiles(M), tiles(N)) >= (4096 if pad == 0 else 8192) and (K + 31) // 32 % 4 in (1, 2)
+    chosen = [_check_choice_and_bits(h, transA, transB, M, N, K, dist_a, dist_b, 41 + i, pad, last)
+              for i, (dist_a, dist_b, last) in enumerate((("urand", "urand", None), (TYPE3, TYPE1, None), ("urand", "urand", np.nan)))]
+    assert chosen == ["fp16", "fp16 scaled", "bf16"]
     h.destroy()
