@@ -426,7 +426,8 @@ ecgemm_status_t hip_fail(ecgemm_handle_t h, hipError_t e, const char* where) {
 //     8192^3 2607 / 2552 (its two choices 20 / 11 each)
 //   * two operands in one launch, whose 32 KiB of LDS leave fewer waves: FP16 8192 x 512 x 1024 41.9 / 39.2, 4096 x 512 x
 //     4096 73.5 / 74.5, 2048 x 2048 x 4096 102.0 / 103.5, 1024 x 1024 x 32768 264 / 259; BF16 512 x 8192 x 1024
-//     57.3 / 53.7; plain FP16 2048 x 2048 x 4096 57.0 / 55.1
+//     57.3 / 53.7; plain FP16 2048 x 2048 x 4096 57.0 / 55.1; but not the unscaled FP16 pair, whose kernel then needs
+//     scratch (Markidis' method, 2048 x 1024 x 4096 79.8 / 82.6, 4096^3 413 / 418)
 //   * one operand by itself: BF16 2048 x 8192 26.6 / 26.1 (the split alone), plain FP16 2048 x 4096 9.2 / 8.4; from 2^14
 //     tiles on it is the other way round until the loads go past the cache (below): 4096 x 8192 in FP16 40.4 / 42.8, in
 //     BF16 64.6 / 69.9
@@ -500,14 +501,16 @@ template <int KIND, bool STATS = false>
 void launch_split_kind(hipStream_t stream, const SplitJob& a, const SplitJob* b) {
   if (b != nullptr) {
     SplitJob first = a, second = *b;
-    if (!STATS && large_k_contiguous(first)) use_deep_blocks(&first);
-    if (!STATS && large_k_contiguous(second)) use_deep_blocks(&second);
+    constexpr bool kDeep = KIND != kSplitFp16Unscaled;
+    if (kDeep && !STATS && large_k_contiguous(first)) use_deep_blocks(&first);
+    if (kDeep && !STATS && large_k_contiguous(second)) use_deep_blocks(&second);
     // one launch up to 2^26 elements in the aligned variants' large blocks (a quarter of that in small ones): in one /
     // two launches 1024 x 1024 x 16384 136 / 139 us a call, 2048 x 2048 x 16384 391 / 406
     if ((uint64_t)first.blocks + second.blocks <= 8192) {
       const dim3 grid(first.blocks + second.blocks), block(256);
-      if (first.variant == kSplitKContiguousVecDeep || second.variant == kSplitKContiguousVecDeep)
-        hipLaunchKernelGGL((split_pair_kernel<KIND, true, STATS>), grid, block, 0, stream, first, second);
+      // (an operand read past the cache is too large for this: without kDeep neither has such blocks)
+      if (kDeep && (first.variant == kSplitKContiguousVecDeep || second.variant == kSplitKContiguousVecDeep))
+        hipLaunchKernelGGL((split_pair_kernel<KIND, kDeep, STATS>), grid, block, 0, stream, first, second);
       else
         hipLaunchKernelGGL((split_pair_kernel<KIND, false, STATS>), grid, block, 0, stream, first, second);
       return;

@@ -177,7 +177,7 @@ def test_split_of_operands_read_past_the_cache(op, mode_bf16):
     h.destroy()
 
 
-@pytest.mark.parametrize("mode", ["fp16", "bf16", "plain", "fp32"])
+@pytest.mark.parametrize("mode", ["fp16", "bf16", "markidis", "plain", "fp32"])
 @pytest.mark.parametrize("transA,transB,M,N,K", [("T", "N", 8192, 300, 1028), ("T", "N", 2100, 2200, 4132), ("N", "N", 300, 2048, 4128),
                                                  ("T", "T", 2048, 520, 4100), ("T", "N", 2048, 130, 4064), ("T", "N", 8200, 2048, 4096)])
 def test_both_operands_in_one_launch_or_two(mode, transA, transB, M, N, K):
@@ -187,7 +187,8 @@ def test_both_operands_in_one_launch_or_two(mode, transA, transB, M, N, K):
     The product of the operands split one by one has the same bits."""
     import torch
     import paper_2203_03341_amd as ec
-    mode = {"fp16": ec.MODE_FP16_SPLIT, "bf16": ec.MODE_BF16_FULL, "plain": ec.MODE_FP16_PLAIN, "fp32": ec.MODE_FP32_MFMA}[mode]
+    mode = {"fp16": ec.MODE_FP16_SPLIT, "bf16": ec.MODE_BF16_FULL, "markidis": ec.MODE_FP16_MARKIDIS,
+            "plain": ec.MODE_FP16_PLAIN, "fp32": ec.MODE_FP32_MFMA}[mode]
     ops = {"N": ec.OP_N, "T": ec.OP_T}
     h = ec.Handle()
     h.set_stream(torch.cuda.current_stream().cuda_stream)
