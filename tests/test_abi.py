@@ -78,6 +78,21 @@ def test_product_path_does_not_touch_the_oracle():
                 assert "oracle" not in text.lower(), os.path.join(dirpath, f)
 
 
+def test_a_ragged_depth_is_not_estimated_beyond_the_next_whole_one():
+    """A one-launch block takes a last chunk of fewer than 64 k at the cost of a whole one where the depth is a multiple
+    of 4 (else an operand with the depth contiguous is not aligned, and it counts as more)."""
+    import paper_2203_03341_amd as ec
+    seen = 0
+    for mode in (ec.MODE_FP16_SPLIT, ec.MODE_BF16_FULL):
+        for (M, N) in [(64, 64), (300, 200), (512, 512), (1000, 1000), (4096, 128), (363, 2804)]:
+            for K in (4, 76, 100, 188, 332, 508, 824, 956):  # (from 1024 on the depth may be cut into slices)
+                ragged, whole = ec.plan_info(M, N, K, mode), ec.plan_info(M, N, -(-K // 64) * 64, mode)
+                if whole["shape"] >= ec.SHAPE_64x64_FUSED and ragged["shape"] >= ec.SHAPE_64x64_FUSED:
+                    assert ragged["estimated_us"] <= whole["estimated_us"], (mode, M, N, K)
+                    seen += 1
+    assert seen > 60
+
+
 def test_plan_of_the_baseline_configs():
     """Host logic: which kernel shape a problem gets, how its tiles become work items, how the kernel is launched."""
     import paper_2203_03341_amd as ec
