@@ -1270,7 +1270,6 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
   const Plan one_fp16 = make_plan(M, N, K, ECGEMM_MODE_FP16_SPLIT, h->shape, kOneLaunchSliced);
   const Plan one_bf16 = make_plan(M, N, K, ECGEMM_MODE_BF16_FULL, h->shape, kOneLaunchSliced);
   const bool fp16_one_launch = one_fp16.shape && one_fp16.shape->fused, bf16_one_launch = one_bf16.shape && one_bf16.shape->fused;
-  h->auto_choice = choice;
   if (fp16_one_launch && bf16_one_launch && try_scaled && K <= kMeasureMaxDepth) {
     // Nothing reads packed operands: both FP16 candidates are measured in one launch that writes none, the choice is
     // another (steps 1 to 3 in two launches instead of five).  The blocks' sums lie where the packed operands would.
@@ -1328,6 +1327,7 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
       ECGEMM_HIP(h, hipGetLastError());
     }
   }
+  h->auto_choice = choice;  // (what writes it is enqueued by now)
   if (!bf16_one_launch) {
     st = launch_split(h, ECGEMM_MODE_BF16_FULL, bf16_a, &bf16_b);
     if (st != ECGEMM_OK) return st;
