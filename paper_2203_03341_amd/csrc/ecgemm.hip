@@ -1336,8 +1336,11 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
   const int log2_out_scale = -(h->log2_scale_a + h->log2_scale_b);
   if (fp16_one_launch && bf16_one_launch && try_scaled && one_fp16.shape->bm == one_bf16.shape->bm &&
       one_fp16.tail_splits == one_bf16.tail_splits) {
-    // the two modes' plans differ in nothing but the kernel: one launch that looks at the choice (1024^3: 27.3 us a call
-    // against 28.9 with a launch for either mode)
+    // the two modes' plans differ in nothing but the kernel: one launch that looks at the choice.  Calls so / with a
+    // launch for either mode, NN: 1024^3 26.4 / 28.1 us, 512^3 17.9 / 19.4, 1024 x 1024 x 128 16.8 / 18.4, 512 x 512 x
+    // 4096 (slices) 40.7 / 44.5, and 4 to 10 % in every other order, aligned or not: also where both bodies in one kernel
+    // spill (64 x 64, an unaligned operand with the depth contiguous beside one with the rows contiguous: 28 vector
+    // registers at worst; 1024^3, odd leading dimensions, NN 31.1 / 32.8, TT 31.4 / 33.2).
     st = launch_fused(h, one_fp16, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, scales_a, scales_b, partials, choice,
                       kChoiceFp16, kChoiceFp16Scaled, one_fp16.shape->bm == 64 ? &kFusedAutoTile64 : &kFusedAutoTile32);
   } else {

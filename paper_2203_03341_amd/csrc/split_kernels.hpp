@@ -191,7 +191,9 @@ __device__ __forceinline__ void store_fragment_row(unsigned short* __restrict__ 
   // The short split where every value of the wave is ordinary: 4 vector instructions per element against about 20, which
   // operands that come from the caches and the measuring split (with its sums in 64 bits) wait for.  Whole calls with
   // the general one throughout / with this: FP16 2048^3 58.4 / 57.2 us, 1024 x 1024 x 65536 527 / 523 us, the automatic
-  // mode at 8192^3 on a wide range (two measuring splits) 2707 / 2679 us; the others within 0.3 %.
+  // mode at 8192^3 on a wide range (two measuring splits) 2707 / 2679 us; the others within 0.3 %.  A wave that does hold
+  // a value beyond the format pays for both: a 2048 x 2048 operand full of them, split by itself, 5.8 / 6.3 us, and the
+  // product of it, 2048^3, 51.6 / 50.8 with the rest of the call.
   constexpr bool kShort = (KIND == kSplitFp16Scaled || KIND == kSplitBf16x3);
   bool done = false;
   if constexpr (kShort) {
