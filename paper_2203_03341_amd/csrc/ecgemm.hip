@@ -432,10 +432,9 @@ ecgemm_status_t hip_fail(ecgemm_handle_t h, hipError_t e, const char* where) {
 //     57.3 / 53.7; plain FP16 2048 x 2048 x 4096 57.0 / 55.1; but not the unscaled FP16 pair, whose kernel then needs
 //     scratch (Markidis' method, 2048 x 1024 x 4096 79.8 / 82.6, 4096^3 413 / 418)
 //   * one operand by itself: BF16 2048 x 8192 26.6 / 26.1 (the split alone), plain FP16 2048 x 4096 9.2 / 8.4; from 2^14
-//     tiles on it is the other way round until the loads go past the cache (below): 4096 x 8192 in FP16 40.4 / 42.8, in
-//     BF16 64.6 / 69.9
+//     tiles on it is the other way round up to 2^15: 4096 x 8192 in FP16 40.4 / 42.8, in BF16 64.6 / 69.9
 //   * the same for FP32, which has nothing to convert: single throughout (2048 x 4096 11.6 / 12.9, 4096 x 8192 40.2 / 42.0)
-constexpr unsigned kSplitDeepFrom = 1 << 12, kSplitDeepAloneBelow = 1 << 14;  // in tiles
+constexpr unsigned kSplitDeepFrom = 1 << 12, kSplitDeepAloneBelow = 1 << 14, kSplitDeepAloneAgain = 1 << 15;  // in tiles
 void use_deep_blocks(SplitJob* job) {
   const unsigned row_blocks = job->blocks / job->fast_tiles;
   job->variant = kSplitKContiguousVecDeep;
@@ -444,12 +443,14 @@ void use_deep_blocks(SplitJob* job) {
 }
 bool large_k_contiguous(const SplitJob& job) { return job.variant == kSplitKContiguousVec && job.blocks >= kSplitDeepFrom; }
 
-// Operands from 256 MiB on, the size of the memory-side cache, are read past it (see load_source4).  Whole calls with
-// ordinary / non-temporal loads of the source: 1024 x 1024 x 65536 (two operands of 256 MiB) 524 / 512.5 us, but
-// 4096^3 (64 MiB) 356 / 360 us and 2048^3 57.5 / 61 us, whose operands a program's next read finds in the cache.  The
-// measuring splits, which read an operand twice, keep ordinary loads (8192^3: level).  Two operands of 128 MiB, which
-// overflow the cache together: with k contiguous 4096 x 4096 x 8192 in FP16 mode 667 / 663, in BF16 mode 1144 / 1152,
-// 1024 x 1024 x 32768 253 / 254 and 392 / 399; with the rows contiguous 680 / 670 and 264 / 259.5.
+// Operands from 256 MiB on, the size of the memory-side cache, with the rows contiguous are read past it (see
+// load_source4).  Whole calls with ordinary / non-temporal loads of the source: 4096 x 1024 x 16384 449 / 443.7 us,
+// 1024 x 1024 x 65536 517 / 513, 1920 x 1024 x 62912 907 / 911; below that size 4096^3 (64 MiB) 356 / 360 and 2048^3
+// 57.5 / 61, whose operands a program's next read finds in the cache; two operands of 128 MiB, 4096 x 4096 x 8192,
+// 680 / 670.  With the depth contiguous ordinary loads always: a row that does not start on a cache line shares its lines
+// with the next block's, which would fetch them again (9000 x 1024 x 9000 534 / 571, the split alone 129 / 167), and on
+// whole lines they gain nothing (8192 x 1024 x 9024 448 / 458, 1024 x 1024 x 65536 507 / 506).  The measuring splits,
+// which read an operand twice, keep ordinary loads (8192^3: level).
 constexpr int64_t kSplitStreamedElems = 1ll << 26;
 
 // X = op(src) is rows x depth.  op == N: X(r, k) = src[r + k * ld]; op == T: X(r, k) = src[k + r * ld].
@@ -472,7 +473,7 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
   job->gate = nullptr;
   job->gate_value = 0;
   job->row_max = nullptr;
-  job->streamed = rows * depth >= kSplitStreamedElems;
+  job->streamed = rows * depth >= kSplitStreamedElems;  // (kSplitRContiguousWide)
   job->variant = k_contiguous ? (vec ? kSplitKContiguousVec : kSplitKContiguous) : (vec ? kSplitRContiguousWide : kSplitRContiguous);
   // blocks are 64 rows x 32 k, except 256 x 32 (wide) and 64 x 64 (k contiguous, unaligned)
   switch (job->variant) {
@@ -480,7 +481,7 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
     case kSplitRContiguous: job->fast_tiles = (unsigned)(Rp / 64), job->blocks = (unsigned)blocks64; break;
     case kSplitKContiguousVec:
       job->fast_tiles = (unsigned)(Kp / 32), job->blocks = (unsigned)blocks64;
-      if (job->streamed) use_deep_blocks(job);
+      if (blocks64 >= kSplitDeepAloneAgain) use_deep_blocks(job);
       break;
     default: job->fast_tiles = (unsigned)((Kp + 63) / 64), job->blocks = (unsigned)((Kp + 63) / 64 * (Rp / 64)); break;
   }
@@ -511,7 +512,7 @@ void launch_split_kind(hipStream_t stream, const SplitJob& a, const SplitJob* b)
     // two launches 1024 x 1024 x 16384 136 / 139 us a call, 2048 x 2048 x 16384 391 / 406
     if ((uint64_t)first.blocks + second.blocks <= 8192) {
       const dim3 grid(first.blocks + second.blocks), block(256);
-      // (an operand read past the cache is too large for this: without kDeep neither has such blocks)
+      // (an operand that always has such blocks is too large for this: without kDeep neither has them)
       if (kDeep && (first.variant == kSplitKContiguousVecDeep || second.variant == kSplitKContiguousVecDeep))
         hipLaunchKernelGGL((split_pair_kernel<KIND, kDeep, STATS>), grid, block, 0, stream, first, second);
       else

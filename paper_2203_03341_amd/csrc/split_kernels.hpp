@@ -246,7 +246,7 @@ struct SplitJob {
   unsigned fast_tiles;        // tiles along the direction in which the blocks are numbered first
   unsigned blocks;
   int variant;                // SplitVariant
-  bool streamed;              // 16-byte loads of the source are non-temporal (operands larger than the memory-side cache)
+  bool streamed;              // kSplitRContiguousWide: non-temporal loads of the source (operands larger than the memory-side cache)
   // Automatic mode choice only, else null: block b leaves its SplitStats at stats[kStatsPerBlock b ...]
   double* stats;
   // Automatic mode choice only, else null: the kernel does nothing unless *gate == gate_value
@@ -289,7 +289,7 @@ __device__ __forceinline__ float4 load_source4(const float* from) {
 // 64 rows x 32 k, 256 threads, thread t handles row t / 4 and the 8 values starting at k = 8 * (t % 4), two 16-byte
 // loads; or TILES such tiles next to each other in k, whose loads are all requested before the first is split.  Blocks
 // are numbered with k fastest.
-template <int KIND, int TILES, bool STREAMED, bool STATS>
+template <int KIND, int TILES, bool STATS>
 __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats) {
   const int t = threadIdx.x;
   const int64_t r = (int64_t)(block / job.fast_tiles) * 64 + (t >> 2);
@@ -302,7 +302,7 @@ __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job
   for (int s = 0; s < TILES; ++s) {
     const int64_t k = k0 + 32 * s;
     if (r < job.rows && k + 8 <= job.depth) {
-      const float4 lo = load_source4<STREAMED>(src + r * job.ld + k), hi = load_source4<STREAMED>(src + r * job.ld + k + 4);
+      const float4 lo = load_source4<false>(src + r * job.ld + k), hi = load_source4<false>(src + r * job.ld + k + 4);
       v[s][0] = lo.x; v[s][1] = lo.y; v[s][2] = lo.z; v[s][3] = lo.w;
       v[s][4] = hi.x; v[s][5] = hi.y; v[s][6] = hi.z; v[s][7] = hi.w;
     } else {
@@ -327,15 +327,14 @@ __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job
     store_fragment_row<KIND, STATS>(job.packed, job.k_steps_total, r, k, v[s], stats);
   }
 }
-// (kernels of their own for one and for four tiles: four take 57 to 81 registers, one 20 to 33)
+// (kernels of their own for one and for four tiles: four take 50 to 81 registers, one 20 to 33)
 template <int KIND, bool STATS = false>
 __device__ __forceinline__ void split_block_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats = nullptr) {
-  split_tiles_k_contiguous_vec<KIND, 1, false, STATS>(job, block, stats);
+  split_tiles_k_contiguous_vec<KIND, 1, STATS>(job, block, stats);
 }
 template <int KIND, bool STATS = false>
 __device__ __forceinline__ void split_block_k_contiguous_vec_deep(const SplitJob& job, unsigned block, SplitStats* stats = nullptr) {
-  if (!STATS && job.streamed) split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, !STATS, STATS>(job, block, stats);
-  else split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, false, STATS>(job, block, stats);
+  split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, STATS>(job, block, stats);
 }
 
 // Source with k contiguous, any alignment (rows that do not start on 16 bytes: lda = 5003).  One block: 64 rows x

@@ -152,7 +152,7 @@ def test_split_of_large_operands_with_the_depth_contiguous(mode_bf16, rows, dept
 @pytest.mark.parametrize("mode_bf16", [False, True])
 @pytest.mark.parametrize("op", ["N", "T"])
 def test_split_of_operands_read_past_the_cache(op, mode_bf16):
-    """Aligned operands of 2^26 elements and more are read with non-temporal loads.  Row blocks are packed one after the
+    """Aligned operands of 2^26 elements and more with the rows contiguous are read with non-temporal loads.  Row blocks are packed one after the
     other, so the packed operand is the packed halves of its rows end to end, each of them split with ordinary loads
     (which the tests above compare with the oracle)."""
     import torch
@@ -208,4 +208,33 @@ def test_both_operands_in_one_launch_or_two(mode, transA, transB, M, N, K):
     torch.cuda.synchronize()
     assert not bool(torch.isnan(whole).any())
     assert torch.equal(whole, parts)
+    h.destroy()
+
+
+def test_a_leading_dimension_off_the_cache_lines_is_not_fetched_twice():
+    """The same large operand with the depth contiguous, its rows on whole cache lines (leading dimension 9024) and not
+    (9000, still a multiple of 16 bytes): neighbouring blocks share lines in the second, which one of them then finds in a
+    cache (118 us against 117; 167 with loads that went past the caches)."""
+    import torch
+    import paper_2203_03341_amd as ec
+    rows = depth = 9000
+    h = ec.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+    src = torch.rand(rows * 9024, device="cuda")
+    packed = torch.empty(ec.split_size(rows, depth, ec.MODE_FP16_SPLIT), dtype=torch.uint8, device="cuda")
+
+    def best_us(ld):
+        def timed():
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(20):
+                h.split(ec.OP_T, rows, depth, src, ld, ec.MODE_FP16_SPLIT, packed)
+            stop.record()
+            torch.cuda.synchronize()
+            return start.elapsed_time(stop) * 1e3 / 20
+        return min(timed() for _ in range(6))
+
+    best_us(9024)
+    whole, shared = best_us(9024), best_us(9000)
+    assert shared < 1.2 * whole, (whole, shared)
     h.destroy()
