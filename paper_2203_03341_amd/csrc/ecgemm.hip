@@ -421,36 +421,25 @@ ecgemm_status_t hip_fail(ecgemm_handle_t h, hipError_t e, const char* where) {
     if (e_ != hipSuccess) return hip_fail((h), e_, #call);    \
   } while (0)
 
-// Aligned operands with k contiguous: one 64 x 32 tile a block, or four (kSplitKContiguousVecDeep), fewer and longer
-// blocks with four times the loads in flight and twice the registers.  Four from 2^12 tiles on (2^23 elements, four
-// blocks of four per unit); below, single tiles, which spread a small operand over the chip.  Whole calls with single /
-// four tiles, us:
-//   * the measuring split, which leaves the choice sums per block to add up: automatic mode, 2048 x 2048 x 4096 135 / 125,
-//     8192^3 2607 / 2552 (its two choices 20 / 11 each)
-//   * two operands in one launch, whose 32 KiB of LDS leave fewer waves: FP16 8192 x 512 x 1024 41.9 / 39.2, 4096 x 512 x
-//     4096 73.5 / 74.5, 2048 x 2048 x 4096 102.0 / 103.5, 1024 x 1024 x 32768 264 / 259; BF16 512 x 8192 x 1024
-//     57.3 / 53.7; plain FP16 2048 x 2048 x 4096 57.0 / 55.1; but not the unscaled FP16 pair, whose kernel then needs
-//     scratch (Markidis' method, 2048 x 1024 x 4096 79.8 / 82.6, 4096^3 413 / 418)
-//   * one operand by itself: BF16 2048 x 8192 26.6 / 26.1 (the split alone), plain FP16 2048 x 4096 9.2 / 8.4; from 2^14
-//     tiles on it is the other way round up to 2^15: 4096 x 8192 in FP16 40.4 / 42.8, in BF16 64.6 / 69.9
-//   * the same for FP32, which has nothing to convert: single throughout (2048 x 4096 11.6 / 12.9, 4096 x 8192 40.2 / 42.0)
-constexpr unsigned kSplitDeepFrom = 1 << 12, kSplitDeepAloneBelow = 1 << 14, kSplitDeepAloneAgain = 1 << 15;  // in tiles
-void use_deep_blocks(SplitJob* job) {
-  const unsigned row_blocks = job->blocks / job->fast_tiles;
-  job->variant = kSplitKContiguousVecDeep;
-  job->fast_tiles = (job->fast_tiles + kSplitDeepTiles - 1) / kSplitDeepTiles;
-  job->blocks = job->fast_tiles * row_blocks;
-}
-bool large_k_contiguous(const SplitJob& job) { return job.variant == kSplitKContiguousVec && job.blocks >= kSplitDeepFrom; }
+// Aligned operands with k contiguous: one 64 x 32 tile a block, or from 2^12 tiles on (2^23 elements, four blocks per
+// unit) four, kSplitKContiguousVecDeep: fewer and longer blocks with four times the loads in flight.  Below, single
+// tiles, which spread a small operand over the chip.  Whole calls with single / four tiles throughout, us: FP16
+// 8192 x 512 x 1024 41.0 / 37.8, 1024 x 1024 x 16384 145.2 / 137.0, 4096^3 361.6 / 358.6, 9000 x 1024 x 9000 551 / 531;
+// BF16 1024 x 1024 x 16384 219.2 / 211.8; FP32, which has nothing to convert, 9000 x 512 x 9000 842 / 821; one operand
+// split and multiplied with a kept one, FP16, 512 x 5000 x 9000 202 / 190, and at worst 512 x 2048 x 20000 165.1 / 166.5.
+// The automatic mode's measuring split also leaves a quarter of the sums to add up for the choice: 2048 x 2048 x 4096
+// 135 / 125, 8192^3 2607 / 2552 (its two choices 20 / 11 each).
+constexpr int64_t kSplitDeepFrom = 1 << 12;  // in tiles
 
 // Operands from 256 MiB on, the size of the memory-side cache, with the rows contiguous are read past it (see
 // load_source4).  Whole calls with ordinary / non-temporal loads of the source: 4096 x 1024 x 16384 449 / 443.7 us,
 // 1024 x 1024 x 65536 517 / 513, 1920 x 1024 x 62912 907 / 911; below that size 4096^3 (64 MiB) 356 / 360 and 2048^3
 // 57.5 / 61, whose operands a program's next read finds in the cache; two operands of 128 MiB, 4096 x 4096 x 8192,
 // 680 / 670.  With the depth contiguous ordinary loads always: a row that does not start on a cache line shares its lines
-// with the next block's, which would fetch them again (9000 x 1024 x 9000 534 / 571, the split alone 129 / 167), and on
-// whole lines they gain nothing (8192 x 1024 x 9024 448 / 458, 1024 x 1024 x 65536 507 / 506).  The measuring splits,
-// which read an operand twice, keep ordinary loads (8192^3: level).
+// with the next block's, which would fetch them again (9000 x 1024 x 9000 517 / 565, the split alone 118 / 167), and on
+// whole lines they are as good or better (8192 x 1024 x 9024 446 / 452, 1536 x 1536 x 45056 682 / 695, 1024 x 1024 x
+// 65536 501 / 506 with both operands so, 513 / 511 with one).  The measuring splits, which read an operand twice, keep
+// ordinary loads (8192^3: level).
 constexpr int64_t kSplitStreamedElems = 1ll << 26;
 
 // X = op(src) is rows x depth.  op == N: X(r, k) = src[r + k * ld]; op == T: X(r, k) = src[k + r * ld].
@@ -481,7 +470,11 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
     case kSplitRContiguous: job->fast_tiles = (unsigned)(Rp / 64), job->blocks = (unsigned)blocks64; break;
     case kSplitKContiguousVec:
       job->fast_tiles = (unsigned)(Kp / 32), job->blocks = (unsigned)blocks64;
-      if (blocks64 >= kSplitDeepAloneAgain) use_deep_blocks(job);
+      if (blocks64 >= kSplitDeepFrom) {
+        job->variant = kSplitKContiguousVecDeep;
+        job->fast_tiles = (unsigned)((Kp / 32 + kSplitDeepTiles - 1) / kSplitDeepTiles);
+        job->blocks = (unsigned)(job->fast_tiles * (Rp / 64));
+      }
       break;
     default: job->fast_tiles = (unsigned)((Kp + 63) / 64), job->blocks = (unsigned)((Kp + 63) / 64 * (Rp / 64)); break;
   }
@@ -500,31 +493,19 @@ void launch_split_job(hipStream_t stream, const SplitJob& job) {
   }
 }
 
-// (the measuring jobs' blocks are fixed by sgemm_auto: their statistics are counted by block)
 template <int KIND, bool STATS = false>
 void launch_split_kind(hipStream_t stream, const SplitJob& a, const SplitJob* b) {
-  if (b != nullptr) {
-    SplitJob first = a, second = *b;
-    constexpr bool kDeep = KIND != kSplitFp16Unscaled;
-    if (kDeep && !STATS && large_k_contiguous(first)) use_deep_blocks(&first);
-    if (kDeep && !STATS && large_k_contiguous(second)) use_deep_blocks(&second);
-    // one launch up to 2^26 elements in the aligned variants' large blocks (a quarter of that in small ones): in one /
-    // two launches 1024 x 1024 x 16384 136 / 139 us a call, 2048 x 2048 x 16384 391 / 406
-    if ((uint64_t)first.blocks + second.blocks <= 8192) {
-      const dim3 grid(first.blocks + second.blocks), block(256);
-      // (an operand that always has such blocks is too large for this: without kDeep neither has them)
-      if (kDeep && (first.variant == kSplitKContiguousVecDeep || second.variant == kSplitKContiguousVecDeep))
-        hipLaunchKernelGGL((split_pair_kernel<KIND, kDeep, STATS>), grid, block, 0, stream, first, second);
-      else
-        hipLaunchKernelGGL((split_pair_kernel<KIND, false, STATS>), grid, block, 0, stream, first, second);
-      return;
-    }
-  }
-  for (const SplitJob* given : {&a, b}) {
-    if (given == nullptr) break;
-    SplitJob job = *given;
-    if (!STATS && KIND != kSplitFp32 && large_k_contiguous(job) && job.blocks < kSplitDeepAloneBelow) use_deep_blocks(&job);
-    launch_split_job<KIND, STATS>(stream, job);
+  // both operands in one launch up to 2^26 elements in the aligned variants' large blocks (a quarter of that in small
+  // ones): in one / two launches 1024 x 1024 x 16384 136 / 139 us a call, 2048 x 2048 x 16384 391 / 406
+  if (b != nullptr && (uint64_t)a.blocks + b->blocks <= 8192) {
+    const dim3 grid(a.blocks + b->blocks), block(256);
+    if (a.variant == kSplitKContiguousVecDeep || b->variant == kSplitKContiguousVecDeep)
+      hipLaunchKernelGGL((split_pair_kernel<KIND, true, STATS>), grid, block, 0, stream, a, *b);
+    else
+      hipLaunchKernelGGL((split_pair_kernel<KIND, false, STATS>), grid, block, 0, stream, a, *b);
+  } else {
+    launch_split_job<KIND, STATS>(stream, a);
+    if (b) launch_split_job<KIND, STATS>(stream, *b);
   }
 }
 
@@ -1239,9 +1220,6 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
   if (st != ECGEMM_OK) return st;
   st = make_split_job(h, op_b, N, K, B, ldb, ws + ap.bf16.a_bytes, h->log2_scale_b, nullptr, &bf16_b);
   if (st != ECGEMM_OK) return st;
-  // (the BF16 split too: where it is not wanted, its blocks return at once, and the fewer there are the better)
-  for (SplitJob* job : {&fp16_a, &fp16_b, &bf16_a, &bf16_b})
-    if (large_k_contiguous(*job)) use_deep_blocks(job);
   if (kStatsPerBlock * sizeof(double) * fp16_a.blocks > ap.stats_a_bytes ||
       kStatsPerBlock * sizeof(double) * fp16_b.blocks > ap.stats_b_bytes)
     return fail(h, ECGEMM_ERR_HIP, "ecgemm_sgemm: internal error, statistics array too small");

@@ -121,7 +121,8 @@ ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepthVec, 32)
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitRContiguous, false>(const SplitJob);      \
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitRContiguousWide, false>(const SplitJob);  \
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitKContiguousVecDeep, false>(const SplitJob); \
-  ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<KIND, false, false>(const SplitJob, const SplitJob);
+  ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<KIND, false, false>(const SplitJob, const SplitJob); \
+  ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<KIND, true, false>(const SplitJob, const SplitJob);
 ECGEMM_SPLIT_KERNELS_OF(kSplitFp16Scaled)
 ECGEMM_SPLIT_KERNELS_OF(kSplitBf16x3)
 ECGEMM_SPLIT_KERNELS_OF(kSplitFp16Unscaled)
@@ -129,11 +130,6 @@ ECGEMM_SPLIT_KERNELS_OF(kSplitFp16Plain)
 ECGEMM_SPLIT_KERNELS_OF(kSplitBf16Plain)
 ECGEMM_SPLIT_KERNELS_OF(kSplitFp32)
 #undef ECGEMM_SPLIT_KERNELS_OF
-ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<kSplitFp16Scaled, true, false>(const SplitJob, const SplitJob);
-ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<kSplitBf16x3, true, false>(const SplitJob, const SplitJob);
-ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<kSplitFp16Plain, true, false>(const SplitJob, const SplitJob);
-ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<kSplitBf16Plain, true, false>(const SplitJob, const SplitJob);
-ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<kSplitFp32, true, false>(const SplitJob, const SplitJob);
 // (the FP16 pair split that also measures what the pair loses: automatic mode choice)
 ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitKContiguousVec, true>(const SplitJob);
 ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitKContiguous, true>(const SplitJob);

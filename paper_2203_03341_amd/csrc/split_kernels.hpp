@@ -298,14 +298,21 @@ __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job
   if (job.row_log2_scale != nullptr && r < job.rows) prescale *= row_scale_factor(job.row_log2_scale[r]);
   const float* src = job.src;
   float v[TILES][8];
+  if (r - (t >> 2) + 64 <= job.rows && k0 - (t & 3) * 8 + 32 * TILES <= job.depth) {  // the same for the block
+    // (without a condition of its own for every tile: the compiler waits for a tile's loads where their branches join)
+    const float* from = src + r * job.ld + k0;
+    float4 lo[TILES], hi[TILES];
 #pragma unroll
-  for (int s = 0; s < TILES; ++s) {
-    const int64_t k = k0 + 32 * s;
-    if (r < job.rows && k + 8 <= job.depth) {
-      const float4 lo = load_source4<false>(src + r * job.ld + k), hi = load_source4<false>(src + r * job.ld + k + 4);
-      v[s][0] = lo.x; v[s][1] = lo.y; v[s][2] = lo.z; v[s][3] = lo.w;
-      v[s][4] = hi.x; v[s][5] = hi.y; v[s][6] = hi.z; v[s][7] = hi.w;
-    } else {
+    for (int s = 0; s < TILES; ++s) lo[s] = load_source4<false>(from + 32 * s), hi[s] = load_source4<false>(from + 32 * s + 4);
+#pragma unroll
+    for (int s = 0; s < TILES; ++s) {
+      v[s][0] = lo[s].x; v[s][1] = lo[s].y; v[s][2] = lo[s].z; v[s][3] = lo[s].w;
+      v[s][4] = hi[s].x; v[s][5] = hi[s].y; v[s][6] = hi[s].z; v[s][7] = hi[s].w;
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < TILES; ++s) {
+      const int64_t k = k0 + 32 * s;
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[s][e] = (r < job.rows && k + e < job.depth) ? src[r * job.ld + k + e] : 0.0f;
     }
@@ -327,7 +334,7 @@ __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job
     store_fragment_row<KIND, STATS>(job.packed, job.k_steps_total, r, k, v[s], stats);
   }
 }
-// (kernels of their own for one and for four tiles: four take 50 to 81 registers, one 20 to 33)
+// (kernels of their own for one and for four tiles: four take 44 to 89 registers, one 20 to 33)
 template <int KIND, bool STATS = false>
 __device__ __forceinline__ void split_block_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats = nullptr) {
   split_tiles_k_contiguous_vec<KIND, 1, STATS>(job, block, stats);
