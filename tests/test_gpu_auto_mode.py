@@ -96,8 +96,9 @@ def _check(h, transA, transB, M, N, K, dist_a, dist_b, seed=0, pad=0, alpha=1.5,
 
 @pytest.mark.parametrize("transA,transB,pad", [("N", "N", 0), ("T", "T", 0), ("N", "T", 1), ("T", "N", 3)])
 def test_choice_and_result_for_the_papers_input_types(transA, transB, pad):
-    """Every split kernel variant (both storage orders, aligned and not) measures the same thing; ragged sizes with
-    several blocks per operand; either operand alone takes the call out of the plain FP16 mode."""
+    """Both storage orders, aligned and not, measure the same thing; ragged sizes with several blocks per operand; either
+    operand alone takes the call out of the plain FP16 mode.  (A product this small is measured by rows; the measuring
+    splits have tests of their own below.)"""
     import paper_2203_03341_amd as ec
     h = ec.Handle()
     M, N, K = 300, 260, 200
