@@ -421,8 +421,8 @@ ecgemm_status_t hip_fail(ecgemm_handle_t h, hipError_t e, const char* where) {
     if (e_ != hipSuccess) return hip_fail((h), e_, #call);    \
   } while (0)
 
-// Aligned operands with k contiguous: one 64 x 32 tile a block, or from 2^12 tiles on (2^23 elements, four blocks per
-// unit) four, kSplitKContiguousVecDeep: fewer and longer blocks with four times the loads in flight.  Below, single
+// Operands with k contiguous: one 64 x 32 tile a block, or from 2^12 tiles on (2^23 elements, four blocks per unit)
+// four, kSplitKContiguousDeep: fewer and longer blocks with four times the loads in flight.  Below, single
 // tiles, which spread a small operand over the chip.  Whole calls with single / four tiles throughout, us: FP16
 // 8192 x 512 x 1024 41.0 / 37.8, 1024 x 1024 x 16384 145.2 / 137.0, 4096^3 361.6 / 358.6, 9000 x 1024 x 9000 551 / 531;
 // BF16 1024 x 1024 x 16384 219.2 / 211.8; FP32, which has nothing to convert, 9000 x 512 x 9000 842 / 821; one operand
@@ -431,25 +431,37 @@ ecgemm_status_t hip_fail(ecgemm_handle_t h, hipError_t e, const char* where) {
 // 135 / 125, 8192^3 2607 / 2552 (its two choices 20 / 11 each).
 constexpr int64_t kSplitDeepFrom = 1 << 12;  // in tiles
 
-// Operands from 256 MiB on, the size of the memory-side cache, with the rows contiguous are read past it (see
+// Operands with the rows contiguous and aligned, from 256 MiB on, the size of the memory-side cache, are read past it (see
 // load_source4).  Whole calls with ordinary / non-temporal loads of the source: 4096 x 1024 x 16384 449 / 443.7 us,
 // 1024 x 1024 x 65536 517 / 513, 1920 x 1024 x 62912 907 / 911; below that size 4096^3 (64 MiB) 356 / 360 and 2048^3
 // 57.5 / 61, whose operands a program's next read finds in the cache; two operands of 128 MiB, 4096 x 4096 x 8192,
-// 680 / 670.  With the depth contiguous ordinary loads always: a row that does not start on a cache line shares its lines
-// with the next block's, which would fetch them again (9000 x 1024 x 9000 517 / 565, the split alone 118 / 167), and on
-// whole lines they are as good or better (8192 x 1024 x 9024 446 / 452, 1536 x 1536 x 45056 682 / 695, 1024 x 1024 x
+// 680 / 670.  A line that two blocks share is fetched by both then, which the FP16 split bears (8196 x 8196 105 / 95,
+// 1024 x 65536 with ld 1028 103 / 96, 9000 x 9000 126 / 134) and the BF16 split does not (130 / 139, 130 / 137, 163 / 169):
+// on whole cache lines only.  With the depth contiguous ordinary loads always: 9000 x 1024 x 9000 517 / 565 a call, and
+// on whole lines they are as good or better (8192 x 1024 x 9024 446 / 452, 1536 x 1536 x 45056 682 / 695, 1024 x 1024 x
 // 65536 501 / 506 with both operands so, 513 / 511 with one).  The measuring splits, which read an operand twice, keep
 // ordinary loads (8192^3: level).
 constexpr int64_t kSplitStreamedElems = 1ll << 26;
 
+// An operand whose source and parts fit the memory-side cache together (8 or 10 bytes per element in the method's modes)
+// is bound by the L2s: where its lines do not start on cache lines, each XCD takes a contiguous run of the tiles
+// (tile_of_block).  Plain order / runs, us, FP16: k contiguous 2052^2 8.6 / 6.7, 4100^2 24.5 / 21.9, 5000^2 35.4 / 30.7, r
+// contiguous 6.6 / 6.4, 22.7 / 21.3, 32.0 / 30.0; larger operands come from memory, where the runs keep fewer
+// neighbouring pages open at a time: k contiguous 6000^2 54.0 / 56.2, 7000^2 71.1 / 76.4, 9000^2 117.9 / 123.1, 1024 x 65536
+// with ld 65540 101 / 124.  Whole lines keep the plain order (runs cost them up to 7 %).
+constexpr int64_t kSplitCachedBytes = 256ll << 20;
+
 // X = op(src) is rows x depth.  op == N: X(r, k) = src[r + k * ld]; op == T: X(r, k) = src[k + r * ld].
+// `alone`: no other operand is split in the same launch.
 ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, int64_t depth, const float* src, int64_t ld,
-                               void* packed, int log2_prescale, const int* row_log2_scale, SplitJob* job) {
+                               ecgemm_mode_t mode, void* packed, int log2_prescale, const int* row_log2_scale, SplitJob* job,
+                               bool alone = false) {
   const int64_t Rp = round_up(rows, kRowPad), Kp = round_up(depth, kDepthPad);
   const int64_t blocks64 = (Kp / 32) * (Rp / 64);
   if (blocks64 > 0x7fffffff) return fail(h, ECGEMM_ERR_INVALID_ARG, "operand has more than 2^42 elements");
   const bool k_contiguous = op == ECGEMM_OP_T;
-  const bool vec = (ld % 4 == 0) && ((uintptr_t)src % 16 == 0);
+  const bool aligned = ld % 4 == 0 && (uintptr_t)src % 16 == 0, whole_lines = ld % 32 == 0 && (uintptr_t)src % 128 == 0;
+  const bool cached = (4 + 2 * parts_of(mode)) * (double)rows * (double)depth <= (double)kSplitCachedBytes;
   job->src = src;
   job->ld = ld;
   job->rows = rows;
@@ -462,21 +474,26 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
   job->gate = nullptr;
   job->gate_value = 0;
   job->row_max = nullptr;
-  job->streamed = rows * depth >= kSplitStreamedElems;  // (kSplitRContiguousWide)
-  job->variant = k_contiguous ? (vec ? kSplitKContiguousVec : kSplitKContiguous) : (vec ? kSplitRContiguousWide : kSplitRContiguous);
-  // blocks are 64 rows x 32 k, except 256 x 32 (wide) and 64 x 64 (k contiguous, unaligned)
+  job->streamed = rows * depth >= kSplitStreamedElems && (split_is_bf16(split_kind_of((int)mode)) ? whole_lines : aligned);  // (kSplitRContiguousWide)
+  job->runs = !whole_lines && cached;
+  // Rows contiguous: 256 rows a block, or 64 where the lines start anywhere and the operand comes from memory (FP16 64 / 256
+  // rows: 9001^2 121 / 126 us, 12001^2 217 / 223; from the caches 4095 x 5003 30.3 / 24.9, 300 x 100000 73 / 63), or where it
+  // makes so few blocks that the launch is all there is to see, and it is split alone (1001 x 2003 4.1 / 4.5; next to
+  // another operand the wide blocks are ahead there too, 1500^3 NT 36.2 / 35.4 a call).
+  const bool wide = aligned || (cached && !(alone && blocks64 / 4 < 2 * kPlanComputeUnits));
+  job->variant = k_contiguous ? kSplitKContiguous : wide ? kSplitRContiguousWide : kSplitRContiguous;
+  // blocks are 64 rows x 32 k, or 256 x 32 (wide), or four tiles along k
   switch (job->variant) {
     case kSplitRContiguousWide: job->fast_tiles = (unsigned)(Rp / 256), job->blocks = (unsigned)(blocks64 / 4); break;
     case kSplitRContiguous: job->fast_tiles = (unsigned)(Rp / 64), job->blocks = (unsigned)blocks64; break;
-    case kSplitKContiguousVec:
+    default:
       job->fast_tiles = (unsigned)(Kp / 32), job->blocks = (unsigned)blocks64;
       if (blocks64 >= kSplitDeepFrom) {
-        job->variant = kSplitKContiguousVecDeep;
+        job->variant = kSplitKContiguousDeep;
         job->fast_tiles = (unsigned)((Kp / 32 + kSplitDeepTiles - 1) / kSplitDeepTiles);
         job->blocks = (unsigned)(job->fast_tiles * (Rp / 64));
       }
       break;
-    default: job->fast_tiles = (unsigned)((Kp + 63) / 64), job->blocks = (unsigned)((Kp + 63) / 64 * (Rp / 64)); break;
   }
   return ECGEMM_OK;
 }
@@ -487,19 +504,18 @@ void launch_split_job(hipStream_t stream, const SplitJob& job) {
   switch (job.variant) {
     case kSplitRContiguousWide: hipLaunchKernelGGL((split_kernel<KIND, kSplitRContiguousWide, STATS>), grid, block, 0, stream, job); break;
     case kSplitRContiguous: hipLaunchKernelGGL((split_kernel<KIND, kSplitRContiguous, STATS>), grid, block, 0, stream, job); break;
-    case kSplitKContiguousVec: hipLaunchKernelGGL((split_kernel<KIND, kSplitKContiguousVec, STATS>), grid, block, 0, stream, job); break;
-    case kSplitKContiguousVecDeep: hipLaunchKernelGGL((split_kernel<KIND, kSplitKContiguousVecDeep, STATS>), grid, block, 0, stream, job); break;
+    case kSplitKContiguousDeep: hipLaunchKernelGGL((split_kernel<KIND, kSplitKContiguousDeep, STATS>), grid, block, 0, stream, job); break;
     default: hipLaunchKernelGGL((split_kernel<KIND, kSplitKContiguous, STATS>), grid, block, 0, stream, job); break;
   }
 }
 
 template <int KIND, bool STATS = false>
 void launch_split_kind(hipStream_t stream, const SplitJob& a, const SplitJob* b) {
-  // both operands in one launch up to 2^26 elements in the aligned variants' large blocks (a quarter of that in small
-  // ones): in one / two launches 1024 x 1024 x 16384 136 / 139 us a call, 2048 x 2048 x 16384 391 / 406
+  // both operands in one launch up to 2^26 elements in large blocks (a quarter of that in small ones): in one / two
+  // launches 1024 x 1024 x 16384 136 / 139 us a call, 2048 x 2048 x 16384 391 / 406
   if (b != nullptr && (uint64_t)a.blocks + b->blocks <= 8192) {
     const dim3 grid(a.blocks + b->blocks), block(256);
-    if (a.variant == kSplitKContiguousVecDeep || b->variant == kSplitKContiguousVecDeep)
+    if (a.variant == kSplitKContiguousDeep || b->variant == kSplitKContiguousDeep)
       hipLaunchKernelGGL((split_pair_kernel<KIND, true, STATS>), grid, block, 0, stream, a, *b);
     else
       hipLaunchKernelGGL((split_pair_kernel<KIND, false, STATS>), grid, block, 0, stream, a, *b);
@@ -975,7 +991,7 @@ ecgemm_status_t ecgemm_split(ecgemm_handle_t handle, ecgemm_op_t op, int64_t row
   if (ld < (op == ECGEMM_OP_N ? rows : depth)) return bad_arg(handle, 6, "ecgemm_split: leading dimension too small");
   if (!packed || ((uintptr_t)packed % 16) != 0) return bad_arg(handle, 8, "ecgemm_split: null or misaligned output");
   SplitJob job;
-  const ecgemm_status_t st = make_split_job(handle, op, rows, depth, src, ld, packed, 0, nullptr, &job);
+  const ecgemm_status_t st = make_split_job(handle, op, rows, depth, src, ld, mode, packed, 0, nullptr, &job, true);
   if (st != ECGEMM_OK) return st;
   return launch_split(handle, mode, job);
 }
@@ -1212,13 +1228,13 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
   rows_a.scale = scales_a;
   rows_b.scale = scales_b;
   SplitJob fp16_a, fp16_b, scaled_a, scaled_b, bf16_a, bf16_b;
-  st = make_split_job(h, transA, M, K, A, lda, ws, h->log2_scale_a, nullptr, &fp16_a);
+  st = make_split_job(h, transA, M, K, A, lda, ECGEMM_MODE_FP16_SPLIT, ws, h->log2_scale_a, nullptr, &fp16_a);
   if (st != ECGEMM_OK) return st;
-  st = make_split_job(h, op_b, N, K, B, ldb, ws + ap.fp16.a_bytes, h->log2_scale_b, nullptr, &fp16_b);
+  st = make_split_job(h, op_b, N, K, B, ldb, ECGEMM_MODE_FP16_SPLIT, ws + ap.fp16.a_bytes, h->log2_scale_b, nullptr, &fp16_b);
   if (st != ECGEMM_OK) return st;
-  st = make_split_job(h, transA, M, K, A, lda, ws, h->log2_scale_a, nullptr, &bf16_a);
+  st = make_split_job(h, transA, M, K, A, lda, ECGEMM_MODE_BF16_FULL, ws, h->log2_scale_a, nullptr, &bf16_a);
   if (st != ECGEMM_OK) return st;
-  st = make_split_job(h, op_b, N, K, B, ldb, ws + ap.bf16.a_bytes, h->log2_scale_b, nullptr, &bf16_b);
+  st = make_split_job(h, op_b, N, K, B, ldb, ECGEMM_MODE_BF16_FULL, ws + ap.bf16.a_bytes, h->log2_scale_b, nullptr, &bf16_b);
   if (st != ECGEMM_OK) return st;
   if (kStatsPerBlock * sizeof(double) * fp16_a.blocks > ap.stats_a_bytes ||
       kStatsPerBlock * sizeof(double) * fp16_b.blocks > ap.stats_b_bytes)
@@ -1401,9 +1417,9 @@ ecgemm_status_t sgemm_common(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t 
   if (!pl.shape->fused) {
     // step 1: op(A) is M x K with rows m; op(B)^T is N x K with rows n.  For B the roles of N and T swap:
     // B stored K x N (transB == N) has k contiguous, i.e. it is the "T" case of the splitter.
-    st = make_split_job(h, transA, M, K, A, lda, a_packed, h->log2_scale_a, row_log2_scale_a, &job_a);
+    st = make_split_job(h, transA, M, K, A, lda, mode, a_packed, h->log2_scale_a, row_log2_scale_a, &job_a);
     if (st != ECGEMM_OK) return st;
-    st = make_split_job(h, transB == ECGEMM_OP_N ? ECGEMM_OP_T : ECGEMM_OP_N, N, K, B, ldb, b_packed, h->log2_scale_b,
+    st = make_split_job(h, transB == ECGEMM_OP_N ? ECGEMM_OP_T : ECGEMM_OP_N, N, K, B, ldb, mode, b_packed, h->log2_scale_b,
                         col_log2_scale_b, &job_b);
     if (st != ECGEMM_OK) return st;
   }

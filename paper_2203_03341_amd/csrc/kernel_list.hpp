@@ -116,11 +116,10 @@ ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepth, 32)
 ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepthVec, 32)
 
 #define ECGEMM_SPLIT_KERNELS_OF(KIND)                                                                     \
-  ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitKContiguousVec, false>(const SplitJob);   \
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitKContiguous, false>(const SplitJob);      \
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitRContiguous, false>(const SplitJob);      \
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitRContiguousWide, false>(const SplitJob);  \
-  ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitKContiguousVecDeep, false>(const SplitJob); \
+  ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitKContiguousDeep, false>(const SplitJob);  \
   ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<KIND, false, false>(const SplitJob, const SplitJob); \
   ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<KIND, true, false>(const SplitJob, const SplitJob);
 ECGEMM_SPLIT_KERNELS_OF(kSplitFp16Scaled)
@@ -131,11 +130,10 @@ ECGEMM_SPLIT_KERNELS_OF(kSplitBf16Plain)
 ECGEMM_SPLIT_KERNELS_OF(kSplitFp32)
 #undef ECGEMM_SPLIT_KERNELS_OF
 // (the FP16 pair split that also measures what the pair loses: automatic mode choice)
-ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitKContiguousVec, true>(const SplitJob);
 ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitKContiguous, true>(const SplitJob);
 ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitRContiguous, true>(const SplitJob);
 ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitRContiguousWide, true>(const SplitJob);
-ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitKContiguousVecDeep, true>(const SplitJob);
+ECGEMM_SPLIT_GROUP template __global__ void split_kernel<kSplitFp16Scaled, kSplitKContiguousDeep, true>(const SplitJob);
 ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<kSplitFp16Scaled, false, true>(const SplitJob, const SplitJob);
 ECGEMM_SPLIT_GROUP template __global__ void split_pair_kernel<kSplitFp16Scaled, true, true>(const SplitJob, const SplitJob);
 

@@ -247,6 +247,7 @@ struct SplitJob {
   unsigned blocks;
   int variant;                // SplitVariant
   bool streamed;              // kSplitRContiguousWide: non-temporal loads of the source (operands larger than the memory-side cache)
+  bool runs;                  // the blocks of one XCD take one contiguous run of the tiles (see tile_of_block)
   // Automatic mode choice only, else null: block b leaves its SplitStats at stats[kStatsPerBlock b ...]
   double* stats;
   // Automatic mode choice only, else null: the kernel does nothing unless *gate == gate_value
@@ -273,24 +274,41 @@ __device__ __forceinline__ void store_block_stats(const SplitStats& mine, double
   if (threadIdx.x < kStatsPerBlock)
     out[threadIdx.x] = (scratch12[threadIdx.x] + scratch12[3 + threadIdx.x]) + (scratch12[6 + threadIdx.x] + scratch12[9 + threadIdx.x]);
 }
-enum SplitVariant { kSplitKContiguousVec = 0, kSplitKContiguous = 1, kSplitRContiguous = 2, kSplitRContiguousWide = 3, kSplitKContiguousVecDeep = 4 };
+enum SplitVariant { kSplitKContiguous = 0, kSplitKContiguousDeep = 1, kSplitRContiguous = 2, kSplitRContiguousWide = 3 };
 
-// Four values of the source.  STREAMED: non-temporal, so that an operand that is too large to be found in the
-// memory-side cache by anyone later does not push out of it what was just packed.
+// Four values of the source, at any multiple of 4 bytes.  STREAMED: non-temporal, so that an operand that is too large to
+// be found in the memory-side cache by anyone later does not push out of it what was just packed.
+typedef float source4_t __attribute__((ext_vector_type(4)));
 template <bool STREAMED>
-__device__ __forceinline__ float4 load_source4(const float* from) {
-  typedef float vec4_t __attribute__((ext_vector_type(4)));
-  const vec4_t* at = reinterpret_cast<const vec4_t*>(from);
-  const vec4_t x = STREAMED ? __builtin_nontemporal_load(at) : *at;
-  return make_float4(x[0], x[1], x[2], x[3]);
+__device__ __forceinline__ source4_t load_source4(const float* from) {
+  typedef float any4_t __attribute__((ext_vector_type(4), aligned(4)));
+  const any4_t* at = reinterpret_cast<const any4_t*>(from);
+  return STREAMED ? __builtin_nontemporal_load(at) : *at;
+}
+// line[at .. at + 3] of a line of `count` >= 4 values, zero behind its end: one load inside the line, whatever `at` >= 0
+template <bool STREAMED>
+__device__ __forceinline__ source4_t load_source4_or_zero(const float* line, int64_t at, int64_t count) {
+  const int64_t inside = at < count - 4 ? at : count - 4;
+  const source4_t x = load_source4<STREAMED>(line + inside);
+  const int behind = at - inside < 4 ? (int)(at - inside) : 4;
+  source4_t y;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    y[i] = behind == 0 ? x[i] : 0.0f;
+#pragma unroll
+    for (int d = 1; i + d < 4; ++d) y[i] = behind == d ? x[i + d] : y[i];
+  }
+  return y;
 }
 
-// Source with k contiguous, X(r, k) = src[k + r * ld], base and leading dimension multiples of 16 bytes.  One block:
-// 64 rows x 32 k, 256 threads, thread t handles row t / 4 and the 8 values starting at k = 8 * (t % 4), two 16-byte
-// loads; or TILES such tiles next to each other in k, whose loads are all requested before the first is split.  Blocks
-// are numbered with k fastest.
+// Source with k contiguous, X(r, k) = src[k + r * ld].  One block: 64 rows x 32 k, 256 threads, thread t handles row
+// t / 4 and the 8 values starting at k = 8 * (t % 4), two 16-byte loads; or TILES such tiles next to each other in k, whose
+// loads are all requested before the first is split (kernels of their own: one tile takes 20 to 33 registers, four 44 to
+// 64).  Blocks are numbered with k fastest.  The memory path takes 16 bytes at any multiple of four, so rows that start on
+// no alignment (lda = 5003) are read like the others: 4095 x 5003 FP16 31.1 us / 25.3 and BF16 36.4 / 32.1 with lanes along
+// k, one value each, handed to the row's thread through LDS / so; 9001 x 9001 161 / 118 and 195 / 149.
 template <int KIND, int TILES, bool STATS>
-__device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats) {
+__device__ __forceinline__ void split_tiles_k_contiguous(const SplitJob& job, unsigned block, SplitStats* stats) {
   const int t = threadIdx.x;
   const int64_t r = (int64_t)(block / job.fast_tiles) * 64 + (t >> 2);
   const int64_t k0 = (int64_t)(block % job.fast_tiles) * (32 * TILES) + (t & 3) * 8;
@@ -301,14 +319,23 @@ __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job
   if (r - (t >> 2) + 64 <= job.rows && k0 - (t & 3) * 8 + 32 * TILES <= job.depth) {  // the same for the block
     // (without a condition of its own for every tile: the compiler waits for a tile's loads where their branches join)
     const float* from = src + r * job.ld + k0;
-    float4 lo[TILES], hi[TILES];
+    source4_t lo[TILES], hi[TILES];
 #pragma unroll
     for (int s = 0; s < TILES; ++s) lo[s] = load_source4<false>(from + 32 * s), hi[s] = load_source4<false>(from + 32 * s + 4);
 #pragma unroll
-    for (int s = 0; s < TILES; ++s) {
-      v[s][0] = lo[s].x; v[s][1] = lo[s].y; v[s][2] = lo[s].z; v[s][3] = lo[s].w;
-      v[s][4] = hi[s].x; v[s][5] = hi[s].y; v[s][6] = hi[s].z; v[s][7] = hi[s].w;
-    }
+    for (int s = 0; s < TILES; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[s][e] = lo[s][e], v[s][4 + e] = hi[s][e];
+  } else if (job.depth >= 4) {
+    const float* line = src + (r < job.rows ? r : job.rows - 1) * job.ld;
+    const int64_t count = job.depth;
+    source4_t x[2 * TILES];
+#pragma unroll
+    for (int s = 0; s < 2 * TILES; ++s) x[s] = load_source4_or_zero<false>(line, k0 + 32 * (s / 2) + 4 * (s % 2), count);
+#pragma unroll
+    for (int s = 0; s < 2 * TILES; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[s / 2][4 * (s % 2) + e] = r < job.rows ? x[s][e] : 0.0f;
   } else {
 #pragma unroll
     for (int s = 0; s < TILES; ++s) {
@@ -334,53 +361,6 @@ __device__ __forceinline__ void split_tiles_k_contiguous_vec(const SplitJob& job
     store_fragment_row<KIND, STATS>(job.packed, job.k_steps_total, r, k, v[s], stats);
   }
 }
-// (kernels of their own for one and for four tiles: four take 44 to 89 registers, one 20 to 33)
-template <int KIND, bool STATS = false>
-__device__ __forceinline__ void split_block_k_contiguous_vec(const SplitJob& job, unsigned block, SplitStats* stats = nullptr) {
-  split_tiles_k_contiguous_vec<KIND, 1, STATS>(job, block, stats);
-}
-template <int KIND, bool STATS = false>
-__device__ __forceinline__ void split_block_k_contiguous_vec_deep(const SplitJob& job, unsigned block, SplitStats* stats = nullptr) {
-  split_tiles_k_contiguous_vec<KIND, kSplitDeepTiles, STATS>(job, block, stats);
-}
-
-// Source with k contiguous, any alignment (rows that do not start on 16 bytes: lda = 5003).  One block: 64 rows x
-// 64 k, read with lanes along k, so that a wave instruction fetches one 256-byte run instead of 4 bytes from each of
-// 16 rows, and handed to the row's thread through LDS (`tile`, 64 x 65 floats; the odd stride keeps both the writes
-// and the reads free of bank conflicts).  Blocks are numbered with the k tile fastest.
-template <int KIND, bool STATS = false>
-__device__ __forceinline__ void split_block_k_contiguous_staged(const SplitJob& job, unsigned block, float* tile, SplitStats* stats = nullptr) {
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int64_t r0 = (int64_t)(block / job.fast_tiles) * 64, k0 = (int64_t)(block % job.fast_tiles) * 64;
-  const float* src = job.src;
-  const int64_t k_in = k0 + lane;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int row = 4 * j + wave;
-    const int64_t r = r0 + row;
-    tile[row * 65 + lane] = (r < job.rows && k_in < job.depth) ? src[r * job.ld + k_in] : 0.0f;
-  }
-  __syncthreads();
-  const int64_t r = r0 + (t >> 2);
-  float prescale = job.prescale;
-  if (job.row_log2_scale != nullptr && r < job.rows) prescale *= row_scale_factor(job.row_log2_scale[r]);
-  int row_hi = -0x7fffffff - 1;
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int k_local = half * 32 + (t & 3) * 8;
-    if (k0 + k_local >= job.k_steps_total * 16) break;  // the padded depth is a multiple of 32, not of 64
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = tile[(t >> 2) * 65 + k_local + e];
-    if constexpr (STATS) row_hi = max(row_hi, finite_exponent8(v));
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] *= prescale;
-    store_fragment_row<KIND, STATS>(job.packed, job.k_steps_total, r, k0 + k_local, v, stats);
-  }
-  if constexpr (STATS)
-    if (job.row_max != nullptr) publish_row_exponent_of_4_lanes(job.row_max, r, r < job.rows, row_hi);
-}
-
 // Source with r contiguous: X(r, k) = src[r + k * ld], any alignment.  One block: 64 rows x 32 k.  Lanes run along r,
 // so a thread reads the 8 consecutive-k values of its row directly and each read instruction of a wave is a 256-byte
 // run.  Blocks are numbered with the row tile fastest: neighbours in the launch order read neighbouring runs.
@@ -392,8 +372,14 @@ __device__ __forceinline__ void split_block_r_contiguous(const SplitJob& job, un
   float prescale = job.prescale;
   if (job.row_log2_scale != nullptr && r < job.rows) prescale *= row_scale_factor(job.row_log2_scale[r]);
   float v[8];
+  if (r - (t & 63) + 64 <= job.rows && k - (t >> 6) * 8 + 32 <= job.depth) {  // the same for the block
+    const float* from = job.src + r + k * job.ld;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = (r < job.rows && k + e < job.depth) ? job.src[r + (k + e) * job.ld] : 0.0f;
+    for (int e = 0; e < 8; ++e) v[e] = from[e * job.ld];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (r < job.rows && k + e < job.depth) ? job.src[r + (k + e) * job.ld] : 0.0f;
+  }
   if constexpr (STATS) {
     const int hi = finite_exponent8(v);
     if (job.row_max != nullptr && r < job.rows && hi != -0x7fffffff - 1) atomicMax(&job.row_max[r], hi);
@@ -403,30 +389,44 @@ __device__ __forceinline__ void split_block_r_contiguous(const SplitJob& job, un
   store_fragment_row<KIND, STATS>(job.packed, job.k_steps_total, r, k, v, stats);
 }
 
-// Source with r contiguous, base and leading dimension multiples of 16 bytes.  One block: 256 rows x 32 k through
-// 32 KiB of LDS (`tile`).  A wave reads one k line of 256 rows per instruction (1 KiB runs, 16 bytes per lane); after
-// the barrier thread t owns row t and picks its 8-value groups out of LDS along k (lanes on consecutive words: no bank
-// conflicts).  5.4 TB/s at 16384^2 against 3.9 TB/s for the 64-row kernel above.
+// Source with r contiguous.  One block: 256 rows x 32 k through 32 KiB of LDS (`tile`).  A wave reads one k line of 256
+// rows per instruction (1 KiB runs, 16 bytes per lane), all eight of its lines before it waits for the first; after the
+// barrier thread t owns row t and picks its 8-value groups out of LDS along k (lanes on consecutive words: no bank
+// conflicts).  5.4 TB/s at 16384^2 against 3.9 TB/s for the 64-row kernel above.  FP16 2048 x 2048 6.6 us / 5.8, 4096 x
+// 4096 25.2 / 21.3, 1024 x 65536 91.7 / 80.4 with each line waited for before the next / so.
 template <bool STREAMED>
 __device__ __forceinline__ void stage_r_contiguous_wide(const SplitJob& job, unsigned block, float* tile) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int64_t r0 = (int64_t)(block % job.fast_tiles) * 256, k0 = (int64_t)(block / job.fast_tiles) * 32;
   const float* src = job.src;
+  if (r0 + 256 <= job.rows && k0 + 32 <= job.depth) {  // the same for the block
+    // (without a condition of its own for every load: the compiler waits for a load where its branches join)
+    const float* from = src + r0 + 4 * lane + (k0 + wave) * job.ld;
+    source4_t x[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int kk = wave + 4 * j;
-    const int64_t k = k0 + kk, r = r0 + 4 * lane;
-    float4 x = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (k < job.depth) {
-      if (r + 4 <= job.rows) {
-        x = load_source4<STREAMED>(src + r + k * job.ld);
-      } else {
-        if (r + 0 < job.rows) x.x = src[r + 0 + k * job.ld];
-        if (r + 1 < job.rows) x.y = src[r + 1 + k * job.ld];
-        if (r + 2 < job.rows) x.z = src[r + 2 + k * job.ld];
-      }
+    for (int j = 0; j < 8; ++j) x[j] = load_source4<STREAMED>(from + 4 * j * job.ld);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) *reinterpret_cast<source4_t*>(&tile[(wave + 4 * j) * 256 + 4 * lane]) = x[j];
+  } else if (job.rows >= 4) {
+    source4_t x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int64_t k = k0 + wave + 4 * j;
+      x[j] = load_source4_or_zero<STREAMED>(src + (k < job.depth ? k : job.depth - 1) * job.ld, r0 + 4 * lane, job.rows);
     }
-    *reinterpret_cast<float4*>(&tile[kk * 256 + 4 * lane]) = x;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const source4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+      *reinterpret_cast<source4_t*>(&tile[(wave + 4 * j) * 256 + 4 * lane]) = k0 + wave + 4 * j < job.depth ? x[j] : zero;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int64_t k = k0 + wave + 4 * j;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        tile[(wave + 4 * j) * 256 + 4 * lane + e] = r0 + 4 * lane + e < job.rows && k < job.depth ? src[r0 + 4 * lane + e + k * job.ld] : 0.0f;
+    }
   }
 }
 template <int KIND, bool STATS = false>
@@ -453,16 +453,16 @@ __device__ __forceinline__ void split_block_r_contiguous_wide(const SplitJob& jo
     if (job.row_max != nullptr && r0 + t < job.rows && row_hi != -0x7fffffff - 1) atomicMax(&job.row_max[r0 + t], row_hi);
 }
 
-// Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  For a source whose rows are not aligned to
-// cache lines, block b of n takes the tile at this position, so that every XCD works through one contiguous run of the
-// tile list: neighbouring tiles, whose rows share a cache line at their common edge, then meet in one L2 instead of
-// being fetched by two (FETCH_SIZE was 45 % above the source's size at lda = 5003; the split of that operand is 10 %
-// faster).  The aligned kernels keep the plain order: for them the runs cost up to 7 % (fewer neighbouring DRAM pages
-// open at a time).
+// Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  Block b of n takes the tile at this position
+// where every XCD is to work through one contiguous run of the tile list.
 __device__ __forceinline__ unsigned xcd_run_position(unsigned b, unsigned n) {
   const unsigned per = n / 8, rem = n % 8, x = b % 8;
   return x * per + (x < rem ? x : rem) + b / 8;
 }
+
+// The tile of block b.  With `runs`, neighbouring tiles, which share cache lines at their common edge where a source's
+// lines start anywhere, meet in one L2 instead of being fetched by two.  (make_split_job in ecgemm.hip decides.)
+__device__ __forceinline__ unsigned tile_of_block(const SplitJob& job, unsigned b) { return job.runs ? xcd_run_position(b, job.blocks) : b; }
 
 // Whether a gated kernel is to run (automatic mode choice: both candidates' kernels are enqueued, and the ones of the
 // mode not chosen return at once).
@@ -478,16 +478,11 @@ __global__ void __launch_bounds__(256) split_kernel(const SplitJob job) {
   SplitStats stats;
   if constexpr (VARIANT == kSplitRContiguousWide) {
     __shared__ float tile[32 * 256];
-    split_block_r_contiguous_wide<KIND, STATS>(job, blockIdx.x, tile, &stats);
+    split_block_r_contiguous_wide<KIND, STATS>(job, tile_of_block(job, blockIdx.x), tile, &stats);
   } else if constexpr (VARIANT == kSplitRContiguous) {
     split_block_r_contiguous<KIND, STATS>(job, blockIdx.x, &stats);
-  } else if constexpr (VARIANT == kSplitKContiguousVec) {
-    split_block_k_contiguous_vec<KIND, STATS>(job, blockIdx.x, &stats);
-  } else if constexpr (VARIANT == kSplitKContiguousVecDeep) {
-    split_block_k_contiguous_vec_deep<KIND, STATS>(job, blockIdx.x, &stats);
   } else {
-    __shared__ float tile[64 * 65];
-    split_block_k_contiguous_staged<KIND, STATS>(job, xcd_run_position(blockIdx.x, job.blocks), tile, &stats);
+    split_tiles_k_contiguous<KIND, VARIANT == kSplitKContiguousDeep ? kSplitDeepTiles : 1, STATS>(job, tile_of_block(job, blockIdx.x), &stats);
   }
   if constexpr (STATS) {
     __shared__ double sums[12];
@@ -497,7 +492,7 @@ __global__ void __launch_bounds__(256) split_kernel(const SplitJob job) {
 }
 
 // Both operands of a product in one launch, for operands up to a size at which the second launch no longer shows: blocks
-// 0 .. a.blocks - 1 split A, the rest split B.  DEEP: kSplitKContiguousVecDeep may be among the variants.
+// 0 .. a.blocks - 1 split A, the rest split B.  DEEP: kSplitKContiguousDeep may be among the variants.
 template <int KIND, bool DEEP, bool STATS = false>
 __global__ void __launch_bounds__(256) split_pair_kernel(const SplitJob a, const SplitJob b) {
   if (!gate_open(a.gate, a.gate_value)) return;
@@ -511,13 +506,11 @@ __global__ void __launch_bounds__(256) split_pair_kernel(const SplitJob a, const
   if (job.variant == kSplitRContiguous) {
     split_block_r_contiguous<KIND, STATS>(job, block, &stats);
   } else if (job.variant == kSplitKContiguous) {
-    split_block_k_contiguous_staged<KIND, STATS>(job, xcd_run_position(block, job.blocks), tile, &stats);
-  } else if (job.variant == kSplitKContiguousVec) {
-    split_block_k_contiguous_vec<KIND, STATS>(job, block, &stats);
-  } else if (DEEP && job.variant == kSplitKContiguousVecDeep) {
-    split_block_k_contiguous_vec_deep<KIND, STATS>(job, block, &stats);
+    split_tiles_k_contiguous<KIND, 1, STATS>(job, tile_of_block(job, block), &stats);
+  } else if (DEEP && job.variant == kSplitKContiguousDeep) {
+    split_tiles_k_contiguous<KIND, kSplitDeepTiles, STATS>(job, tile_of_block(job, block), &stats);
   } else {
-    split_block_r_contiguous_wide<KIND, STATS>(job, block, tile, &stats);
+    split_block_r_contiguous_wide<KIND, STATS>(job, tile_of_block(job, block), tile, &stats);
   }
   if constexpr (STATS) {
     __shared__ double sums[12];

@@ -150,6 +150,46 @@ def test_split_of_large_operands_with_the_depth_contiguous(mode_bf16, rows, dept
 
 
 @pytest.mark.parametrize("mode_bf16", [False, True])
+@pytest.mark.parametrize("op,rows,depth,pad", [
+    ("N", 1021, 4099, 0), ("N", 1022, 4100, 1), ("N", 1023, 4097, 2), ("N", 3, 40, 1), ("N", 2, 33, 2), ("N", 259, 31, 1),
+    ("T", 70, 3, 0), ("T", 65, 2, 3), ("T", 67, 1, 3), ("T", 131, 203, 2), ("T", 2047, 4101, 0), ("T", 2046, 4103, 3)])
+def test_split_of_lines_on_any_alignment(op, rows, depth, pad, mode_bf16):
+    """Sources are read 16 bytes at a time wherever their lines start: 0 to 3 values left over at the end of a line, lines
+    shorter than one such read, few blocks and many, in either orientation, NaN behind every line.  Bit for bit."""
+    sr, sc = (rows, depth) if op == "N" else (depth, rows)
+    store = si.exp_rand(sr, sc, -30, 20, 11, si.ID_A, ld=sr + pad)
+    got = _run(op, store, rows, depth, mode_bf16)
+    assert np.array_equal(got, _expected(op, store, rows, depth, mode_bf16))
+
+
+@pytest.mark.parametrize("mode_bf16", [False, True])
+@pytest.mark.parametrize("op", ["N", "T"])
+def test_split_of_lines_on_any_alignment_from_memory_and_from_the_caches(op, mode_bf16):
+    """An operand that does not fit the memory-side cache together with its parts is split in other blocks and another
+    order than its halves, which do: the packed operand is the packed halves of its rows end to end."""
+    import torch
+    import paper_2203_03341_amd as ec
+    rows, depth = 512, 100003 if mode_bf16 else 131069
+    mode = ec.MODE_BF16_FULL if mode_bf16 else ec.MODE_FP16_SPLIT
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    src = torch.randn((depth, rows + 1) if op == "N" else (rows, depth), generator=gen, device="cuda")
+    h = ec.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+
+    def packed(first, count):
+        out = torch.empty(ec.split_size(count, depth, mode), dtype=torch.uint8, device="cuda")
+        part = src[:, first:] if op == "N" else src[first:]
+        h.split(ec.OP_N if op == "N" else ec.OP_T, count, depth, part, src.shape[1], mode, out)
+        return out
+
+    whole, halves = packed(0, rows), [packed(0, 256), packed(256, 256)]
+    torch.cuda.synchronize()
+    assert torch.equal(whole, torch.cat(halves))
+    h.destroy()
+
+
+@pytest.mark.parametrize("mode_bf16", [False, True])
 @pytest.mark.parametrize("op", ["N", "T"])
 def test_split_of_operands_read_past_the_cache(op, mode_bf16):
     """Aligned operands of 2^26 elements and more with the rows contiguous are read with non-temporal loads.  Row blocks are packed one after the
