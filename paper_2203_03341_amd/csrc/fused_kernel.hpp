@@ -20,7 +20,7 @@
 // op(B), TILE / 8 of each per thread, with the lanes of a wave along whichever index is contiguous in memory
 // (FusedLayout); the values of the next kFusedRing chunks are in flight in registers while the current one is split
 // and written to LDS in fragment order (two buffers, one barrier per chunk), where the multiplying waves pick it up.
-// The split takes a short form (FastSplit, 3.5 to 7.5 vector instructions per element) whenever every value a wave
+// The split takes a short form (FastSplit, 3.5 to 4 vector instructions per element) whenever every value a wave
 // holds is ordinary, and Splitter, which saturates and handles infinities and NaN, otherwise; both give the same
 // bits on the values the short form accepts.  Measured on single blocks, what bounded a chunk in turn was: the
 // instruction stream of one splitting wave per SIMD (hence eight waves, a loop for the bulk of the depth without
@@ -235,15 +235,19 @@ struct FusedOperand {
   }
 
   // The short split of all V values, with (general == true) or without the multiplication by the scaling factors.
+  // Returns whether every value is ordinary (see FastSplit).
   template <bool GENERAL>
-  __device__ __forceinline__ void split_ordinary(const float (&x)[V], unsigned (&words)[V / 2][NP]) const {
+  __device__ __forceinline__ bool split_ordinary(const float (&x)[V], unsigned (&words)[V / 2][NP]) const {
+    float largest = 0.0f;
 #pragma unroll
     for (int e = 0; e < V / 2; ++e) {
       const float v0 = GENERAL ? x[2 * e] * factor[(2 * e) / PER_ROW] : x[2 * e];
       const float v1 = GENERAL ? x[2 * e + 1] * factor[(2 * e + 1) / PER_ROW] : x[2 * e + 1];
       // (times 2^11 after the factor, not with it: a factor of 2^126 is legitimate, 2^137 is not a number)
+      FastSplit<KIND>::raise(largest, v0, v1);
       FastSplit<KIND>::split2(v0, v1, v0 * 2048.0f, v1 * 2048.0f, words[e]);
     }
+    return FastSplit<KIND>::ordinary(largest);
   }
 
   // Splitter on all V values; k beyond the depth (last chunk) counts as zero.
@@ -265,11 +269,9 @@ struct FusedOperand {
     const bool whole = (int64_t)c * 64 + 64 <= K;  // block-uniform
     bool done = false;
     if (whole) {
-      if (unscaled)  // block-uniform: no pre-scaling, no scaling vectors: every factor is 1
-        split_ordinary<false>(x, words);
-      else
-        split_ordinary<true>(x, words);
-      done = __builtin_amdgcn_ballot_w64(!FastSplit<KIND>::high_parts_finite(words)) == 0;  // wave-uniform
+      // (block-uniform: without pre-scaling and scaling vectors every factor is 1)
+      const bool ordinary = unscaled ? split_ordinary<false>(x, words) : split_ordinary<true>(x, words);
+      done = __builtin_amdgcn_ballot_w64(!ordinary) == 0;  // wave-uniform
     }
     if (!done) split_with_care(x, c, words);
     write(words, region);
@@ -280,8 +282,8 @@ struct FusedOperand {
   template <bool GENERAL>
   __device__ __forceinline__ void deposit_whole(const float (&x)[V], int c, char* region) const {
     unsigned words[V / 2][NP];
-    split_ordinary<GENERAL>(x, words);
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!FastSplit<KIND>::high_parts_finite(words)) != 0, 0)) {
+    const bool ordinary = split_ordinary<GENERAL>(x, words);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!ordinary) != 0, 0)) {
       // (with a write of its own: joining the two paths in front of one write costs a register copy per word)
       unsigned careful[V / 2][NP];
       split_with_care(x, c, careful);
@@ -303,8 +305,8 @@ struct FusedOperand {
     // (one write for both paths, unlike deposit_whole: another copy of its two moves the registers of the loop over the
     // whole chunks, 192 x 1920 x 62912 TT in FP16 mode 334 us with this, 345 with that)
     unsigned words[V / 2][NP];
-    split_ordinary<GENERAL>(v, words);
-    if (__builtin_amdgcn_ballot_w64(!FastSplit<KIND>::high_parts_finite(words)) != 0) split_with_care(v, c, words);
+    const bool ordinary = split_ordinary<GENERAL>(v, words);
+    if (__builtin_amdgcn_ballot_w64(!ordinary) != 0) split_with_care(v, c, words);
     write(words, region);
   }
 

@@ -93,12 +93,10 @@ struct Splitter {
 // value whose high part comes out finite both give the same bits: the high part is then at most the largest finite
 // number of the format whether or not the value was clamped to it first, the residuals are at most half a unit of
 // its last place, far inside the range of the low parts, and nothing is masked.  A value that Splitter treats
-// differently (beyond the format's range, where it saturates; infinite; NaN) shows as a high part that is infinite or
-// NaN, which high_parts_finite() finds on the packed registers.
+// differently (beyond the format's range, where it saturates; infinite; NaN) is one whose high part is infinite or NaN.
 typedef float fused_float2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 fused_half2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 fused_bf16x2_t __attribute__((ext_vector_type(2)));
-typedef unsigned short fused_ushort2_t __attribute__((ext_vector_type(2)));
 template <int KIND>
 struct FastSplit {
   static constexpr int kParts = parts_of_split(KIND);
@@ -110,9 +108,12 @@ struct FastSplit {
       const fused_half2_t hi = __builtin_convertvector(fused_float2_t{v0, v1}, fused_half2_t);
       out[0] = __builtin_bit_cast(unsigned, hi);
       if constexpr (KIND == kSplitFp16Scaled) {
-        // (each rounded to FP16 by itself: the multiply-add then delivers its result as one half of the register)
-        const fused_half2_t lo = {(_Float16)__builtin_fmaf((float)hi[0], -2048.0f, scaled0), (_Float16)__builtin_fmaf((float)hi[1], -2048.0f, scaled1)};
-        out[1] = __builtin_bit_cast(unsigned, lo);
+        // (the multiply-add in 32 bits and one packed conversion: the form that delivers a half by itself takes 8 cycles
+        // where the others take 4, and holds up the matrix instructions of other waves; hence the empty statement.  FP16 calls
+        // with that form / with this one: 1024^3 15.5 / 14.4 us, 512^3 7.5 / 7.35, 256^3 6.2 / 6.0)
+        float r0 = __builtin_fmaf((float)hi[0], -2048.0f, scaled0), r1 = __builtin_fmaf((float)hi[1], -2048.0f, scaled1);
+        asm("" : "+v"(r0), "+v"(r1));
+        out[1] = __builtin_bit_cast(unsigned, __builtin_convertvector(fused_float2_t{r0, r1}, fused_half2_t));
       } else if constexpr (kParts == 2) {
         const fused_float2_t residual = {v0 - (float)hi[0], v1 - (float)hi[1]};  // exact
         out[1] = __builtin_bit_cast(unsigned, __builtin_convertvector(residual, fused_half2_t));
@@ -129,16 +130,13 @@ struct FastSplit {
       }
     }
   }
-  // true if none of the 2 W high parts in `words[..][0]` is infinite or NaN
-  template <int W>
-  __device__ static __forceinline__ bool high_parts_finite(const unsigned (&words)[W][kParts]) {
-    const unsigned magnitude = 0x7fff7fffu;
-    fused_ushort2_t most = {0, 0};
-#pragma unroll
-    for (int e = 0; e < W; ++e)
-      most = __builtin_elementwise_max(most, __builtin_bit_cast(fused_ushort2_t, words[e][0] & magnitude));
-    const unsigned short exponent_all_ones = split_is_bf16(KIND) ? 0x7f80 : 0x7c00;
-    return most[0] < exponent_all_ones && most[1] < exponent_all_ones;
+  // The test for that, one instruction for two values: `largest` starts at 0 and is raised to their magnitudes (a NaN
+  // stays one); every high part is finite if ordinary(largest).
+  __device__ static __forceinline__ void raise(float& largest, float v0, float v1) {
+    largest = __builtin_elementwise_maximum(__builtin_elementwise_maximum(largest, __builtin_fabsf(v0)), __builtin_fabsf(v1));
+  }
+  __device__ static __forceinline__ bool ordinary(float largest) {
+    return largest < (split_is_bf16(KIND) ? 0x1.ffp127f : 65520.0f);  // from here on a value rounds to infinity
   }
 };
 
@@ -198,9 +196,13 @@ __device__ __forceinline__ void store_fragment_row(unsigned short* __restrict__ 
   bool done = false;
   if constexpr (kShort) {
     unsigned words[4][NP];
+    float largest = 0.0f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) FastSplit<KIND>::split2(v[2 * e], v[2 * e + 1], v[2 * e] * 2048.0f, v[2 * e + 1] * 2048.0f, words[e]);
-    done = __builtin_amdgcn_ballot_w64(!FastSplit<KIND>::high_parts_finite(words)) == 0;  // wave-uniform
+    for (int e = 0; e < 4; ++e) {
+      FastSplit<KIND>::raise(largest, v[2 * e], v[2 * e + 1]);
+      FastSplit<KIND>::split2(v[2 * e], v[2 * e + 1], v[2 * e] * 2048.0f, v[2 * e + 1] * 2048.0f, words[e]);
+    }
+    done = __builtin_amdgcn_ballot_w64(!FastSplit<KIND>::ordinary(largest)) == 0;  // wave-uniform
     typedef unsigned uint4_t __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int p = 0; p < NP; ++p)
@@ -285,12 +287,8 @@ __device__ __forceinline__ source4_t load_source4(const float* from) {
   const any4_t* at = reinterpret_cast<const any4_t*>(from);
   return STREAMED ? __builtin_nontemporal_load(at) : *at;
 }
-// line[at .. at + 3] of a line of `count` >= 4 values, zero behind its end: one load inside the line, whatever `at` >= 0
-template <bool STREAMED>
-__device__ __forceinline__ source4_t load_source4_or_zero(const float* line, int64_t at, int64_t count) {
-  const int64_t inside = at < count - 4 ? at : count - 4;
-  const source4_t x = load_source4<STREAMED>(line + inside);
-  const int behind = at - inside < 4 ? (int)(at - inside) : 4;
+// x[behind .. 3] and zeros after it
+__device__ __forceinline__ source4_t shift_or_zero(const source4_t& x, int64_t behind) {
   source4_t y;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -299,6 +297,12 @@ __device__ __forceinline__ source4_t load_source4_or_zero(const float* line, int
     for (int d = 1; i + d < 4; ++d) y[i] = behind == d ? x[i + d] : y[i];
   }
   return y;
+}
+// line[at .. at + 3] of a line of `count` >= 4 values, zero behind its end: one load inside the line, whatever `at` >= 0
+template <bool STREAMED>
+__device__ __forceinline__ source4_t load_source4_or_zero(const float* line, int64_t at, int64_t count) {
+  const int64_t inside = at < count - 4 ? at : count - 4;
+  return shift_or_zero(load_source4<STREAMED>(line + inside), at - inside);
 }
 
 // Source with k contiguous, X(r, k) = src[k + r * ld].  One block: 64 rows x 32 k, 256 threads, thread t handles row
