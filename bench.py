@@ -258,12 +258,16 @@ class Workload:
         # a small product runs as one launch that reads the FP32 operands itself: no packed copies, no split kernel
         one_launch = (not self.auto) and self.h.plan_info(M, N, K, self.plan_mode_id)["shape"] >= 3
         kernel = "fused_kernel" if one_launch else "product_kernel"
+        traffic = MEASURED_TRAFFIC_BYTES.get(self.name)
+        if not one_launch and split_ms * 1e-3 * PEAK_HBM_GBS * 1e9 < split_bytes:
+            # nothing was split in that time: the plan was carried out by the kernel that splits for itself
+            one_launch, kernel, traffic = True, "wide_kernel", None
         if one_launch:
             product_bytes = (M + N) * K * 4 + M * N * 4 * (2 if self.beta != 0 else 1)
             split_bytes, split_ms = 0, 0.0
         mfma_tflops = PRODUCTS[self.mode] * self.flops / (product_ms * 1e-3) / 1e12
         mfma = {"bound": "mfma", "achieved": round(mfma_tflops, 1), "peak": PEAK_MFMA_16BIT_TFLOPS, "unit": "TFLOP/s",
-                "frac": round(mfma_tflops / PEAK_MFMA_16BIT_TFLOPS, 4), "traffic": MEASURED_TRAFFIC_BYTES.get(self.name),
+                "frac": round(mfma_tflops / PEAK_MFMA_16BIT_TFLOPS, 4), "traffic": traffic,
                 "kernel": kernel, "flops_per_launch": PRODUCTS[self.mode] * self.flops}
         # the same kernel against the HBM roof (it matters for shallow K, where writing C is most of the bytes):
         # algorithmic bytes = packed operands once + C written once (+ read once when beta != 0)

@@ -685,6 +685,69 @@ ecgemm_status_t launch_fused(ecgemm_handle_t h, const Plan& pl, ecgemm_op_t tran
   return ECGEMM_OK;
 }
 
+// Whether a call carries out its plan with the wide kernel, in one pass over the FP32 operands (see wide_kernel.hpp).  The
+// plan stays what it is, the workspace included; the wide kernel sums every element over the same slices in the same
+// order, so this is not part of the plan: ecgemm_product and the automatic mode, which have packed operands, give its bits
+// with the product kernels.
+// For split-first plans whose tiles are all whole or all in slices, where the wide blocks fit the chip in one round: 55
+// random ones, 64 to 20000 deep, took 0.60 to 0.96 of the time (2048 x 2048 x 512 25.3 / 16.5 us, 2048^3 53.3 / 52.5,
+// 1536 x 1088 x 1536 35.8 / 31.1, 8179 x 459 x 676 32.4 / 26.3, 384 x 2112 x 8640 75.3 / 53.4), and in two rounds if the
+// operands are large next to the product (1 / M + 1 / N >= 1 / 800): 40 of them 0.60 to 0.98 (1024 x 1024 x 65536 509 / 437,
+// 512 x 1920 x 21248 184 / 140, 1024 x 2176 x 8448 137 / 134); the nearest beyond that line 1728 x 1728 x 17280 352 / 365
+// and 1344 x 2368 x 20672 496 / 500.  Beyond two rounds, or two rounds of whole tiles, the split is a small part of the
+// call and splitting every element M / 128 or N / 128 times costs more (0.82 to 1.39).
+struct WidePlan {
+  bool use = false;
+  int tiles_m = 0, tiles_n = 0, slices = 1;
+  int64_t slice_depth = 0;
+};
+WidePlan make_wide_plan(const Plan& pl, int64_t M, int64_t N, int64_t K, ecgemm_mode_t mode, int64_t lda, int64_t ldb) {
+  WidePlan w;
+  if (mode != ECGEMM_MODE_FP16_SPLIT || M < kWideTile || N < kWideTile || K < 64 || lda > kWideLargestLd || ldb > kWideLargestLd) return w;
+  const int64_t tiles = ((M + kWideTile - 1) / kWideTile) * ((N + kWideTile - 1) / kWideTile);
+  if (tiles > 2 * kPlanComputeUnits) return w;
+  if (pl.shape->fused || (pl.tail_splits > 1 && pl.full_tiles > 0)) return w;
+  w.slices = pl.tail_splits;
+  w.slice_depth = (int64_t)((pl.k_tiles + pl.tail_splits - 1) / pl.tail_splits) * pl.shape->bk;
+  if ((w.slices - 1) * w.slice_depth >= K) return w;  // (the last slice holds nothing but padding)
+  w.tiles_m = (int)((M + kWideTile - 1) / kWideTile);
+  w.tiles_n = (int)((N + kWideTile - 1) / kWideTile);
+  const int64_t blocks = tiles * w.slices;
+  w.use = blocks <= kPlanComputeUnits || (w.slices > 1 && blocks <= 2 * kPlanComputeUnits && M * N <= 800 * (M + N));
+  return w;
+}
+
+// Steps 1 to 5 of such a call.
+ecgemm_status_t launch_wide(ecgemm_handle_t h, const WidePlan& w, ecgemm_op_t transA, ecgemm_op_t transB, int64_t M, int64_t N,
+                            int64_t K, float alpha, const float* A, int64_t lda, const float* B, int64_t ldb, float beta,
+                            float* C, int64_t ldc, float* partials) {
+  WideParams wp;
+  wp.A = A, wp.B = B;
+  wp.lda = lda, wp.ldb = ldb;
+  wp.M = M, wp.N = N, wp.K = K, wp.ldc = ldc;
+  wp.tiles_m = w.tiles_m, wp.tiles_n = w.tiles_n;
+  wp.alpha = alpha, wp.beta = beta;
+  wp.C = C;
+  wp.slices = w.slices;
+  wp.slice_depth = w.slice_depth;
+  wp.partials = partials;
+  static void (*const kernels[2][2])(WideParams) = {
+      {wide_kernel<kMethodFp16Split, false, false>, wide_kernel<kMethodFp16Split, false, true>},
+      {wide_kernel<kMethodFp16Split, true, false>, wide_kernel<kMethodFp16Split, true, true>}};
+  const int64_t tiles = (int64_t)w.tiles_m * w.tiles_n;
+  void* args[] = {&wp};
+  // op(A)(m, k) = A[k + m lda] if transA == T; op(B)(k, n) = B[k + n ldb] if transB == N
+  ECGEMM_HIP(h, hipLaunchKernel(reinterpret_cast<const void*>(kernels[transA == ECGEMM_OP_T][transB == ECGEMM_OP_N]),
+                                dim3((unsigned)(tiles * w.slices)), dim3(kWideThreads), args, 0, h->stream));
+  if (w.slices > 1) {
+    const dim3 rgrid((unsigned)tiles, kWideTile * kWideTile / 1024);
+    hipLaunchKernelGGL((reduce_tail_kernel<kWideTile, kWideTile>), rgrid, dim3(256), 0, h->stream, partials, w.slices, (int)tiles, 0,
+                       w.tiles_m, w.tiles_n, 4, 1, M, N, alpha, beta, C, ldc, (const int*)nullptr, 0, 0);
+    ECGEMM_HIP(h, hipGetLastError());
+  }
+  return ECGEMM_OK;
+}
+
 // Device memory for this call: the caller's workspace if one is set (never allocating), else the handle's own,
 // grown on demand; or the library's built-in one (never allocating either).
 enum WorkspaceKind { kWorkspaceOfHandle, kWorkspaceBuiltIn };
@@ -1407,6 +1470,9 @@ ecgemm_status_t sgemm_common(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t 
   const Plan pl = make_plan(M, N, K, mode, h->shape, kOneLaunchSliced);
   if (!pl.shape) return no_plan(h, pl, "ecgemm_sgemm");
   if (pl.items() + 16 > 0x7fffffffLL) return bad_arg(h, 4, "ecgemm_sgemm: too many tiles");
+  WidePlan wide;
+  if (h->shape == ECGEMM_SHAPE_AUTO && row_log2_scale_a == nullptr && h->log2_scale_a == 0 && h->log2_scale_b == 0)
+    wide = make_wide_plan(pl, M, N, K, mode, lda, ldb);
   SplitJob job_a, job_b;
   char* ws = nullptr;
   st = acquire_workspace(h, pl.total_bytes, &ws, workspace_kind);
@@ -1414,7 +1480,7 @@ ecgemm_status_t sgemm_common(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t 
   char* a_packed = ws;
   char* b_packed = ws + pl.a_bytes;
   float* partials = pl.tail_splits > 1 ? reinterpret_cast<float*>(ws + pl.a_bytes + pl.b_bytes) : nullptr;
-  if (!pl.shape->fused) {
+  if (!pl.shape->fused && !wide.use) {
     // step 1: op(A) is M x K with rows m; op(B)^T is N x K with rows n.  For B the roles of N and T swap:
     // B stored K x N (transB == N) has k contiguous, i.e. it is the "T" case of the splitter.
     st = make_split_job(h, transA, M, K, A, lda, mode, a_packed, h->log2_scale_a, row_log2_scale_a, &job_a);
@@ -1435,8 +1501,11 @@ ecgemm_status_t sgemm_common(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t 
     ECGEMM_HIP(h, hipEventRecord(tc.start, h->stream));
   }
 
-  if (pl.shape->fused) {
+  if (wide.use) {
     if (timing) ECGEMM_HIP(h, hipEventRecord(tc.split_done, h->stream));  // no split pass: all the time is the product's
+    st = launch_wide(h, wide, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, partials);
+  } else if (pl.shape->fused) {
+    if (timing) ECGEMM_HIP(h, hipEventRecord(tc.split_done, h->stream));
     st = launch_fused(h, pl, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, row_log2_scale_a, col_log2_scale_b, partials);
   } else {
     st = launch_split(h, mode, job_a, &job_b);

@@ -8,6 +8,7 @@
 #include "fused_kernel.hpp"
 #include "product_kernel.hpp"
 #include "split_kernels.hpp"
+#include "wide_kernel.hpp"
 
 namespace ecgemm {
 
@@ -62,6 +63,11 @@ typedef ProductConfig<kMethodFp32, 256, 128, 128, 64, 2, 3, 1> Fp32Config;
 #else
 #define ECGEMM_FUSED_AUTO_GROUP extern
 #endif
+#ifdef ECGEMM_INSTANTIATE_WIDE
+#define ECGEMM_WIDE_GROUP
+#else
+#define ECGEMM_WIDE_GROUP extern
+#endif
 #ifdef ECGEMM_INSTANTIATE_SPLIT
 #define ECGEMM_SPLIT_GROUP
 #else
@@ -114,6 +120,11 @@ ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepthVec, 64)
 ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedRows, 32)
 ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepth, 32)
 ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepthVec, 32)
+
+ECGEMM_WIDE_GROUP template __global__ void wide_kernel<kMethodFp16Split, false, false>(const WideParams);
+ECGEMM_WIDE_GROUP template __global__ void wide_kernel<kMethodFp16Split, false, true>(const WideParams);
+ECGEMM_WIDE_GROUP template __global__ void wide_kernel<kMethodFp16Split, true, false>(const WideParams);
+ECGEMM_WIDE_GROUP template __global__ void wide_kernel<kMethodFp16Split, true, true>(const WideParams);
 
 #define ECGEMM_SPLIT_KERNELS_OF(KIND)                                                                     \
   ECGEMM_SPLIT_GROUP template __global__ void split_kernel<KIND, kSplitKContiguous, false>(const SplitJob);      \

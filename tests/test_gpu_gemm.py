@@ -1133,3 +1133,80 @@ def test_sizes_beyond_the_supported_depth_are_refused():
         h.sgemm(ec.OP_N, ec.OP_N, 1 << 23, 1 << 23, 1, 1.0, dummy, 1 << 23, dummy, 1, 0.0, dummy, 1 << 23, ec.MODE_FP16_SPLIT)
     assert ei.value.status == ec.ERR_INVALID_ARG
     h.destroy()
+
+
+@pytest.mark.parametrize("transA,transB", [("N", "N"), ("N", "T"), ("T", "N"), ("T", "T")])
+@pytest.mark.parametrize("M,N,K,pads", [
+    (2048, 2048, 512, (0, 0, 0)),          # 256 blocks, whole tiles and chunks
+    (1537, 1663, 1000, (1, 3, 1)),         # ragged in every direction, lines on no alignment
+    (1290, 1500, 65, (0, 1, 0)),           # one k behind a chunk
+    (1400, 1285, 127, (3, 0, 2)),          # one k short of two chunks
+    (257, 7070, 190, (0, 2, 0)),           # a last row of tiles with one row of its own; 3 chunks
+    (1500, 2000, 64, (4, 4, 4)),           # one chunk
+    (1024, 1030, 16389, (0, 3, 0)),        # every tile in slices, the last of them ragged
+    (640, 1664, 2752, (1, 0, 0))])
+def test_one_pass_over_the_operands_gives_the_bits_of_the_plan(transA, transB, M, N, K, pads):
+    """A split-first FP16 plan that the kernel of 128 x 128 one-launch blocks carries out: the same bits as the plan's own
+    kernel shape when the caller fixes that, with alpha and beta and without, NaN behind every line, and with values that
+    only the general split takes (infinities, NaN, 2^118) or that saturate."""
+    import torch
+    import paper_2203_03341_amd as ec
+    ops = {"N": ec.OP_N, "T": ec.OP_T}
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    h = ec.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+    plan = h.plan_info(M, N, K, ec.MODE_FP16_SPLIT)
+    assert plan["shape"] in (ec.SHAPE_256x128_W4, ec.SHAPE_128x128_X2)
+
+    def operand(cols, rows, pad):
+        store = torch.full((cols, rows + pad), float("nan"), device="cuda")
+        store[:, :rows] = torch.randn((cols, rows), generator=gen, device="cuda")
+        return store
+
+    A = operand(*((K, M) if transA == "N" else (M, K)), pads[0])
+    B = operand(*((N, K) if transB == "N" else (K, N)), pads[1])
+    C = torch.randn((N, M + pads[2]), generator=gen, device="cuda")
+
+    def call(shape, alpha, beta):
+        out = C.clone()
+        h.set_shape(shape)
+        h.sgemm(ops[transA], ops[transB], M, N, K, alpha, A, A.shape[1], B, B.shape[1], beta, out, C.shape[1], ec.MODE_FP16_SPLIT)
+        torch.cuda.synchronize()
+        return out
+
+    for special in (False, True):
+        if special:
+            A[0, 0], A[A.shape[0] // 2, 3], A[1, 7], A[3, 5] = float("inf"), 1e6, 2.0 ** 118, 65535.9
+            B[B.shape[0] - 1, 2], B[1, 1], B[2, 9] = float("nan"), -70000.0, -float("inf")
+        for alpha, beta in ((1.0, 0.0), (1.5, 0.5)):
+            got, want = call(ec.SHAPE_AUTO, alpha, beta), call(plan["shape"], alpha, beta)
+            assert bool(torch.isnan(want[:, :M]).any()) == special
+            assert torch.equal(torch.isnan(got), torch.isnan(want))
+            assert torch.equal(torch.nan_to_num(got, nan=0.0), torch.nan_to_num(want, nan=0.0)), (special, alpha, beta)
+            assert torch.equal(got[:, M:], C[:, M:])
+    h.destroy()
+
+
+def test_a_deep_product_is_not_split_first():
+    """1024 x 1024 x 32768: the interval in front of the product (ecgemm_set_timing) holds no split pass, whose 0.5 GB the
+    card cannot move in the time; with the shape fixed by the caller it does."""
+    import torch
+    import paper_2203_03341_amd as ec
+    M = N = 1024
+    K = 32768
+    A, B, C = torch.randn((K, M), device="cuda"), torch.randn((N, K), device="cuda"), torch.empty((N, M), device="cuda")
+    split_us = {}
+    for shape in (ec.SHAPE_AUTO, ec.SHAPE_256x128_W4):
+        h = ec.Handle()
+        h.set_stream(torch.cuda.current_stream().cuda_stream)
+        h.set_shape(shape)
+        for timing in (False, True):
+            h.set_timing(timing)
+            for _ in range(5):
+                h.sgemm(ec.OP_N, ec.OP_N, M, N, K, 1.0, A, M, B, K, 0.0, C, M, ec.MODE_FP16_SPLIT)
+        torch.cuda.synchronize()
+        calls, split_ms, _ = h.get_timing()
+        split_us[shape] = split_ms * 1e3 / calls
+        h.destroy()
+    assert split_us[ec.SHAPE_AUTO] < 40 < 60 < split_us[ec.SHAPE_256x128_W4], split_us
