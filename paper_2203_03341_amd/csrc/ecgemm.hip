@@ -49,21 +49,19 @@ namespace {
 typedef void (*reduce_fn_t)(const float*, int, int, int, int, int, int, int, int64_t, int64_t, float, float, float*, int64_t,
                             const int*, int, int);
 struct FusedKernels {
-  void (*kernel[3][3])(FusedParams);  // [FusedLayout of A][FusedLayout of B]
+  void (*kernel[2][2])(FusedParams);  // [FusedLayout of A][FusedLayout of B]
 };
 template <int METHOD, int TILE>
 constexpr FusedKernels fused_kernels_of() {
-  return FusedKernels{{{fused_kernel<METHOD, 0, 0, TILE>, fused_kernel<METHOD, 0, 1, TILE>, fused_kernel<METHOD, 0, 2, TILE>},
-                       {fused_kernel<METHOD, 1, 0, TILE>, fused_kernel<METHOD, 1, 1, TILE>, fused_kernel<METHOD, 1, 2, TILE>},
-                       {fused_kernel<METHOD, 2, 0, TILE>, fused_kernel<METHOD, 2, 1, TILE>, fused_kernel<METHOD, 2, 2, TILE>}}};
+  return FusedKernels{{{fused_kernel<METHOD, 0, 0, TILE>, fused_kernel<METHOD, 0, 1, TILE>},
+                       {fused_kernel<METHOD, 1, 0, TILE>, fused_kernel<METHOD, 1, 1, TILE>}}};
 }
 const FusedKernels kFusedFp16Tile64 = fused_kernels_of<kMethodFp16Split, 64>(), kFusedFp16Tile32 = fused_kernels_of<kMethodFp16Split, 32>(),
                    kFusedBf16Tile64 = fused_kernels_of<kMethodBf16Full, 64>(), kFusedBf16Tile32 = fused_kernels_of<kMethodBf16Full, 32>();
 template <int TILE>
 constexpr FusedKernels fused_auto_kernels_of() {
-  return FusedKernels{{{fused_auto_kernel<0, 0, TILE>, fused_auto_kernel<0, 1, TILE>, fused_auto_kernel<0, 2, TILE>},
-                       {fused_auto_kernel<1, 0, TILE>, fused_auto_kernel<1, 1, TILE>, fused_auto_kernel<1, 2, TILE>},
-                       {fused_auto_kernel<2, 0, TILE>, fused_auto_kernel<2, 1, TILE>, fused_auto_kernel<2, 2, TILE>}}};
+  return FusedKernels{{{fused_auto_kernel<0, 0, TILE>, fused_auto_kernel<0, 1, TILE>},
+                       {fused_auto_kernel<1, 0, TILE>, fused_auto_kernel<1, 1, TILE>}}};
 }
 const FusedKernels kFusedAutoTile64 = fused_auto_kernels_of<64>(), kFusedAutoTile32 = fused_auto_kernels_of<32>();
 struct Shape {
@@ -288,10 +286,10 @@ Plan plan_with_shape(int64_t M, int64_t N, int64_t K, ecgemm_mode_t mode, ecgemm
 //   FP16 mode, 0.46 / 0.76 in BF16 mode; a fifth more for 64 x 64 BF16 blocks once nearly every unit has one) plus
 //   its first loads and its stores, which are nearly free in a single round (0.4 to 1.1 us) and cost 1.6 to 3 us per
 //   round when rounds follow each other.  A last chunk that is not whole counts as a whole one, or as three where the
-//   depth is no multiple of 4: no operand with the depth contiguous is aligned then, which costs more in every chunk.
-//   Three for either, against this, on problems whose plan differs (4 % of random ones with such depths; 103 of them
-//   timed, every storage order): FP16 on average 4 % slower, BF16 5 %, and 37 % faster at worst (an unaligned operand,
-//   which the plan does not see); one instead of three for odd depths: FP16 2 % slower, BF16 3 % faster, 0.74 to 1.27.
+//   depth is no multiple of 4, but for BF16 products up to 1024 deep.  One for either, against this, on problems whose
+//   plan differs (4 % of random ones with such depths; 60 of them timed): FP16, whose split-first plans the wide kernel
+//   carries out, 7 % slower on average, 0.92 to 1.30 of the time; BF16 beyond 1024 deep 0.92 to 1.16, level on average.
+//   Three for BF16 up to 1024 deep: 20 of these 0.75 to 0.93 with one (2746 x 330 x 622 TN 32.3 us / 24.1).
 double split_first_us(const Plan& pl, int64_t M, int64_t N, int64_t K, ecgemm_mode_t mode) {
   const double operand_mb = 4.0 * ((double)M + (double)N) * (double)K / 1e6;
   // (beyond 8.5 us the pass runs at the memory's pace: 8 or 10 bytes moved per element)
@@ -310,7 +308,7 @@ double one_launch_us(const Plan& pl, int64_t K, ecgemm_mode_t mode) {
     const double share = (double)fused_chunks_per_slice(K, pl.tail_splits), partial_mb = pl.partial_bytes / 1e6;
     return 4.4 + (small ? (bf16 ? 0.7 : 0.4) : (bf16 ? 1.1 : 0.8)) + share * per_chunk + 2.2 + 0.35 * partial_mb;
   }
-  const double chunks = (double)(K / 64) + (K % 4 ? 3.0 : K % 64 ? 1.0 : 0.0);
+  const double chunks = (double)(K / 64) + (K % 4 && !(bf16 && K <= 1024) ? 3.0 : K % 64 ? 1.0 : 0.0);
   if (rounds == 1.0) {
     const double nearly_full = (!small && bf16 && blocks_per_unit > 0.9) ? 1.2 : 1.0;
     return 4.4 + (small ? (bf16 ? 0.7 : 0.4) : (bf16 ? 1.1 : 0.8)) + chunks * per_chunk * nearly_full;
@@ -655,10 +653,7 @@ ecgemm_status_t launch_fused(ecgemm_handle_t h, const Plan& pl, ecgemm_op_t tran
   fp.lda = lda;
   fp.ldb = ldb;
   // op(A)(m, k) = A[k + m lda] if transA == T; op(B)(k, n) = B[k + n ldb] if transB == N
-  auto layout_of = [K](bool k_contiguous, const float* base, int64_t ld) {
-    return !k_contiguous ? kFusedRows : (ld % 4 == 0 && (uintptr_t)base % 16 == 0 && K % 4 == 0) ? kFusedDepthVec : kFusedDepth;
-  };
-  const int layout_a = layout_of(transA == ECGEMM_OP_T, A, lda), layout_b = layout_of(transB == ECGEMM_OP_N, B, ldb);
+  const int layout_a = transA == ECGEMM_OP_T ? kFusedDepth : kFusedRows, layout_b = transB == ECGEMM_OP_N ? kFusedDepth : kFusedRows;
   fp.prescale_a = std::ldexp(1.0f, h->log2_scale_a);
   fp.prescale_b = std::ldexp(1.0f, h->log2_scale_b);
   fp.M = M;

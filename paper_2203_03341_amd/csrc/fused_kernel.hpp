@@ -36,11 +36,13 @@ namespace ecgemm {
 // How the V = TILE / 8 values per thread and chunk are laid over one operand's TILE rows x 64 k (X(r, k): op(A)(m, k)
 // or op(B)(k, n) with r = n), wave w, lane l:
 //   kFusedRows      r contiguous, X(r, k) = src[r + k ld]: row l % TILE, the V consecutive k from 8 w + V (l / TILE)
-//   kFusedDepth     k contiguous, X(r, k) = src[k + r ld]: k = l, rows V w .. V w + V - 1
-//   kFusedDepthVec  k contiguous, base and ld multiples of 16 bytes, K a multiple of 4: the four values k = 4 (l % 16) ..
-//                   + 3 of rows w + 8 (l / 16) + 32 j, j = 0 .. V / 4 - 1, one 16-byte load each (rows 8 apart: with
-//                   the rotation of fused_lds_slot the 64 lanes of a write then go to 64 different places of a bank period)
-enum FusedLayout { kFusedRows = 0, kFusedDepth = 1, kFusedDepthVec = 2 };
+//   kFusedDepth     k contiguous, X(r, k) = src[k + r ld]: the four values k = 4 (l % 16) .. + 3 of rows w + 8 (l / 16) + 32 j,
+//                   j = 0 .. V / 4 - 1, one 16-byte load each, at any multiple of four bytes (rows 8 apart: with the
+//                   rotation of fused_lds_slot the 64 lanes of a write then go to 64 different places of a bank period).
+//                   Lines on no alignment, or a depth that is no multiple of four, read one value per lane before: 1024^3
+//                   TN with odd leading dimensions FP16 21.0 us / 14.1, BF16 27.0 / 18.1, 512^3 9.7 / 7.7 and 11.5 / 8.9, 300 x
+//                   200 x 77 TT BF16 6.96 / 6.57; aligned operands, FP16 256^3 NN 6.0 / 6.1, 512^3 7.3 / 7.4.
+enum FusedLayout { kFusedRows = 0, kFusedDepth = 1 };
 // Chunks in flight in registers (the loop is unrolled by this: a register ring is indexed statically).  Four and six
 // instead of two measured slower at every size (1024^3: 18.9 and 29.6 against 18.1 us).
 constexpr int kFusedRing = 2;
@@ -87,10 +89,10 @@ struct FusedOperand {
   static_assert(TILE == 64 || TILE == 32, "tile sizes");
   static constexpr int NP = parts_of_split(KIND);
   static constexpr int V = TILE / kFusedSplitWaves;                                      // values per thread and chunk
-  static constexpr int ROWS = LAYOUT == kFusedRows ? 1 : LAYOUT == kFusedDepth ? V : V / 4;  // rows this thread holds values of
+  static constexpr int ROWS = LAYOUT == kFusedRows ? 1 : V / 4;                            // rows this thread holds values of
   static constexpr int PER_ROW = V / ROWS;                                               // consecutive k per row
   static constexpr int REGION_BYTES = (TILE / 32) * 4 * NP * 1024;  // a chunk of one operand in LDS: [row block][k step][part] x 1 KiB
-  static constexpr int LOADS = LAYOUT == kFusedDepthVec ? ROWS : V;  // load instructions per thread and chunk
+  static constexpr int LOADS = LAYOUT == kFusedDepth ? ROWS : V;     // load instructions per thread and chunk
   static constexpr int64_t kLargestShortLd = (int64_t)1 << 23;       // up to here every value of a chunk lies within 2^32 bytes of its first
 
   // Addresses are a part that is the same for the whole wave plus a small per-lane offset wherever the layout allows
@@ -98,20 +100,19 @@ struct FusedOperand {
   // (its values end up in rows or columns of the tile that are never stored).
   const float* tile;           // &X(first row of the tile, 0)
   const float* row_ptr[ROWS];  // &X(row, 0) for each of the thread's rows
-  unsigned lane_offset;        // kFusedRows: the lane's row within the tile; kFusedDepth: the lane's k within the chunk
+  unsigned lane_offset;        // kFusedRows: the lane's row within the tile
   float factor[ROWS];          // the handle's pre-scaling times the row's own
   bool unscaled;               // every factor is 1 (the same for the whole block)
   int64_t ld, K;
   int k_here;                  // k within the chunk of the thread's first value
   // byte offset within the operand's region, part 0, of the thread's first value (kFusedRows), of the first value of
-  // each of its rows (kFusedDepthVec); kFusedDepth: of row 0 at the thread's k, before the rotation
-  int lds_offset[LAYOUT == kFusedDepthVec ? ROWS : 1];
+  // each of its rows (kFusedDepth)
+  int lds_offset[ROWS];
   int first_row;               // within the tile
   // A whole chunk, when ld <= kLargestShortLd: load i reads at &X(first row of the tile, 64 c) + offset[i] bytes, an
   // address that is the same for the wave plus 32 bits per lane that never change, so a chunk's loads need no
-  // address arithmetic at all.  (kFusedDepth: a wave's rows are the same for all its lanes, row_ptr is not a vector
-  // and serves as it is.)
-  unsigned offset[LAYOUT == kFusedDepth ? 1 : LOADS];
+  // address arithmetic at all.
+  unsigned offset[LOADS];
   int64_t chunk_bytes;         // from one chunk's first value to the next one's
 
   __device__ __forceinline__ void init(const float* src, int64_t ld_, int64_t rows, int64_t K_, int64_t tile_row0, float prescale,
@@ -123,16 +124,13 @@ struct FusedOperand {
     if constexpr (LAYOUT == kFusedRows) {
       first_row = lane % TILE, k_here = (64 / kFusedSplitWaves) * wave + V * (lane / TILE);
       lane_offset = (unsigned)(first_row < rows_here ? first_row : rows_here - 1);
-    } else if constexpr (LAYOUT == kFusedDepth) {
-      first_row = V * wave, k_here = lane;
-      lane_offset = (unsigned)lane;
     } else {
       first_row = wave + 8 * (lane >> 4), k_here = 4 * (lane & 15);
       lane_offset = 0;
     }
 #pragma unroll
     for (int j = 0; j < ROWS; ++j) {
-      const int row = first_row + (LAYOUT == kFusedDepthVec ? 32 * j : j);
+      const int row = first_row + 32 * j;
       const int row_clamped = row < rows_here ? row : rows_here - 1;
       row_ptr[j] = tile + (LAYOUT == kFusedRows ? (int64_t)row_clamped : row_clamped * ld);
       factor[j] = prescale;
@@ -140,35 +138,25 @@ struct FusedOperand {
     }
     const bool short_ld = ld <= kLargestShortLd;  // else `offset` is not used
     chunk_bytes = LAYOUT == kFusedRows ? 256 * ld : 256;
-    offset[0] = 0;
-    if constexpr (LAYOUT != kFusedDepth) {
 #pragma unroll
-      for (int i = 0; i < LOADS; ++i) {
-        if constexpr (LAYOUT == kFusedRows) {
-          offset[i] = short_ld ? (unsigned)(((k_here + i) * ld + lane_offset) * 4) : 0u;
-        } else {
-          const int row = first_row + 32 * i;
-          const int row_clamped = row < rows_here ? row : rows_here - 1;
-          offset[i] = short_ld ? (unsigned)((row_clamped * ld + k_here) * 4) : 0u;
-        }
+    for (int i = 0; i < LOADS; ++i) {
+      if constexpr (LAYOUT == kFusedRows) {
+        offset[i] = short_ld ? (unsigned)(((k_here + i) * ld + lane_offset) * 4) : 0u;
+      } else {
+        const int row = first_row + 32 * i;
+        const int row_clamped = row < rows_here ? row : rows_here - 1;
+        offset[i] = short_ld ? (unsigned)((row_clamped * ld + k_here) * 4) : 0u;
       }
     }
-    if constexpr (LAYOUT == kFusedRows) {
-      static_assert(V <= 8, "a thread's values lie in one half of a k step");
-      lds_offset[0] = fused_lds_slot<NP>(first_row, k_here);
-    } else if constexpr (LAYOUT == kFusedDepthVec) {
+    static_assert(LAYOUT != kFusedRows || V <= 8, "a thread's values lie in one half of a k step");
 #pragma unroll
-      for (int j = 0; j < ROWS; ++j) lds_offset[j] = fused_lds_slot<NP>(first_row + 32 * j, k_here);
-    } else {
-      static_assert(V <= 32, "a thread's rows lie in one block of 32");
-      lds_offset[0] = (k_here >> 4) * NP * 1024 + ((k_here >> 3) & 1) * 512 + (k_here & 7) * 2;
-    }
+    for (int j = 0; j < ROWS; ++j) lds_offset[j] = fused_lds_slot<NP>(first_row + 32 * j, k_here);
   }
 
-  // Requests the values of chunk c (which exists).  Every address is valid: in the last chunk, k beyond the depth is
-  // clamped to the last k (and replaced by zero in deposit()).  No load sits under a condition and both branches
-  // issue the same number of loads, so the number in flight is the same on every path: the waits that the compiler
-  // places count them.
+  // Requests the values of chunk c (which exists).  Every address is valid, given that the operand is at least four deep
+  // (kFusedDepth; the slice of it that the block takes need not be): in the last chunk, k beyond the depth is clamped
+  // (complete() does the rest).  No load sits under a condition and both branches issue the same number of loads, so the
+  // number in flight is the same on every path: the waits that the compiler places count them.
   __device__ __forceinline__ void fetch(float (&x)[V], int c) const {
     const int64_t chunk_k = (int64_t)c * 64;
     if (chunk_k + 64 <= K) {  // block-uniform
@@ -176,34 +164,53 @@ struct FusedOperand {
         const float* first = tile + chunk_k * ld;
 #pragma unroll
         for (int i = 0; i < V; ++i) x[i] = first[(k_here + i) * ld + lane_offset];
-      } else if constexpr (LAYOUT == kFusedDepth) {
-#pragma unroll
-        for (int j = 0; j < V; ++j) x[j] = (row_ptr[j] + chunk_k)[lane_offset];
       } else {
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
-          const float4 v = *reinterpret_cast<const float4*>(row_ptr[j] + chunk_k + k_here);
-          x[4 * j] = v.x, x[4 * j + 1] = v.y, x[4 * j + 2] = v.z, x[4 * j + 3] = v.w;
+          const source4_t v = load_source4<false>(row_ptr[j] + chunk_k + k_here);
+          x[4 * j] = v[0], x[4 * j + 1] = v[1], x[4 * j + 2] = v[2], x[4 * j + 3] = v[3];
         }
       }
     } else {
       const int64_t k0 = chunk_k + k_here;
-      if constexpr (LAYOUT == kFusedDepthVec) {
-        // K is a multiple of 4 here (the host's condition for this layout): four values that start below K end below it
-        const int64_t k = k0 < K ? k0 : K - 4;
+      if constexpr (LAYOUT == kFusedRows) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) x[e] = row_ptr[0][(k0 + e < K ? k0 + e : K - 1) * ld];
+      } else {
+        const int64_t k = k0 < K - 4 ? k0 : K - 4;
 #pragma unroll
         for (int j = 0; j < ROWS; ++j) {
-          const float4 v = *reinterpret_cast<const float4*>(row_ptr[j] + k);
-          x[4 * j] = v.x, x[4 * j + 1] = v.y, x[4 * j + 2] = v.z, x[4 * j + 3] = v.w;
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-          const int64_t k = k0 + e % PER_ROW < K ? k0 + e % PER_ROW : K - 1;
-          x[e] = LAYOUT == kFusedRows ? row_ptr[0][k * ld] : row_ptr[e][k];
+          const source4_t v = load_source4<false>(row_ptr[j] + k);
+          x[4 * j] = v[0], x[4 * j + 1] = v[1], x[4 * j + 2] = v[2], x[4 * j + 3] = v[3];
         }
       }
     }
+  }
+  // The values of the last chunk where the depth ends inside it, as fetch() left them: k beyond the depth counts as zero.
+  __device__ __forceinline__ void complete(const float (&x)[V], int c, float (&v)[V]) const {
+    const int left = (int)(K - (int64_t)c * 64) - k_here;  // values of each row that lie inside the depth, from this thread's first on
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) {
+      if constexpr (LAYOUT == kFusedDepth) {
+        const source4_t y = shift_or_zero(source4_t{x[4 * j], x[4 * j + 1], x[4 * j + 2], x[4 * j + 3]}, left < 4 ? 4 - left : 0);
+        v[4 * j] = y[0], v[4 * j + 1] = y[1], v[4 * j + 2] = y[2], v[4 * j + 3] = y[3];
+      } else {
+#pragma unroll
+        for (int e = 0; e < V; ++e) v[e] = e < left ? x[e] : 0.0f;
+      }
+    }
+  }
+  // Fetches, splits and writes the one chunk of an operand less than four deep, value by value.
+  __device__ __forceinline__ void deposit_shallow(char* region) const {
+    float v[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const int64_t k = k_here + e % PER_ROW;
+      v[e] = k < K ? row_ptr[e / PER_ROW][LAYOUT == kFusedRows ? k * ld : k] : 0.0f;
+    }
+    unsigned words[V / 2][NP];
+    split_with_care(v, words);
+    write(words, region);
   }
 
   // The same for a chunk that lies inside the depth, ld <= kLargestShortLd.
@@ -213,19 +220,15 @@ struct FusedOperand {
     // per load through the loop in vector registers and advance each of them every chunk, or widen the offsets to 64
     // bits outside the loop and add the base to each with a vector instruction.)
     asm volatile("" : "+s"(first));
-    if constexpr (LAYOUT != kFusedDepth) {
 #pragma unroll
-      for (int i = 0; i < LOADS; ++i) asm volatile("" : "+v"(offset[i]));
-    }
+    for (int i = 0; i < LOADS; ++i) asm volatile("" : "+v"(offset[i]));
     typedef __attribute__((address_space(1))) char global_char_t;  // (what passed through the line above is no longer known to be global memory)
-    typedef float plain_float4_t __attribute__((ext_vector_type(4)));
+    typedef float plain_float4_t __attribute__((ext_vector_type(4), aligned(4)));
     typedef __attribute__((address_space(1))) plain_float4_t global_float4_t;
     const global_char_t* chunk = (const global_char_t*)first;
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
       if constexpr (LAYOUT == kFusedDepth) {
-        x[i] = (row_ptr[i] + (int64_t)c * 64)[lane_offset];
-      } else if constexpr (LAYOUT == kFusedDepthVec) {
         const plain_float4_t v = *reinterpret_cast<const global_float4_t*>(chunk + offset[i]);
         x[4 * i] = v[0], x[4 * i + 1] = v[1], x[4 * i + 2] = v[2], x[4 * i + 3] = v[3];
       } else {
@@ -250,43 +253,28 @@ struct FusedOperand {
     return FastSplit<KIND>::ordinary(largest);
   }
 
-  // Splitter on all V values; k beyond the depth (last chunk) counts as zero.
-  __device__ __forceinline__ void split_with_care(const float (&x)[V], int c, unsigned (&words)[V / 2][NP]) const {
-    const int64_t k0 = (int64_t)c * 64 + k_here;
+  // Splitter on all V values.
+  __device__ __forceinline__ void split_with_care(const float (&x)[V], unsigned (&words)[V / 2][NP]) const {
 #pragma unroll
     for (int e = 0; e < V / 2; ++e) {
       unsigned short even[NP], odd[NP];
-      Splitter<KIND>::split(k0 + (2 * e) % PER_ROW < K ? x[2 * e] * factor[(2 * e) / PER_ROW] : 0.0f, even);
-      Splitter<KIND>::split(k0 + (2 * e + 1) % PER_ROW < K ? x[2 * e + 1] * factor[(2 * e + 1) / PER_ROW] : 0.0f, odd);
+      Splitter<KIND>::split(x[2 * e] * factor[(2 * e) / PER_ROW], even);
+      Splitter<KIND>::split(x[2 * e + 1] * factor[(2 * e + 1) / PER_ROW], odd);
 #pragma unroll
       for (int q = 0; q < NP; ++q) words[e][q] = (unsigned)even[q] | ((unsigned)odd[q] << 16);
     }
   }
 
-  // Splits the values of chunk c and writes the parts to `region` where the fragment reads expect them.
-  __device__ __forceinline__ void deposit(const float (&x)[V], int c, char* region) const {
-    unsigned words[V / 2][NP];  // part q of values 2 e and 2 e + 1
-    const bool whole = (int64_t)c * 64 + 64 <= K;  // block-uniform
-    bool done = false;
-    if (whole) {
-      // (block-uniform: without pre-scaling and scaling vectors every factor is 1)
-      const bool ordinary = unscaled ? split_ordinary<false>(x, words) : split_ordinary<true>(x, words);
-      done = __builtin_amdgcn_ballot_w64(!ordinary) == 0;  // wave-uniform
-    }
-    if (!done) split_with_care(x, c, words);
-    write(words, region);
-  }
-
-  // The same for a chunk that lies inside the depth, with what is the same for the whole block decided by the caller:
-  // GENERAL == false if every factor is 1.
+  // Splits the values of a chunk that lies inside the depth and writes the parts to `region` where the fragment reads
+  // expect them.  GENERAL == false: every factor is 1.
   template <bool GENERAL>
-  __device__ __forceinline__ void deposit_whole(const float (&x)[V], int c, char* region) const {
+  __device__ __forceinline__ void deposit_whole(const float (&x)[V], char* region) const {
     unsigned words[V / 2][NP];
     const bool ordinary = split_ordinary<GENERAL>(x, words);
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(!ordinary) != 0, 0)) {
       // (with a write of its own: joining the two paths in front of one write costs a register copy per word)
       unsigned careful[V / 2][NP];
-      split_with_care(x, c, careful);
+      split_with_care(x, careful);
       write(careful, region);
     } else {
       write(words, region);
@@ -298,15 +286,13 @@ struct FusedOperand {
   // both operands transposed, takes 6.95 us against 7.36).
   template <bool GENERAL>
   __device__ __forceinline__ void deposit_last(const float (&x)[V], int c, char* region) const {
-    const int left = (int)(K - (int64_t)c * 64) - k_here;  // values of each row that lie inside the depth, from this thread's first on
     float v[V];
-#pragma unroll
-    for (int e = 0; e < V; ++e) v[e] = e % PER_ROW < left ? x[e] : 0.0f;
+    complete(x, c, v);
     // (one write for both paths, unlike deposit_whole: another copy of its two moves the registers of the loop over the
     // whole chunks, 192 x 1920 x 62912 TT in FP16 mode 334 us with this, 345 with that)
     unsigned words[V / 2][NP];
     const bool ordinary = split_ordinary<GENERAL>(v, words);
-    if (__builtin_amdgcn_ballot_w64(!ordinary) != 0) split_with_care(v, c, words);
+    if (__builtin_amdgcn_ballot_w64(!ordinary) != 0) split_with_care(v, words);
     write(words, region);
   }
 
@@ -325,14 +311,6 @@ struct FusedOperand {
         } else {
           static_assert(V == 4, "half of an 8-deep run");
           *reinterpret_cast<uint2_t*>(base + q * 1024) = uint2_t{words[0][q], words[1][q]};
-        }
-      } else if constexpr (LAYOUT == kFusedDepth) {  // one k of consecutive rows
-#pragma unroll
-        for (int e = 0; e < V / 2; ++e) {
-          const int row = first_row + 2 * e, rotation = fused_lds_rotation(k_here);
-          char* block = base + (row >> 5) * 4 * NP * 1024 + q * 1024;
-          *reinterpret_cast<unsigned short*>(block + ((row + rotation) & 31) * 16) = (unsigned short)words[e][q];
-          *reinterpret_cast<unsigned short*>(block + ((row + 1 + rotation) & 31) * 16) = (unsigned short)(words[e][q] >> 16);
         }
       } else {  // four consecutive k of each of the thread's rows
 #pragma unroll
@@ -366,6 +344,7 @@ __device__ __forceinline__ void fused_block(FusedParams p, char* lds) {
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   int tile_index = (int)blockIdx.x, slice = 0;
+  const bool shallow = p.K < 4;  // (then there are no slices and one chunk)
   if (p.k_slices > 1) {  // the block's slice of the depth is a product of its own from here on
     const int tiles = p.tiles_m * p.tiles_n;
     slice = tile_index / tiles, tile_index -= slice * tiles;
@@ -389,6 +368,12 @@ __device__ __forceinline__ void fused_block(FusedParams p, char* lds) {
     OperandB b;
     a.init(p.A, p.lda, p.M, p.K, (int64_t)tile_m * BM, p.prescale_a, p.row_log2_scale, lane, wave);
     b.init(p.B, p.ldb, p.N, p.K, (int64_t)tile_n * BN, p.prescale_b, p.col_log2_scale, lane, wave);
+    if ((LAYOUT_A == kFusedDepth || LAYOUT_B == kFusedDepth) && __builtin_expect(shallow, 0)) {
+      a.deposit_shallow(lds);
+      b.deposit_shallow(lds + REGION_BYTES);
+      __syncthreads();
+      return;
+    }
     static_assert(kFusedRing % 2 == 0, "a ring slot always meets the same LDS buffer");
     float xa[kFusedRing][V], xb[kFusedRing][V];
     // (a chunk beyond the last is requested again as the last one and never used: in the loop every fetch is
@@ -403,17 +388,18 @@ __device__ __forceinline__ void fused_block(FusedParams p, char* lds) {
     int c0 = 0;
     // The bulk of the depth: chunks that lie inside it and whose successors in the ring do too, so that nothing in
     // the loop depends on where the depth ends, and what is the same for the whole block (are there scaling factors?)
-    // is decided outside it.  Ring slot r holds chunk c0 + r at the top of every loop here.  The loops further down,
-    // which decide everything chunk by chunk, are for the calls that cannot take this one.
+    // is decided outside it.  Ring slot r holds chunk c0 + r at the top of every loop here.
     auto bulk = [&](auto general_c) {
       constexpr bool GENERAL = decltype(general_c)::value;
       const int whole_chunks = (int)(p.K / 64);
-      for (; c0 + 2 * kFusedRing <= whole_chunks; c0 += kFusedRing) {
+      // (leading dimensions beyond 2^23 take the loop further down throughout)
+      const int bulk_chunks = p.lda <= OperandA::kLargestShortLd && p.ldb <= OperandB::kLargestShortLd ? whole_chunks : 0;
+      for (; c0 + 2 * kFusedRing <= bulk_chunks; c0 += kFusedRing) {
         static_for<kFusedRing>([&](auto r_c) {
           constexpr int r = decltype(r_c)::value;
           char* stage = lds + (r & 1) * STAGE_BYTES;
-          a.template deposit_whole<GENERAL>(xa[r], c0 + r, stage);
-          b.template deposit_whole<GENERAL>(xb[r], c0 + r, stage + REGION_BYTES);
+          a.template deposit_whole<GENERAL>(xa[r], stage);
+          b.template deposit_whole<GENERAL>(xb[r], stage + REGION_BYTES);
           __builtin_amdgcn_sched_barrier(0);
           a.fetch_whole(xa[r], c0 + r + kFusedRing), b.fetch_whole(xb[r], c0 + r + kFusedRing);
           __syncthreads();
@@ -429,8 +415,8 @@ __device__ __forceinline__ void fused_block(FusedParams p, char* lds) {
           if (c < chunks) {
             char* stage = lds + (r & 1) * STAGE_BYTES;
             if (__builtin_expect(c < whole_chunks, 1)) {
-              a.template deposit_whole<GENERAL>(xa[r], c, stage);
-              b.template deposit_whole<GENERAL>(xb[r], c, stage + REGION_BYTES);
+              a.template deposit_whole<GENERAL>(xa[r], stage);
+              b.template deposit_whole<GENERAL>(xb[r], stage + REGION_BYTES);
             } else {
               a.template deposit_last<GENERAL>(xa[r], c, stage);
               b.template deposit_last<GENERAL>(xb[r], c, stage + REGION_BYTES);
@@ -442,37 +428,10 @@ __device__ __forceinline__ void fused_block(FusedParams p, char* lds) {
         c0 += kFusedRing;
       }
     };
-    // (kFusedDepth, the layout of last resort, only next to kFusedRows: with one row pointer and one factor per
-    // value it leaves no registers for a second copy of the loop next to another depth-contiguous operand)
-    if constexpr ((LAYOUT_A != kFusedDepth && LAYOUT_B != kFusedDepth) || LAYOUT_A == kFusedRows || LAYOUT_B == kFusedRows) {
-      if (p.lda <= OperandA::kLargestShortLd && p.ldb <= OperandB::kLargestShortLd) {  // block-uniform
-        if (a.unscaled && b.unscaled)
-          bulk(std::false_type{});
-        else
-          bulk(std::true_type{});  // (a factor of 1 changes no bit)
-      }
-    }
-    for (; c0 + kFusedRing <= chunks; c0 += kFusedRing) {
-      static_for<kFusedRing>([&](auto r_c) {
-        constexpr int r = decltype(r_c)::value;
-        const int c = c0 + r, ahead = c + kFusedRing < last ? c + kFusedRing : last;
-        char* stage = lds + (r & 1) * STAGE_BYTES;
-        a.deposit(xa[r], c, stage);
-        b.deposit(xb[r], c, stage + REGION_BYTES);
-        __builtin_amdgcn_sched_barrier(0);
-        a.fetch(xa[r], ahead), b.fetch(xb[r], ahead);
-        __syncthreads();
-      });
-    }
-    static_for<kFusedRing - 1>([&](auto r_c) {  // the chunks left over: their values are on their way or here
-      constexpr int r = decltype(r_c)::value;
-      if (c0 + r < chunks) {  // block-uniform
-        char* stage = lds + (r & 1) * STAGE_BYTES;
-        a.deposit(xa[r], c0 + r, stage);
-        b.deposit(xb[r], c0 + r, stage + REGION_BYTES);
-        __syncthreads();
-      }
-    });
+    if (a.unscaled && b.unscaled)  // block-uniform
+      bulk(std::false_type{});
+    else
+      bulk(std::true_type{});  // (a factor of 1 changes no bit)
     return;
   }
 

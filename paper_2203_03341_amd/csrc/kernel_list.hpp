@@ -99,27 +99,21 @@ ECGEMM_COMPARE_B_GROUP template __global__ void product_kernel<PlainBf16Config, 
 ECGEMM_COMPARE_B_GROUP template __global__ void product_kernel<Fp32Config, false>(const ProductParams);
 #define ECGEMM_FUSED_KERNELS_OF(METHOD, LAYOUT_A, TILE)                                                            \
   ECGEMM_FUSED_GROUP template __global__ void fused_kernel<METHOD, LAYOUT_A, kFusedRows, TILE>(const FusedParams);   \
-  ECGEMM_FUSED_GROUP template __global__ void fused_kernel<METHOD, LAYOUT_A, kFusedDepth, TILE>(const FusedParams);  \
-  ECGEMM_FUSED_GROUP template __global__ void fused_kernel<METHOD, LAYOUT_A, kFusedDepthVec, TILE>(const FusedParams);
+  ECGEMM_FUSED_GROUP template __global__ void fused_kernel<METHOD, LAYOUT_A, kFusedDepth, TILE>(const FusedParams);
 #define ECGEMM_FUSED_KERNELS_OF_METHOD(METHOD)           \
   ECGEMM_FUSED_KERNELS_OF(METHOD, kFusedRows, 64)        \
   ECGEMM_FUSED_KERNELS_OF(METHOD, kFusedDepth, 64)       \
-  ECGEMM_FUSED_KERNELS_OF(METHOD, kFusedDepthVec, 64)    \
   ECGEMM_FUSED_KERNELS_OF(METHOD, kFusedRows, 32)        \
-  ECGEMM_FUSED_KERNELS_OF(METHOD, kFusedDepth, 32)       \
-  ECGEMM_FUSED_KERNELS_OF(METHOD, kFusedDepthVec, 32)
+  ECGEMM_FUSED_KERNELS_OF(METHOD, kFusedDepth, 32)
 ECGEMM_FUSED_KERNELS_OF_METHOD(kMethodFp16Split)
 ECGEMM_FUSED_KERNELS_OF_METHOD(kMethodBf16Full)
 #define ECGEMM_FUSED_AUTO_KERNELS_OF(LAYOUT_A, TILE)                                                                    \
   ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<LAYOUT_A, kFusedRows, TILE>(const FusedParams);   \
-  ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<LAYOUT_A, kFusedDepth, TILE>(const FusedParams);  \
-  ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<LAYOUT_A, kFusedDepthVec, TILE>(const FusedParams);
+  ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<LAYOUT_A, kFusedDepth, TILE>(const FusedParams);
 ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedRows, 64)
 ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepth, 64)
-ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepthVec, 64)
 ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedRows, 32)
 ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepth, 32)
-ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepthVec, 32)
 
 ECGEMM_WIDE_GROUP template __global__ void wide_kernel<kMethodFp16Split, false, false>(const WideParams);
 ECGEMM_WIDE_GROUP template __global__ void wide_kernel<kMethodFp16Split, false, true>(const WideParams);

@@ -1210,3 +1210,71 @@ def test_a_deep_product_is_not_split_first():
         split_us[shape] = split_ms * 1e3 / calls
         h.destroy()
     assert split_us[ec.SHAPE_AUTO] < 40 < 60 < split_us[ec.SHAPE_256x128_W4], split_us
+
+
+@pytest.mark.parametrize("mode", ["fp16", "bf16"])
+@pytest.mark.parametrize("transA,transB", [("T", "N"), ("N", "N"), ("T", "T")])
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 61, 63, 66, 127, 509])
+def test_one_launch_shapes_on_lines_of_any_alignment(transA, transB, K, mode):
+    """Operands with the depth contiguous are read 16 bytes at a time wherever their lines start: depths shorter than one
+    such read, ending inside one, inside a chunk and just behind one, lines padded by 0 to 3 values (NaN), a base that is
+    not 16-byte aligned; ordinary values, and some that the general split takes.  The bits of the split-first shape (one
+    slice of the depth)."""
+    import torch
+    import paper_2203_03341_amd as ec
+    mode_id = _modes()[mode]
+    ops = {"N": ec.OP_N, "T": ec.OP_T}
+    M, N = 70, 45
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    h = ec.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+
+    def operand(cols, rows, pad, offset):
+        flat = torch.full((offset + (cols - 1) * (rows + pad) + rows,), float("nan"), device="cuda")    # (nothing behind the last value)
+        lines = flat[offset:].as_strided((cols, rows), (rows + pad, 1))
+        lines.copy_(torch.randn((cols, rows), generator=gen, device="cuda"))
+        return flat[offset:], lines, rows + pad
+
+    for pad, offset, special in ((0, 0, False), (1, 1, False), (2, 3, True), (3, 0, True)):
+        A, lines_a, lda = operand(*((K, M) if transA == "N" else (M, K)), pad, offset)
+        B, lines_b, ldb = operand(*((N, K) if transB == "N" else (K, N)), pad, offset)
+        if special:
+            lines_a[0, 0], lines_b[-1, -1] = 1e6, float("inf")
+        out = {}
+        for shape in (ec.SHAPE_128x128_X2, ec.SHAPE_64x64_FUSED, ec.SHAPE_32x32_FUSED):
+            h.set_shape(shape)
+            out[shape] = torch.zeros((N, M), device="cuda")
+            h.sgemm(ops[transA], ops[transB], M, N, K, 1.0, A, lda, B, ldb, 0.0, out[shape], M, mode_id)
+        torch.cuda.synchronize()
+        want = out[ec.SHAPE_128x128_X2]
+        assert bool(torch.isfinite(want).all()) != special
+        for shape in (ec.SHAPE_64x64_FUSED, ec.SHAPE_32x32_FUSED):
+            assert torch.equal(torch.isnan(out[shape]), torch.isnan(want))
+            assert torch.equal(torch.nan_to_num(out[shape], nan=0.0), torch.nan_to_num(want, nan=0.0)), (pad, offset, shape)
+    h.destroy()
+
+
+@pytest.mark.parametrize("mode", ["fp16", "bf16"])
+@pytest.mark.parametrize("K", [4097, 4098, 4099, 4161])
+def test_one_launch_slices_that_end_in_a_few_values(K, mode):
+    """A deep product of few tiles whose last slice is 1, 2, 3 or 65 deep, lines on no alignment: element by element within
+    one rounding of the FP32 sum per eight products of the exact product, (K / 8 + 4) 2^-23 |A| |B|."""
+    import torch
+    import paper_2203_03341_amd as ec
+    mode_id = _modes()[mode]
+    M = N = 128
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    h = ec.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+    plan = h.plan_info(M, N, K, mode_id)
+    assert plan["shape"] >= ec.SHAPE_64x64_FUSED and plan["slices"] > 1
+    A, B = torch.randn((M, K + 1), generator=gen, device="cuda"), torch.randn((N, K + 1), generator=gen, device="cuda")
+    A[:, K], B[:, K] = float("nan"), float("nan")
+    C = torch.zeros((N, M), device="cuda")
+    h.sgemm(ec.OP_T, ec.OP_N, M, N, K, 1.0, A, K + 1, B, K + 1, 0.0, C, M, mode_id)
+    torch.cuda.synchronize()
+    a, b = A[:, :K].double().cpu(), B[:, :K].double().cpu()
+    assert bool(((C.double().cpu() - b @ a.t()).abs() <= (K / 8 + 4) * 2.0 ** -23 * (b.abs() @ a.abs().t())).all())
+    h.destroy()
