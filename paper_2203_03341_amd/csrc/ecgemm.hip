@@ -58,12 +58,17 @@ constexpr FusedKernels fused_kernels_of() {
 }
 const FusedKernels kFusedFp16Tile64 = fused_kernels_of<kMethodFp16Split, 64>(), kFusedFp16Tile32 = fused_kernels_of<kMethodFp16Split, 32>(),
                    kFusedBf16Tile64 = fused_kernels_of<kMethodBf16Full, 64>(), kFusedBf16Tile32 = fused_kernels_of<kMethodBf16Full, 32>();
-template <int TILE>
-constexpr FusedKernels fused_auto_kernels_of() {
-  return FusedKernels{{{fused_auto_kernel<0, 0, TILE>, fused_auto_kernel<0, 1, TILE>},
-                       {fused_auto_kernel<1, 0, TILE>, fused_auto_kernel<1, 1, TILE>}}};
+struct FusedAutoKernels {
+  void (*kernel[2][2])(FusedParams, RowSums);
+};
+template <bool CHOOSES, int TILE>
+constexpr FusedAutoKernels fused_auto_kernels_of() {
+  return FusedAutoKernels{{{fused_auto_kernel<CHOOSES, 0, 0, TILE>, fused_auto_kernel<CHOOSES, 0, 1, TILE>},
+                           {fused_auto_kernel<CHOOSES, 1, 0, TILE>, fused_auto_kernel<CHOOSES, 1, 1, TILE>}}};
 }
-const FusedKernels kFusedAutoTile64 = fused_auto_kernels_of<64>(), kFusedAutoTile32 = fused_auto_kernels_of<32>();
+// [the kernel makes the choice][tiles of 32]
+const FusedAutoKernels kFusedAuto[2][2] = {{fused_auto_kernels_of<false, 64>(), fused_auto_kernels_of<false, 32>()},
+                                           {fused_auto_kernels_of<true, 64>(), fused_auto_kernels_of<true, 32>()}};
 struct Shape {
   void (*product)(ProductParams);  // steps 2 to 5 on packed operands, or
   void (*product_scaled)(ProductParams);  // the instance to prefer for calls with scaling vectors, if the mode has one
@@ -636,7 +641,7 @@ ecgemm_status_t launch_fused(ecgemm_handle_t h, const Plan& pl, ecgemm_op_t tran
                              int64_t K, float alpha, const float* A, int64_t lda, const float* B, int64_t ldb, float beta,
                              float* C, int64_t ldc, const int* row_log2_scale, const int* col_log2_scale, float* partials = nullptr,
                              const int* gate = nullptr, int gate_value = 0, int gate_value_scaled = 0,
-                             const FusedKernels* every_candidate = nullptr) {
+                             const FusedAutoKernels* every_candidate = nullptr, RowSums sums = RowSums{}) {
   if (pl.tail_splits > 1 && partials == nullptr)
     return fail(h, ECGEMM_ERR_UNSUPPORTED, "ecgemm_sgemm: a sliced one-launch plan without room for its partial sums");
   FusedParams fp;
@@ -667,9 +672,10 @@ ecgemm_status_t launch_fused(ecgemm_handle_t h, const Plan& pl, ecgemm_op_t tran
   fp.out_scale = std::ldexp(1.0f, -(h->log2_scale_a + h->log2_scale_b));
   fp.C = C;
   const int64_t tiles = (int64_t)pl.tiles_m * pl.tiles_n;
-  void* args[] = {&fp};
-  const FusedKernels* kernels = every_candidate ? every_candidate : pl.shape->fused;
-  ECGEMM_HIP(h, hipLaunchKernel(reinterpret_cast<const void*>(kernels->kernel[layout_a][layout_b]),
+  void* args[] = {&fp, &sums};  // (the second for the kernels of every candidate only)
+  const void* kernel = every_candidate ? reinterpret_cast<const void*>(every_candidate->kernel[layout_a][layout_b])
+                                       : reinterpret_cast<const void*>(pl.shape->fused->kernel[layout_a][layout_b]);
+  ECGEMM_HIP(h, hipLaunchKernel(kernel,
                                 dim3((unsigned)(tiles * pl.tail_splits)), dim3((unsigned)pl.shape->threads), args, 0, h->stream));
   if (pl.tail_splits > 1) {  // the slices in ascending order, then alpha / beta (tiles in the order of the kernel above)
     const dim3 rgrid((unsigned)tiles, (unsigned)(pl.shape->bm * pl.shape->bn / 1024));
@@ -1323,7 +1329,19 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
   const Plan one_fp16 = make_plan(M, N, K, ECGEMM_MODE_FP16_SPLIT, h->shape, kOneLaunchSliced);
   const Plan one_bf16 = make_plan(M, N, K, ECGEMM_MODE_BF16_FULL, h->shape, kOneLaunchSliced);
   const bool fp16_one_launch = one_fp16.shape && one_fp16.shape->fused, bf16_one_launch = one_bf16.shape && one_bf16.shape->fused;
-  if (fp16_one_launch && bf16_one_launch && try_scaled && K <= kMeasureMaxDepth) {
+  const bool by_rows = fp16_one_launch && bf16_one_launch && try_scaled && K <= kMeasureMaxDepth;
+  // The two modes' plans differ in nothing but the kernel: one launch for every candidate (with a launch for either mode
+  // the calls took 4 to 10 % longer in every order of the operands).  Where its blocks fit the chip in one round, they also
+  // make the choice, each by itself.  Calls so / with a launch for the choice: 64^3 11.8 / 12.7 us, 512^3 15.4 / 16.6, 1024^3
+  // 22.8 / 24.0, 128 x 128 x 2048 20.7 / 21.7; in a second round the blocks would make it again.
+  const bool one_for_all = fp16_one_launch && bf16_one_launch && try_scaled && one_fp16.shape->bm == one_bf16.shape->bm &&
+                           one_fp16.tail_splits == one_bf16.tail_splits;
+  const bool chooses_itself = one_for_all && by_rows &&
+                              (int64_t)one_fp16.tiles_m * one_fp16.tiles_n * one_fp16.tail_splits <= kPlanComputeUnits;
+  RowSums sums{};
+  sums.if_fits = kChoiceFp16, sums.if_fits_scaled = kChoiceFp16Scaled, sums.if_not = kChoiceBf16;
+  sums.choice = choice;
+  if (by_rows) {
     // Nothing reads packed operands: both FP16 candidates are measured in one launch that writes none, the choice is
     // another (steps 1 to 3 in two launches instead of five).  The blocks' sums lie where the packed operands would.
     const int rows_per_block = measure_rows_per_block(M, N, K);
@@ -1343,9 +1361,14 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
     hipLaunchKernelGGL(measure, dim3(blocks_a + blocks_b), dim3(kMeasureThreads), 0, h->stream,
                        job_of(rows_a, h->log2_scale_a, sums_a), job_of(rows_b, h->log2_scale_b, sums_b), blocks_a, blocks_b);
     ECGEMM_HIP(h, hipGetLastError());
-    hipLaunchKernelGGL(choose_from_rows_kernel, dim3(1), dim3(256), 0, h->stream, sums_a, blocks_a, (double)M, sums_b, blocks_b,
-                       (double)N, kAutoTolerance, kAutoMinTerms, choice, (int)kChoiceFp16, (int)kChoiceFp16Scaled, (int)kChoiceBf16);
-    ECGEMM_HIP(h, hipGetLastError());
+    sums.a = sums_a, sums.b = sums_b;
+    sums.blocks_a = blocks_a, sums.blocks_b = blocks_b;
+    sums.rows_a = (double)M, sums.rows_b = (double)N;
+    sums.tolerance = kAutoTolerance, sums.min_terms = kAutoMinTerms;
+    if (!chooses_itself) {
+      hipLaunchKernelGGL(choose_from_rows_kernel, dim3(1), dim3(256), 0, h->stream, sums);
+      ECGEMM_HIP(h, hipGetLastError());
+    }
   } else {
     if (try_scaled) {
       // the first split also finds every row's largest exponent (on the operands as the caller passed them), so that
@@ -1380,22 +1403,17 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
       ECGEMM_HIP(h, hipGetLastError());
     }
   }
-  h->auto_choice = choice;  // (what writes it is enqueued by now)
+  if (!chooses_itself) h->auto_choice = choice;  // (what writes it is enqueued by now)
   if (!bf16_one_launch) {
     st = launch_split(h, ECGEMM_MODE_BF16_FULL, bf16_a, &bf16_b);
     if (st != ECGEMM_OK) return st;
   }
   if (timing) ECGEMM_HIP(h, hipEventRecord(tc.split_done, h->stream));
   const int log2_out_scale = -(h->log2_scale_a + h->log2_scale_b);
-  if (fp16_one_launch && bf16_one_launch && try_scaled && one_fp16.shape->bm == one_bf16.shape->bm &&
-      one_fp16.tail_splits == one_bf16.tail_splits) {
-    // the two modes' plans differ in nothing but the kernel: one launch that looks at the choice.  Calls so / with a
-    // launch for either mode, NN: 1024^3 26.4 / 28.1 us, 512^3 17.9 / 19.4, 1024 x 1024 x 128 16.8 / 18.4, 512 x 512 x
-    // 4096 (slices) 40.7 / 44.5, and 4 to 10 % in every other order, aligned or not: also where both bodies in one kernel
-    // spill (64 x 64, an unaligned operand with the depth contiguous beside one with the rows contiguous: 28 vector
-    // registers at worst; 1024^3, odd leading dimensions, NN 31.1 / 32.8, TT 31.4 / 33.2).
-    st = launch_fused(h, one_fp16, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, scales_a, scales_b, partials, choice,
-                      kChoiceFp16, kChoiceFp16Scaled, one_fp16.shape->bm == 64 ? &kFusedAutoTile64 : &kFusedAutoTile32);
+  if (one_for_all) {
+    st = launch_fused(h, one_fp16, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, scales_a, scales_b, partials, nullptr, 0, 0,
+                      &kFusedAuto[chooses_itself][one_fp16.shape->bm == 32], sums);
+    if (st == ECGEMM_OK) h->auto_choice = choice;  // (where the launch above writes it)
   } else {
     if (fp16_one_launch) {  // with and without the scaling vectors in one launch, which looks at the choice itself
       st = launch_fused(h, one_fp16, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, try_scaled ? scales_a : nullptr,

@@ -559,16 +559,18 @@ __global__ void __launch_bounds__(fused_threads(TILE), 1) fused_kernel(const Fus
   fused_block<METHOD, LAYOUT_A, LAYOUT_B, TILE>(p, lds);
 }
 
-// Automatic mode choice, where both modes' plans have the same tiles and slices: all three candidates in one launch,
-// the word at p.gate (always one of the three values) says which this is.  What it saves is a launch that would
-// return at once, and a second one for the reduction of plans in slices.
-template <int LAYOUT_A, int LAYOUT_B, int TILE>
-__global__ void __launch_bounds__(fused_threads(TILE), 1) fused_auto_kernel(const FusedParams params) {
+// Automatic mode choice, where both modes' plans have the same tiles and slices: all three candidates in one launch.
+// CHOOSES: every block makes the choice from the rows' sums by itself (about 2 us, where a launch for it takes 3.5 us) and the
+// first one writes it down; else it is at sums.choice.
+template <bool CHOOSES, int LAYOUT_A, int LAYOUT_B, int TILE>
+__global__ void __launch_bounds__(fused_threads(TILE), 1) fused_auto_kernel(const FusedParams params, const RowSums sums) {
   FusedParams p = params;
-  const int choice = *p.gate;
-  if (choice != p.gate_value_scaled) p.row_log2_scale = p.col_log2_scale = nullptr;
+  int choice;
+  if constexpr (CHOOSES) choice = choose_from_rows(sums, blockIdx.x == 0);
+  else choice = *sums.choice;
+  if (choice != sums.if_fits_scaled) p.row_log2_scale = p.col_log2_scale = nullptr;
   __shared__ __attribute__((aligned(1024))) char lds[fused_lds_bytes(kMethodBf16Full, TILE)];
-  if (choice == p.gate_value || choice == p.gate_value_scaled)
+  if (choice != sums.if_not)
     fused_block<kMethodFp16Split, LAYOUT_A, LAYOUT_B, TILE>(p, lds);
   else
     fused_block<kMethodBf16Full, LAYOUT_A, LAYOUT_B, TILE>(p, lds);

@@ -166,16 +166,6 @@ __global__ void __launch_bounds__(256, 1) mfma_rate_kernel(const unsigned short*
   sink[(int64_t)blockIdx.x * 256 + threadIdx.x] = s;
 }
 
-// The criterion of the automatic mode choice (see choose_mode_kernel) on the sums (err2, norm2, abs1) of A and of B.
-__device__ __forceinline__ bool choice_fits(const double* a, double rows_a, const double* b, double rows_b, double tolerance2,
-                                            double min_terms) {
-  const bool represented = a[0] <= tolerance2 * a[1] && b[0] <= tolerance2 * b[1];
-  // (sum |x|)^2 >= min_terms rows sum x^2, for either operand; an all-zero operand has nothing to lose
-  const bool spread = a[2] * a[2] >= min_terms * rows_a * a[1] || b[2] * b[2] >= min_terms * rows_b * b[1] ||
-                      a[1] == 0.0 || b[1] == 0.0;
-  return represented && spread;
-}
-
 // Automatic mode choice: from the blocks' statistics of both operands, *choice = if_fits or if_not.  It fits if
 //   * the FP16 pair represents both operands as they were split to within `tolerance`, relative, in the Frobenius
 //     norm, and
@@ -250,7 +240,6 @@ __global__ void __launch_bounds__(1024) choose_mode_kernel(const double* __restr
 // whole calls: 1024^3 25.2 us against 34.1 with clearing, two measuring splits and two choices, five launches, before
 // the products; 16384 x 64 x 64 17.2 against 32.
 constexpr int kMeasureThreads = 512;
-constexpr int kMeasureSums = 6;  // per block: err2, norm2, abs1 as they are (see SplitStats), then with the rows scaled
 struct MeasureJob {
   const float* src;             // X(r, k) = src[r * row_stride + k * k_stride]
   int64_t row_stride, k_stride;  // one of them is 1
@@ -370,38 +359,7 @@ __global__ void __launch_bounds__(kMeasureThreads) measure_rows_kernel(const Mea
   }
 }
 
-// The choice from what measure_rows_kernel left, by the criteria of choose_mode_kernel for either candidate: *choice =
-// if_fits, else if_fits_scaled, else if_not.  One block; every sum in a fixed order.
-__global__ void __launch_bounds__(256) choose_from_rows_kernel(const double* __restrict__ sums_a, unsigned blocks_a, double rows_a,
-                                                               const double* __restrict__ sums_b, unsigned blocks_b, double rows_b,
-                                                               double tolerance, double min_terms, int* __restrict__ choice,
-                                                               int if_fits, int if_fits_scaled, int if_not) {
-  __shared__ double partial[4][kMeasureSums];
-  const int t = threadIdx.x, wave = t >> 6;
-  const bool second = t >= 128;  // two waves per operand
-  const double* from = second ? sums_b : sums_a;
-  const unsigned blocks = second ? blocks_b : blocks_a;
-  double sums[kMeasureSums] = {};
-#pragma unroll 2
-  for (unsigned i = t & 127; i < blocks; i += 128)
-#pragma unroll
-    for (int q = 0; q < kMeasureSums; ++q) sums[q] += from[kMeasureSums * (size_t)i + q];
-#pragma unroll
-  for (int q = 0; q < kMeasureSums; ++q) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) sums[q] += __shfl_xor(sums[q], d, 64);
-    if ((t & 63) == 0) partial[wave][q] = sums[q];
-  }
-  __syncthreads();
-  if (t != 0) return;
-  const double t2 = tolerance * tolerance;
-  auto fits = [&](int at) {
-    double a[kStatsPerBlock], b[kStatsPerBlock];
-#pragma unroll
-    for (int q = 0; q < kStatsPerBlock; ++q) a[q] = partial[0][at + q] + partial[1][at + q], b[q] = partial[2][at + q] + partial[3][at + q];
-    return choice_fits(a, rows_a, b, rows_b, t2, min_terms);
-  };
-  *choice = fits(0) ? if_fits : fits(kStatsPerBlock) ? if_fits_scaled : if_not;
-}
+// The choice from what measure_rows_kernel left, in a launch of its own (for calls whose candidates are not one kernel).
+__global__ void __launch_bounds__(256) choose_from_rows_kernel(const RowSums sums) { choose_from_rows(sums, true); }
 
 }  // namespace ecgemm

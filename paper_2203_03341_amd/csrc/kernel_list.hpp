@@ -107,13 +107,17 @@ ECGEMM_COMPARE_B_GROUP template __global__ void product_kernel<Fp32Config, false
   ECGEMM_FUSED_KERNELS_OF(METHOD, kFusedDepth, 32)
 ECGEMM_FUSED_KERNELS_OF_METHOD(kMethodFp16Split)
 ECGEMM_FUSED_KERNELS_OF_METHOD(kMethodBf16Full)
-#define ECGEMM_FUSED_AUTO_KERNELS_OF(LAYOUT_A, TILE)                                                                    \
-  ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<LAYOUT_A, kFusedRows, TILE>(const FusedParams);   \
-  ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<LAYOUT_A, kFusedDepth, TILE>(const FusedParams);
-ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedRows, 64)
-ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepth, 64)
-ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedRows, 32)
-ECGEMM_FUSED_AUTO_KERNELS_OF(kFusedDepth, 32)
+#define ECGEMM_FUSED_AUTO_KERNELS_OF(CHOOSES, LAYOUT_A, TILE)                                                                    \
+  ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<CHOOSES, LAYOUT_A, kFusedRows, TILE>(const FusedParams, const RowSums);   \
+  ECGEMM_FUSED_AUTO_GROUP template __global__ void fused_auto_kernel<CHOOSES, LAYOUT_A, kFusedDepth, TILE>(const FusedParams, const RowSums);
+ECGEMM_FUSED_AUTO_KERNELS_OF(false, kFusedRows, 64)
+ECGEMM_FUSED_AUTO_KERNELS_OF(true, kFusedRows, 64)
+ECGEMM_FUSED_AUTO_KERNELS_OF(false, kFusedDepth, 64)
+ECGEMM_FUSED_AUTO_KERNELS_OF(true, kFusedDepth, 64)
+ECGEMM_FUSED_AUTO_KERNELS_OF(false, kFusedRows, 32)
+ECGEMM_FUSED_AUTO_KERNELS_OF(true, kFusedRows, 32)
+ECGEMM_FUSED_AUTO_KERNELS_OF(false, kFusedDepth, 32)
+ECGEMM_FUSED_AUTO_KERNELS_OF(true, kFusedDepth, 32)
 
 ECGEMM_WIDE_GROUP template __global__ void wide_kernel<kMethodFp16Split, false, false>(const WideParams);
 ECGEMM_WIDE_GROUP template __global__ void wide_kernel<kMethodFp16Split, false, true>(const WideParams);

@@ -148,6 +148,61 @@ struct SplitStats {
 };
 constexpr int kStatsPerBlock = 3;  // doubles a block leaves: err2, norm2, abs1
 
+// The criterion of the automatic mode choice (see choose_mode_kernel) on the sums (err2, norm2, abs1) of A and of B.
+__device__ __forceinline__ bool choice_fits(const double* a, double rows_a, const double* b, double rows_b, double tolerance2,
+                                            double min_terms) {
+  const bool represented = a[0] <= tolerance2 * a[1] && b[0] <= tolerance2 * b[1];
+  // (sum |x|)^2 >= min_terms rows sum x^2, for either operand; an all-zero operand has nothing to lose
+  const bool spread = a[2] * a[2] >= min_terms * rows_a * a[1] || b[2] * b[2] >= min_terms * rows_b * b[1] ||
+                      a[1] == 0.0 || b[1] == 0.0;
+  return represented && spread;
+}
+
+// What measure_rows_kernel leaves: per block kMeasureSums sums, err2, norm2, abs1 as they are (see SplitStats), then with
+// the rows scaled; and what is made of them.
+constexpr int kMeasureSums = 6;
+struct RowSums {
+  const double* a;
+  const double* b;
+  unsigned blocks_a, blocks_b;
+  double rows_a, rows_b, tolerance, min_terms;
+  int if_fits, if_fits_scaled, if_not;
+  int* choice;
+};
+// The choice by the criterion above for either candidate: if_fits, else if_fits_scaled, else if_not.  Called by every
+// thread of a block of at least 256; every sum in a fixed order, so that every block comes to the same choice.
+__device__ __forceinline__ int choose_from_rows(const RowSums& sums, bool publish) {
+  __shared__ double partial[4][kMeasureSums];
+  const int t = threadIdx.x, wave = t >> 6;
+  if (t < 256) {
+    const bool second = t >= 128;  // two waves per operand
+    const double* from = second ? sums.b : sums.a;
+    const unsigned blocks = second ? sums.blocks_b : sums.blocks_a;
+    double sum[kMeasureSums] = {};
+#pragma unroll 2
+    for (unsigned i = t & 127; i < blocks; i += 128)
+#pragma unroll
+      for (int q = 0; q < kMeasureSums; ++q) sum[q] += from[kMeasureSums * (size_t)i + q];
+#pragma unroll
+    for (int q = 0; q < kMeasureSums; ++q) {
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) sum[q] += __shfl_xor(sum[q], d, 64);
+      if ((t & 63) == 0) partial[wave][q] = sum[q];
+    }
+  }
+  __syncthreads();
+  const double t2 = sums.tolerance * sums.tolerance;
+  auto fits = [&](int at) {
+    double a[kStatsPerBlock], b[kStatsPerBlock];
+#pragma unroll
+    for (int q = 0; q < kStatsPerBlock; ++q) a[q] = partial[0][at + q] + partial[1][at + q], b[q] = partial[2][at + q] + partial[3][at + q];
+    return choice_fits(a, sums.rows_a, b, sums.rows_b, t2, sums.min_terms);
+  };
+  const int choice = fits(0) ? sums.if_fits : fits(kStatsPerBlock) ? sums.if_fits_scaled : sums.if_not;
+  if (publish && t == 0) *sums.choice = choice;
+  return __builtin_amdgcn_readfirstlane(choice);
+}
+
 // Binary exponent of a non-zero finite value, FP32 subnormals counted as -127; INT_MIN for zero, infinities and NaN
 // (the elements that the per-row scaling exponents ignore).
 __device__ __forceinline__ int finite_exponent(float v) {
