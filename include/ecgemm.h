@@ -102,7 +102,9 @@ ecgemm_status_t ecgemm_set_stream(ecgemm_handle_t handle, void *hip_stream);
 /* Bytes of device workspace ecgemm_sgemm needs for this problem: the split operands in matrix-unit fragment order,
  * zero-padded to whole tiles, plus at most 128 MiB of partial sums for output tiles that are cut into slices along K.
  * (Small products run as one launch that needs no packed operands, and partial sums only where deep products of few
- * tiles are cut into slices along K; the size returned for them is the larger of that and what ecgemm_product needs.)
+ * tiles are cut into slices along K; the size returned for them is the larger of that and what ecgemm_product needs.
+ * FP16 products of a few hundred tiles may be computed in one pass as well, with the bits of their plan: the size
+ * returned for them is the plan's all the same.)
  * The plan behind it is made for the 256 compute units of the MI355X, so the size depends on the problem, the mode and
  * the kernel shape only; `handle` supplies the shape forced with ecgemm_set_shape (ecgemm_debug.h) and may be NULL
  * (automatic choice).  transA and transB are checked and otherwise do not matter: the split pass absorbs the
@@ -222,7 +224,7 @@ ecgemm_status_t ecgemm_sgemm_noalloc(ecgemm_handle_t handle, ecgemm_op_t transA,
  * size asks for ECGEMM_MODE_BF16_FULL.  Cost over calling the chosen arrangement directly: the statistics in the split
  * (it stays bound by memory traffic), seven to a dozen kernel launches, most of which do nothing, and for the later candidates the
  * splits that are thrown away; small products (both modes' plans one launch, K up to 4096) are measured without being
- * split, in two launches more than the fixed mode's.  Workspace: that of the BF16 mode plus 24 bytes per 64 x 32 block of each operand, 4 (M + N)
+ * split, in one launch more than the fixed mode's, or two.  Workspace: that of the BF16 mode plus 24 bytes per 64 x 32 block of each operand, 4 (M + N)
  * bytes and 256 (ecgemm_workspace_size with ECGEMM_MODE_AUTO).  Not available with caller-given scaling vectors,
  * ecgemm_split / ecgemm_product, ecgemm_plan_info or a forced one-launch kernel shape (ECGEMM_ERR_UNSUPPORTED or
  * ECGEMM_ERR_INVALID_ARG for the mode).
@@ -326,7 +328,8 @@ ecgemm_status_t ecgemm_product(ecgemm_handle_t handle, int64_t M, int64_t N, int
 ecgemm_status_t ecgemm_split_size(int64_t rows, int64_t depth, ecgemm_mode_t mode, size_t *bytes);
 
 /* When enabled, every ecgemm_sgemm brackets its split kernels and its product kernel with HIP events on
- * the handle's stream so that their device durations can be read back; off by default. */
+ * the handle's stream so that their device durations can be read back; off by default.  (A call in one pass over the
+ * FP32 operands has no split kernels: all of its time is the product kernel's.) */
 ecgemm_status_t ecgemm_set_timing(ecgemm_handle_t handle, int enabled);
 
 /* Synchronises with the events of the calls made since timing was enabled (or since the last call of

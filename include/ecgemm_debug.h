@@ -48,7 +48,9 @@ extern "C" {
 /*
  * Kernel shape of the product (steps 2 and 3 of ecgemm_sgemm); a tuning and test knob.  The paper's counterpart are the
  * block and warp tile sizes that it picks for each matrix size by grid search (section "Parameter tuning of CUTLASS").
- * ECGEMM_SHAPE_AUTO (the default) picks per call from the mode and the problem size.  The others force one shape for
+ * ECGEMM_SHAPE_AUTO (the default) picks per call from the mode and the problem size, and may carry a split-first plan out
+ * in one pass over the FP32 operands (blocks of 128 x 128 that split for themselves, the plan's bits; FP16 mode, where
+ * that is faster: ecgemm_plan_info reports the plan either way).  The others force one shape for
  * every later ecgemm_sgemm / ecgemm_product / ecgemm_workspace_size on the handle:
  *   256x128_W4     block tile 256 x 128, 4 waves of 128 x 64, one block per compute unit (every mode);
  *   128x128_X2     block tile 128 x 128, 4 waves of 64 x 64, two blocks per compute unit (the two modes of the method);
