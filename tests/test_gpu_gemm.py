@@ -1144,7 +1144,9 @@ def test_sizes_beyond_the_supported_depth_are_refused():
     (257, 7070, 190, (0, 2, 0)),           # a last row of tiles with one row of its own; 3 chunks
     (1500, 2000, 64, (4, 4, 4)),           # one chunk
     (1024, 1030, 16389, (0, 3, 0)),        # every tile in slices, the last of them ragged
-    (640, 1664, 2752, (1, 0, 0))])
+    (640, 1664, 2752, (1, 0, 0)),
+    (2176, 2433, 225, (0, 1, 0)),          # more blocks than units: two rounds of whole tiles
+    (1800, 3000, 512, (4, 0, 2))])
 def test_one_pass_over_the_operands_gives_the_bits_of_the_plan(transA, transB, M, N, K, pads):
     """A split-first FP16 plan that the kernel of 128 x 128 one-launch blocks carries out: the same bits as the plan's own
     kernel shape when the caller fixes that, with alpha and beta and without, NaN behind every line, and with values that
