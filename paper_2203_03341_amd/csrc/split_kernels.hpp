@@ -371,6 +371,16 @@ __device__ __forceinline__ void split_tiles_k_contiguous(const SplitJob& job, un
   const int t = threadIdx.x;
   const int64_t r = (int64_t)(block / job.fast_tiles) * 64 + (t >> 2);
   const int64_t k0 = (int64_t)(block % job.fast_tiles) * (32 * TILES) + (t & 3) * 8;
+  // A block of nothing but padding (the same for all its threads) has nothing to load: 64 x 31936 FP16 9.1 us / 8.0 with the
+  // clamped loads below / so.  (It returns: a path without loads that joined the others would make every block wait for
+  // all of its loads at the join, 2048 x 4096 FP16 12.4 us / 12.8.)
+  if (r - (t >> 2) >= job.rows) {
+    const float zeros[8] = {};
+#pragma unroll
+    for (int s = 0; s < TILES; ++s)
+      if (k0 + 32 * s < job.k_steps_total * 16) store_fragment_row<KIND>(job.packed, job.k_steps_total, r, k0 + 32 * s, zeros);
+    return;
+  }
   float prescale = job.prescale;
   if (job.row_log2_scale != nullptr && r < job.rows) prescale *= row_scale_factor(job.row_log2_scale[r]);
   const float* src = job.src;
