@@ -362,10 +362,11 @@ __device__ __forceinline__ source4_t load_source4_or_zero(const float* line, int
 
 // Source with k contiguous, X(r, k) = src[k + r * ld].  One block: 64 rows x 32 k, 256 threads, thread t handles row
 // t / 4 and the 8 values starting at k = 8 * (t % 4), two 16-byte loads; or TILES such tiles next to each other in k, whose
-// loads are all requested before the first is split (kernels of their own: one tile takes 20 to 33 registers, four 44 to
-// 64).  Blocks are numbered with k fastest.  The memory path takes 16 bytes at any multiple of four, so rows that start on
-// no alignment (lda = 5003) are read like the others: 4095 x 5003 FP16 31.1 us / 25.3 and BF16 36.4 / 32.1 with lanes along
-// k, one value each, handed to the row's thread through LDS / so; 9001 x 9001 161 / 118 and 195 / 149.
+// loads are all requested before the first is split (kernels of their own: one tile takes 24 to 34 registers, four 58 to
+// 61, which leaves eight waves on a SIMD).  Blocks are numbered with k fastest.  The memory path takes 16 bytes at any
+// multiple of four, so rows that start on no alignment (lda = 5003) are read like the others: 4095 x 5003 FP16 31.1 us /
+// 25.3 and BF16 36.4 / 32.1 with lanes along k, one value each, handed to the row's thread through LDS / so; 9001 x 9001
+// 161 / 118 and 195 / 149.
 template <int KIND, int TILES, bool STATS>
 __device__ __forceinline__ void split_tiles_k_contiguous(const SplitJob& job, unsigned block, SplitStats* stats) {
   const int t = threadIdx.x;
@@ -398,13 +399,20 @@ __device__ __forceinline__ void split_tiles_k_contiguous(const SplitJob& job, un
   } else if (job.depth >= 4) {
     const float* line = src + (r < job.rows ? r : job.rows - 1) * job.ld;
     const int64_t count = job.depth;
-    source4_t x[2 * TILES];
+    // (two tiles at a time: the clamped loads of four would take 70 registers and a wave of every SIMD, 2048 x 4096 FP16
+    // 12.0 us / 11.7 so, BF16 level)
+    constexpr int GROUP = TILES > 1 ? TILES / 2 : 1;
 #pragma unroll
-    for (int s = 0; s < 2 * TILES; ++s) x[s] = load_source4_or_zero<false>(line, k0 + 32 * (s / 2) + 4 * (s % 2), count);
+    for (int g = 0; g < TILES; g += GROUP) {
+      source4_t x[2 * GROUP];
 #pragma unroll
-    for (int s = 0; s < 2 * TILES; ++s)
+      for (int s = 0; s < 2 * GROUP; ++s) x[s] = load_source4_or_zero<false>(line, k0 + 32 * (g + s / 2) + 4 * (s % 2), count);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[s / 2][4 * (s % 2) + e] = r < job.rows ? x[s][e] : 0.0f;
+      for (int s = 0; s < 2 * GROUP; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[g + s / 2][4 * (s % 2) + e] = r < job.rows ? x[s][e] : 0.0f;
+      if (TILES > 1) __builtin_amdgcn_sched_barrier(0);
+    }
   } else {
 #pragma unroll
     for (int s = 0; s < TILES; ++s) {
