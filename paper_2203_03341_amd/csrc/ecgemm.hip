@@ -454,11 +454,22 @@ constexpr int64_t kSplitStreamedElems = 1ll << 26;
 // with ld 65540 101 / 124.  Whole lines keep the plain order (runs cost them up to 7 %).
 constexpr int64_t kSplitCachedBytes = 256ll << 20;
 
+// Rows contiguous, lines that start anywhere: 64 rows a block (kSplitRContiguous), or 256 (kSplitRContiguousWide) where
+// the operand comes from the caches (from memory, FP16 64 / 256 rows: 9001^2 121 / 126 us, 12001^2 217 / 223; from the
+// caches 4095 x 5003 30.3 / 24.9, 300 x 100000 73 / 63) and there is enough to split, in tiles of 64 rows x 32 k that hold
+// any of it, that a quarter as many blocks fill the chip.  Alone, 64 / 256 rows: FP16 832 x 2726 (1118 tiles) 4.7 / 5.1, 2238 x
+// 1062 (1190) 4.5 / 4.8, 450 x 7391 (1848) 6.1 / 5.7, BF16 5401 x 212 (595) 4.0 / 4.5, 786 x 3099 (1261) 6.8 / 6.1, 2888 x 944
+// (1380) 6.4 / 6.0.  Both operands of a product, whose blocks of either kind meet, split part of BF16 calls with the rows
+// of both contiguous: 2329 x 413 x 140 (220 tiles together) 7.1 / 8.4, 1344 x 10597 x 66 (561) 10.5 / 12.4, 7159 x 9457 x 155
+// (1300) 13.2 / 14.6, 4297 x 5480 x 339 (1694) 13.0 / 13.4, 3081 x 3162 x 552 (1782) 13.9 / 14.4, 4118 x 5786 x 366 (1872)
+// 13.7 / 13.3, 1190 x 939 x 1753 (1870) 12.4 / 10.6, 5768 x 1241 x 567 (1998) 15.1 / 12.4.
+constexpr int64_t kSplitWideFrom = 1200, kSplitWideFromPair = 1800;
+
 // X = op(src) is rows x depth.  op == N: X(r, k) = src[r + k * ld]; op == T: X(r, k) = src[k + r * ld].
-// `alone`: no other operand is split in the same launch.
+// `rows_beside`: of the other operand of the product, which is as deep and is split next to this one; 0 if there is none.
 ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, int64_t depth, const float* src, int64_t ld,
                                ecgemm_mode_t mode, void* packed, int log2_prescale, const int* row_log2_scale, SplitJob* job,
-                               bool alone = false) {
+                               int64_t rows_beside) {
   const int64_t Rp = round_up(rows, kRowPad), Kp = round_up(depth, kDepthPad);
   const int64_t blocks64 = (Kp / 32) * (Rp / 64);
   if (blocks64 > 0x7fffffff) return fail(h, ECGEMM_ERR_INVALID_ARG, "operand has more than 2^42 elements");
@@ -479,11 +490,8 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
   job->row_max = nullptr;
   job->streamed = rows * depth >= kSplitStreamedElems && (split_is_bf16(split_kind_of((int)mode)) ? whole_lines : aligned);  // (kSplitRContiguousWide)
   job->runs = !whole_lines && cached;
-  // Rows contiguous: 256 rows a block, or 64 where the lines start anywhere and the operand comes from memory (FP16 64 / 256
-  // rows: 9001^2 121 / 126 us, 12001^2 217 / 223; from the caches 4095 x 5003 30.3 / 24.9, 300 x 100000 73 / 63), or where it
-  // makes so few blocks that the launch is all there is to see, and it is split alone (1001 x 2003 4.1 / 4.5; next to
-  // another operand the wide blocks are ahead there too, 1500^3 NT 36.2 / 35.4 a call).
-  const bool wide = aligned || (cached && !(alone && blocks64 / 4 < 2 * kPlanComputeUnits));
+  const int64_t tiles_alone = (Kp / 32) * ((rows + 63) / 64), tiles_together = tiles_alone + (Kp / 32) * ((rows_beside + 63) / 64);
+  const bool wide = aligned || (cached && tiles_together >= (rows_beside > 0 ? kSplitWideFromPair : kSplitWideFrom));
   job->variant = k_contiguous ? kSplitKContiguous : wide ? kSplitRContiguousWide : kSplitRContiguous;
   // blocks are 64 rows x 32 k, or 256 x 32 (wide), or four tiles along k
   switch (job->variant) {
@@ -1060,7 +1068,7 @@ ecgemm_status_t ecgemm_split(ecgemm_handle_t handle, ecgemm_op_t op, int64_t row
   if (ld < (op == ECGEMM_OP_N ? rows : depth)) return bad_arg(handle, 6, "ecgemm_split: leading dimension too small");
   if (!packed || ((uintptr_t)packed % 16) != 0) return bad_arg(handle, 8, "ecgemm_split: null or misaligned output");
   SplitJob job;
-  const ecgemm_status_t st = make_split_job(handle, op, rows, depth, src, ld, mode, packed, 0, nullptr, &job, true);
+  const ecgemm_status_t st = make_split_job(handle, op, rows, depth, src, ld, mode, packed, 0, nullptr, &job, 0);
   if (st != ECGEMM_OK) return st;
   return launch_split(handle, mode, job);
 }
@@ -1297,13 +1305,13 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
   rows_a.scale = scales_a;
   rows_b.scale = scales_b;
   SplitJob fp16_a, fp16_b, scaled_a, scaled_b, bf16_a, bf16_b;
-  st = make_split_job(h, transA, M, K, A, lda, ECGEMM_MODE_FP16_SPLIT, ws, h->log2_scale_a, nullptr, &fp16_a);
+  st = make_split_job(h, transA, M, K, A, lda, ECGEMM_MODE_FP16_SPLIT, ws, h->log2_scale_a, nullptr, &fp16_a, N);
   if (st != ECGEMM_OK) return st;
-  st = make_split_job(h, op_b, N, K, B, ldb, ECGEMM_MODE_FP16_SPLIT, ws + ap.fp16.a_bytes, h->log2_scale_b, nullptr, &fp16_b);
+  st = make_split_job(h, op_b, N, K, B, ldb, ECGEMM_MODE_FP16_SPLIT, ws + ap.fp16.a_bytes, h->log2_scale_b, nullptr, &fp16_b, M);
   if (st != ECGEMM_OK) return st;
-  st = make_split_job(h, transA, M, K, A, lda, ECGEMM_MODE_BF16_FULL, ws, h->log2_scale_a, nullptr, &bf16_a);
+  st = make_split_job(h, transA, M, K, A, lda, ECGEMM_MODE_BF16_FULL, ws, h->log2_scale_a, nullptr, &bf16_a, N);
   if (st != ECGEMM_OK) return st;
-  st = make_split_job(h, op_b, N, K, B, ldb, ECGEMM_MODE_BF16_FULL, ws + ap.bf16.a_bytes, h->log2_scale_b, nullptr, &bf16_b);
+  st = make_split_job(h, op_b, N, K, B, ldb, ECGEMM_MODE_BF16_FULL, ws + ap.bf16.a_bytes, h->log2_scale_b, nullptr, &bf16_b, M);
   if (st != ECGEMM_OK) return st;
   if (kStatsPerBlock * sizeof(double) * fp16_a.blocks > ap.stats_a_bytes ||
       kStatsPerBlock * sizeof(double) * fp16_b.blocks > ap.stats_b_bytes)
@@ -1501,10 +1509,10 @@ ecgemm_status_t sgemm_common(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t 
   if (!pl.shape->fused && !wide.use) {
     // step 1: op(A) is M x K with rows m; op(B)^T is N x K with rows n.  For B the roles of N and T swap:
     // B stored K x N (transB == N) has k contiguous, i.e. it is the "T" case of the splitter.
-    st = make_split_job(h, transA, M, K, A, lda, mode, a_packed, h->log2_scale_a, row_log2_scale_a, &job_a);
+    st = make_split_job(h, transA, M, K, A, lda, mode, a_packed, h->log2_scale_a, row_log2_scale_a, &job_a, N);
     if (st != ECGEMM_OK) return st;
     st = make_split_job(h, transB == ECGEMM_OP_N ? ECGEMM_OP_T : ECGEMM_OP_N, N, K, B, ldb, mode, b_packed, h->log2_scale_b,
-                        col_log2_scale_b, &job_b);
+                        col_log2_scale_b, &job_b, M);
     if (st != ECGEMM_OK) return st;
   }
 

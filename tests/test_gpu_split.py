@@ -278,3 +278,40 @@ def test_a_leading_dimension_off_the_cache_lines_is_not_fetched_twice():
     whole, shared = best_us(9024), best_us(9000)
     assert shared < 1.2 * whole, (whole, shared)
     h.destroy()
+
+
+@pytest.mark.parametrize("mode_bf16", [False, True])
+@pytest.mark.parametrize("transA,transB,M,N,K,pad", [("N", "T", 1030, 1101, 900, 1),     # rows contiguous, few tiles together: 64 rows a block
+                                                     ("N", "T", 2050, 1999, 900, 1),     # many: 256
+                                                     ("N", "T", 1028, 333, 201, 0),      # on 16 bytes beside lines that are not
+                                                     ("T", "T", 131, 1027, 333, 2),      # beside the depth contiguous
+                                                     ("N", "N", 2059, 2111, 1500, 3)])   # four tiles a block beside 256 rows
+def test_two_operands_split_together_are_what_each_is_alone(transA, transB, M, N, K, pad, mode_bf16):
+    """The operands of a product are split in one launch, in blocks that depend on both: the product has the bits of one
+    made from operands that were split one by one, in other blocks.  NaN behind every line."""
+    import torch
+    import paper_2203_03341_amd as ec
+    mode = ec.MODE_BF16_FULL if mode_bf16 else ec.MODE_FP16_SPLIT
+    ops = {"N": ec.OP_N, "T": ec.OP_T}
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+
+    def operand(cols, rows):
+        store = torch.full((cols, rows + pad), float("nan"), device="cuda")
+        store[:, :rows] = torch.randn((cols, rows), generator=gen, device="cuda")
+        return store
+
+    A = operand(*((K, M) if transA == "N" else (M, K)))
+    B = operand(*((N, K) if transB == "N" else (K, N)))
+    h = ec.Handle()
+    h.set_stream(torch.cuda.current_stream().cuda_stream)
+    h.set_shape(ec.SHAPE_128x128_X2)
+    together, alone = torch.zeros((N, M), device="cuda"), torch.zeros((N, M), device="cuda")
+    h.sgemm(ops[transA], ops[transB], M, N, K, 1.0, A, A.shape[1], B, B.shape[1], 0.0, together, M, mode)
+    packed = [torch.empty(ec.split_size(rows, K, mode), dtype=torch.uint8, device="cuda") for rows in (M, N)]
+    h.split(ops[transA], M, K, A, A.shape[1], mode, packed[0])
+    h.split(ec.OP_T if transB == "N" else ec.OP_N, N, K, B, B.shape[1], mode, packed[1])
+    h.product(M, N, K, 1.0, packed[0], packed[1], 0.0, alone, M, mode)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(alone).all()) and torch.equal(together, alone)
+    h.destroy()
