@@ -155,8 +155,7 @@ struct FusedOperand {
 
   // Requests the values of chunk c (which exists).  Every address is valid, given that the operand is at least four deep
   // (kFusedDepth; the slice of it that the block takes need not be): in the last chunk, k beyond the depth is clamped
-  // (complete() does the rest).  No load sits under a condition and both branches issue the same number of loads, so the
-  // number in flight is the same on every path: the waits that the compiler places count them.
+  // (complete() does the rest).  No load sits under a condition of its own and both branches issue the same number of loads.
   __device__ __forceinline__ void fetch(float (&x)[V], int c) const {
     const int64_t chunk_k = (int64_t)c * 64;
     if (chunk_k + 64 <= K) {  // block-uniform
@@ -376,15 +375,6 @@ __device__ __forceinline__ void fused_block(FusedParams p, char* lds) {
     }
     static_assert(kFusedRing % 2 == 0, "a ring slot always meets the same LDS buffer");
     float xa[kFusedRing][V], xb[kFusedRing][V];
-    // (a chunk beyond the last is requested again as the last one and never used: in the loop every fetch is
-    // unconditional; the scheduling barriers keep the requests of one ring slot together and the slots in order, which
-    // is what lets the wait in front of a slot's first use leave the younger slots' loads in flight)
-    const int last = chunks - 1;
-    static_for<kFusedRing>([&](auto r_c) {
-      constexpr int r = decltype(r_c)::value;
-      a.fetch(xa[r], r < last ? r : last), b.fetch(xb[r], r < last ? r : last);
-      __builtin_amdgcn_sched_barrier(0);
-    });
     int c0 = 0;
     // The bulk of the depth: chunks that lie inside it and whose successors in the ring do too, so that nothing in
     // the loop depends on where the depth ends, and what is the same for the whole block (are there scaling factors?)
@@ -394,15 +384,33 @@ __device__ __forceinline__ void fused_block(FusedParams p, char* lds) {
       const int whole_chunks = (int)(p.K / 64);
       // (leading dimensions beyond 2^23 take the loop further down throughout)
       const int bulk_chunks = p.lda <= OperandA::kLargestShortLd && p.ldb <= OperandB::kLargestShortLd ? whole_chunks : 0;
-      for (; c0 + 2 * kFusedRing <= bulk_chunks; c0 += kFusedRing) {
+      // The first chunks are requested by the loads of the loop, into the registers of the loop (scheduling barriers keep the
+      // requests of one slot together and the slots in order).  With the general fetch in front of the loop, whichever
+      // branches it has, the compiler no longer knows which loads are in flight at the top, and makes every round of the loop
+      // wait for chunks that it has only just requested: FP16 192 x 1920 x 62912 NN 353 us / 307, TN 335 / 304, 6080 x 64 x
+      // 18752 NN 122 / 109; 256^3 NT 6.4 / 6.0, 1024 x 1024 x 192 7.2 / 6.8, BF16 7.5 / 7.1.
+      if (bulk_chunks >= kFusedRing) {
         static_for<kFusedRing>([&](auto r_c) {
           constexpr int r = decltype(r_c)::value;
-          char* stage = lds + (r & 1) * STAGE_BYTES;
-          a.template deposit_whole<GENERAL>(xa[r], stage);
-          b.template deposit_whole<GENERAL>(xb[r], stage + REGION_BYTES);
+          a.fetch_whole(xa[r], r), b.fetch_whole(xb[r], r);
           __builtin_amdgcn_sched_barrier(0);
-          a.fetch_whole(xa[r], c0 + r + kFusedRing), b.fetch_whole(xb[r], c0 + r + kFusedRing);
-          __syncthreads();
+        });
+        for (; c0 + 2 * kFusedRing <= bulk_chunks; c0 += kFusedRing) {
+          static_for<kFusedRing>([&](auto r_c) {
+            constexpr int r = decltype(r_c)::value;
+            char* stage = lds + (r & 1) * STAGE_BYTES;
+            a.template deposit_whole<GENERAL>(xa[r], stage);
+            b.template deposit_whole<GENERAL>(xb[r], stage + REGION_BYTES);
+            __builtin_amdgcn_sched_barrier(0);
+            a.fetch_whole(xa[r], c0 + r + kFusedRing), b.fetch_whole(xb[r], c0 + r + kFusedRing);
+            __syncthreads();
+          });
+        }
+      } else {
+        static_for<kFusedRing>([&](auto r_c) {
+          constexpr int r = decltype(r_c)::value;
+          if (r < chunks) a.fetch(xa[r], r), b.fetch(xb[r], r);
+          __builtin_amdgcn_sched_barrier(0);
         });
       }
       // The last chunks, whose successors in the ring do not exist or are not whole: the same split for those that
