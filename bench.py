@@ -259,9 +259,8 @@ class Workload:
         one_launch = (not self.auto) and self.h.plan_info(M, N, K, self.plan_mode_id)["shape"] >= 3
         kernel = "fused_kernel" if one_launch else "product_kernel"
         traffic = MEASURED_TRAFFIC_BYTES.get(self.name)
-        if not one_launch and split_ms * 1e-3 * PEAK_HBM_GBS * 1e9 < split_bytes:
-            # nothing was split in that time: the plan was carried out by the kernel that splits for itself
-            one_launch, kernel, traffic = True, "wide_kernel", None
+        if not self.auto and self.h.one_pass(M, N, K, self.plan_mode_id, self.A.shape[0], self.B.shape[0]):
+            one_launch, kernel, traffic = True, "wide_kernel", None     # the plan carried out by the kernel that splits for itself
         if one_launch:
             product_bytes = (M + N) * K * 4 + M * N * 4 * (2 if self.beta != 0 else 1)
             split_bytes, split_ms = 0, 0.0

@@ -50,7 +50,7 @@ extern "C" {
  * block and warp tile sizes that it picks for each matrix size by grid search (section "Parameter tuning of CUTLASS").
  * ECGEMM_SHAPE_AUTO (the default) picks per call from the mode and the problem size, and may carry a split-first plan out
  * in one pass over the FP32 operands (blocks of 128 x 128 that split for themselves, the plan's bits; FP16 mode, where
- * that is faster: ecgemm_plan_info reports the plan either way).  The others force one shape for
+ * that is faster: ecgemm_plan_info reports the plan either way, ecgemm_debug_one_pass which it is).  The others force one shape for
  * every later ecgemm_sgemm / ecgemm_product / ecgemm_workspace_size on the handle:
  *   256x128_W4     block tile 256 x 128, 4 waves of 128 x 64, one block per compute unit (every mode);
  *   128x128_X2     block tile 128 x 128, 4 waves of 64 x 64, two blocks per compute unit (the two modes of the method);
@@ -102,6 +102,14 @@ ecgemm_status_t ecgemm_debug_set_tile_order(ecgemm_handle_t handle, int xcd_rema
  */
 ecgemm_status_t ecgemm_debug_tile_order(ecgemm_handle_t handle, int64_t M, int64_t N, int64_t K, ecgemm_mode_t mode,
                                         int32_t *tile_m, int32_t *tile_n, int64_t *disagreements);
+
+/*
+ * Host only: *one_pass = 1 if ecgemm_sgemm with these leading dimensions on this handle (NULL: a fresh one) carries its
+ * split-first plan out in one pass over the FP32 operands (see ECGEMM_SHAPE_AUTO above), 0 if it runs the kernels that
+ * ecgemm_plan_info reports.  For tests, which compare the two, and for programs that read the times of ecgemm_get_timing.
+ */
+ecgemm_status_t ecgemm_debug_one_pass(ecgemm_handle_t handle, int64_t M, int64_t N, int64_t K, ecgemm_mode_t mode, int64_t lda,
+                                      int64_t ldb, int *one_pass);
 
 /*
  * Diagnostic: executes `count` independent v_mfma_f32_32x32x16_f16 (bf16 == 0) or _bf16 (bf16 != 0) instructions,

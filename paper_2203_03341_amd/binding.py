@@ -23,7 +23,7 @@ OK, ERR_INVALID_ARG, ERR_ALLOC, ERR_HIP, ERR_UNSUPPORTED = 0, 1, 2, 3, 4
 SHAPE_AUTO, SHAPE_256x128_W4, SHAPE_128x128_X2, SHAPE_64x64_FUSED, SHAPE_32x32_FUSED = 0, 1, 2, 3, 4
 
 EXPORTS = ["ecgemm_create", "ecgemm_destroy", "ecgemm_set_stream", "ecgemm_workspace_size", "ecgemm_plan_info", "ecgemm_set_workspace",
-           "ecgemm_sgemm", "ecgemm_sgemm_scaled", "ecgemm_sgemm_noalloc", "ecgemm_auto_choice", "ecgemm_last_error_argument", "ecgemm_row_scales", "ecgemm_set_shape", "ecgemm_debug_set_tile_order", "ecgemm_debug_tile_order", "ecgemm_set_scaling", "ecgemm_exponent_range", "ecgemm_choose_mode", "ecgemm_product", "ecgemm_split", "ecgemm_split_size", "ecgemm_debug_mfma", "ecgemm_debug_mfma_rate", "ecgemm_set_timing", "ecgemm_get_timing",
+           "ecgemm_sgemm", "ecgemm_sgemm_scaled", "ecgemm_sgemm_noalloc", "ecgemm_auto_choice", "ecgemm_last_error_argument", "ecgemm_row_scales", "ecgemm_set_shape", "ecgemm_debug_set_tile_order", "ecgemm_debug_tile_order", "ecgemm_debug_one_pass", "ecgemm_set_scaling", "ecgemm_exponent_range", "ecgemm_choose_mode", "ecgemm_product", "ecgemm_split", "ecgemm_split_size", "ecgemm_debug_mfma", "ecgemm_debug_mfma_rate", "ecgemm_set_timing", "ecgemm_get_timing",
            "ecgemm_last_error_string", "ecgemm_status_string"]
 
 
@@ -69,6 +69,7 @@ def _load() -> ctypes.CDLL:
     lib.ecgemm_set_shape.argtypes = [vp, ctypes.c_int]
     lib.ecgemm_debug_set_tile_order.argtypes = [vp, ctypes.c_int, ctypes.c_int, ctypes.c_int]
     lib.ecgemm_debug_tile_order.argtypes = [vp, i64, i64, i64, ctypes.c_int, vp, vp, ctypes.POINTER(i64)]
+    lib.ecgemm_debug_one_pass.argtypes = [vp, i64, i64, i64, ctypes.c_int, i64, i64, ctypes.POINTER(ctypes.c_int)]
     lib.ecgemm_set_scaling.argtypes = [vp, ctypes.c_int, ctypes.c_int]
     lib.ecgemm_exponent_range.argtypes = [vp, i64, i64, vp, i64, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
     lib.ecgemm_choose_mode.argtypes = [vp, ctypes.c_int, ctypes.c_int, i64, i64, i64, vp, i64, vp, i64,
@@ -154,6 +155,12 @@ class Handle:
         info = PlanInfo()
         self._check(_lib.ecgemm_plan_info(self._h, M, N, K, mode, ctypes.byref(info)))
         return info.as_dict()
+
+    def one_pass(self, M: int, N: int, K: int, mode: int, lda: int, ldb: int) -> bool:
+        """ecgemm_debug_one_pass: whether sgemm carries its split-first plan out in one pass over the FP32 operands."""
+        out = ctypes.c_int(-1)
+        self._check(_lib.ecgemm_debug_one_pass(self._h, M, N, K, mode, lda, ldb, ctypes.byref(out)))
+        return out.value == 1
 
     def set_workspace(self, buffer, nbytes: int):
         self._check(_lib.ecgemm_set_workspace(self._h, _ptr(buffer), nbytes))
@@ -244,6 +251,15 @@ def plan_info(M: int, N: int, K: int, mode: int) -> dict:
     if st != OK:
         raise EcgemmError(st, "ecgemm_plan_info")
     return info.as_dict()
+
+
+def one_pass(M: int, N: int, K: int, mode: int, lda: int, ldb: int) -> bool:
+    """ecgemm_debug_one_pass without a handle."""
+    out = ctypes.c_int(-1)
+    st = _lib.ecgemm_debug_one_pass(None, M, N, K, mode, lda, ldb, ctypes.byref(out))
+    if st != OK:
+        raise EcgemmError(st, "ecgemm_debug_one_pass")
+    return out.value == 1
 
 
 def debug_tile_order(M: int, N: int, K: int, mode: int, handle=None):

@@ -735,6 +735,14 @@ WidePlan make_wide_plan(const Plan& pl, int64_t M, int64_t N, int64_t K, ecgemm_
   return w;
 }
 
+// The same for a call on `h` (null: a fresh handle): a shape fixed by the caller, scaling vectors and the handle's
+// pre-scaling keep the plan's own kernels.
+WidePlan wide_plan_of_call(ecgemm_handle_t h, const Plan& pl, int64_t M, int64_t N, int64_t K, ecgemm_mode_t mode, int64_t lda,
+                           int64_t ldb, bool scaling_vectors) {
+  if (scaling_vectors || (h && (h->shape != ECGEMM_SHAPE_AUTO || h->log2_scale_a != 0 || h->log2_scale_b != 0))) return WidePlan();
+  return make_wide_plan(pl, M, N, K, mode, lda, ldb);
+}
+
 // Steps 1 to 5 of such a call.
 ecgemm_status_t launch_wide(ecgemm_handle_t h, const WidePlan& w, ecgemm_op_t transA, ecgemm_op_t transB, int64_t M, int64_t N,
                             int64_t K, float alpha, const float* A, int64_t lda, const float* B, int64_t ldb, float beta,
@@ -984,6 +992,23 @@ ecgemm_status_t ecgemm_debug_tile_order(ecgemm_handle_t handle, int64_t M, int64
     if (m != m_plain || n != n_plain) *disagreements += 1;
     tile_m[pid] = m, tile_n[pid] = n;
   }
+  return ECGEMM_OK;
+}
+
+ecgemm_status_t ecgemm_debug_one_pass(ecgemm_handle_t handle, int64_t M, int64_t N, int64_t K, ecgemm_mode_t mode, int64_t lda,
+                                      int64_t ldb, int* one_pass) {
+  if (M <= 0) return bad_arg(handle, 2, "ecgemm_debug_one_pass: M must be positive");
+  if (N <= 0) return bad_arg(handle, 3, "ecgemm_debug_one_pass: N must be positive");
+  if (K <= 0) return bad_arg(handle, 4, "ecgemm_debug_one_pass: K must be positive");
+  if (!valid_mode(mode)) return bad_arg(handle, 5, "ecgemm_debug_one_pass: unknown mode");
+  if (lda <= 0) return bad_arg(handle, 6, "ecgemm_debug_one_pass: lda must be positive");
+  if (ldb <= 0) return bad_arg(handle, 7, "ecgemm_debug_one_pass: ldb must be positive");
+  if (!one_pass) return bad_arg(handle, 8, "ecgemm_debug_one_pass: null output");
+  const ecgemm_status_t st = check_sizes(handle, M, N, K, mode, 2);
+  if (st != ECGEMM_OK) return st;
+  const Plan pl = make_plan(M, N, K, mode, handle ? handle->shape : ECGEMM_SHAPE_AUTO, kOneLaunchSliced);  // as ecgemm_plan_info
+  if (!pl.shape) return no_plan(handle, pl, "ecgemm_debug_one_pass");
+  *one_pass = wide_plan_of_call(handle, pl, M, N, K, mode, lda, ldb, false).use ? 1 : 0;
   return ECGEMM_OK;
 }
 
@@ -1500,9 +1525,7 @@ ecgemm_status_t sgemm_common(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t 
   const Plan pl = make_plan(M, N, K, mode, h->shape, kOneLaunchSliced);
   if (!pl.shape) return no_plan(h, pl, "ecgemm_sgemm");
   if (pl.items() + 16 > 0x7fffffffLL) return bad_arg(h, 4, "ecgemm_sgemm: too many tiles");
-  WidePlan wide;
-  if (h->shape == ECGEMM_SHAPE_AUTO && row_log2_scale_a == nullptr && h->log2_scale_a == 0 && h->log2_scale_b == 0)
-    wide = make_wide_plan(pl, M, N, K, mode, lda, ldb);
+  const WidePlan wide = wide_plan_of_call(h, pl, M, N, K, mode, lda, ldb, row_log2_scale_a != nullptr);
   SplitJob job_a, job_b;
   char* ws = nullptr;
   st = acquire_workspace(h, pl.total_bytes, &ws, workspace_kind);

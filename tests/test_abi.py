@@ -230,6 +230,27 @@ def test_plans_of_random_problems_are_well_formed():
             assert per_slice * (p["slices"] - 1) < stages, case                            # the last slice is not empty
 
 
+def test_which_plans_are_carried_out_in_one_pass():
+    """Both sides of every line of the rule, the sizes that the GPU tests rely on, and what keeps a call out of it."""
+    import paper_2203_03341_amd as ec
+    one_pass = lambda M, N, K, mode=ec.MODE_FP16_SPLIT, lda=None, ldb=None: ec.one_pass(M, N, K, mode, lda or M, ldb or K)
+    slices = lambda M, N, K: ec.plan_info(M, N, K, ec.MODE_FP16_SPLIT)["slices"]
+    whole = lambda *size: slices(*size) == 1 and ec.plan_info(*size, ec.MODE_FP16_SPLIT)["shape"] <= ec.SHAPE_128x128_X2
+    for size in ((2048, 2048, 512), (2048, 2048, 2048), (1500, 2000, 64), (1400, 1285, 127)):     # one round of whole tiles
+        assert whole(*size) and one_pass(*size), size
+    for size, taken in (((2304, 2176, 223), False), ((2304, 2176, 224), True), ((2304, 2176, 512), True), ((2304, 2176, 513), False),
+                        ((4096, 2048, 256), True), ((4097, 2048, 256), False)):                      # two rounds, 224 to 512 deep
+        assert whole(*size) and one_pass(*size) == taken, size
+    for size, taken in (((1024, 1024, 65536), True), ((1024, 1024, 32768), True),                     # two rounds of slices,
+                        ((1600, 1600, 17280), True), ((1728, 1728, 17280), False)):                   # 1 / M + 1 / N at least 1 / 800
+        blocks = slices(*size) * -(-size[0] // 128) * -(-size[1] // 128)
+        assert slices(*size) > 1 and 256 < blocks <= 512 and one_pass(*size) == taken, (size, blocks)
+    assert one_pass(2048, 2048, 512, lda=1 << 21, ldb=1 << 21)
+    assert not one_pass(2048, 2048, 512, lda=(1 << 21) + 1) and not one_pass(2048, 2048, 512, ldb=(1 << 21) + 1)
+    assert not one_pass(2048, 2048, 512, ec.MODE_BF16_FULL) and not one_pass(2048, 2048, 512, ec.MODE_FP16_MARKIDIS)
+    assert not one_pass(256, 256, 256) and not one_pass(16384, 16384, 16384)                         # one launch; too many tiles
+
+
 def test_tile_order_reciprocal_arithmetic_agrees_with_division():
     """The kernels locate a tile with multiplications by reciprocals prepared on the host.  For grids of many shapes
     (bands of equal and unequal width, a shorter last group of tile rows, one row, one column, forced orders) every

@@ -299,13 +299,14 @@ def test_bitwise_reproducible_and_stream(mode):
 
 
 @pytest.mark.parametrize("mode", ["fp16", "bf16"])
-@pytest.mark.parametrize("size", [(1280, 1024, 3072), (300, 200, 260), (128, 128, 4096)])
+@pytest.mark.parametrize("size", [(1280, 1024, 3072), (2900, 2900, 1024), (300, 200, 260), (128, 128, 4096)])
 def test_a_call_can_be_captured_in_a_graph_and_replayed(mode, size):
     """With a caller workspace the call only launches kernels (no allocation, no memset, no wait), so it can be recorded
     into a HIP graph.  Every replay, with eager work and synchronisations in between, must give the eager bits.
-    The first size runs as split pair + product with every tile sliced along K + reduction, three kernels; the second
-    as one launch that needs no workspace; the third as one launch with the depth in slices + reduction, whose partial
-    sums are all the workspace holds."""
+    The first size has every tile sliced along K: split pair + product + reduction, three kernels, in BF16 mode, one pass
+    over the operands + reduction in FP16 mode; the second is split first in both, its last tiles sliced; the third runs as
+    one launch that needs no workspace; the fourth as one launch with the depth in slices + reduction, whose partial sums
+    are all the workspace holds."""
     import torch
     import paper_2203_03341_amd as ec
     M, N, K = size
@@ -318,6 +319,7 @@ def test_a_call_can_be_captured_in_a_graph_and_replayed(mode, size):
     nbytes = h.workspace_size(ec.OP_N, ec.OP_N, M, N, K, mode_id)
     plan = h.plan_info(M, N, K, mode_id)
     assert (plan["shape"] >= ec.SHAPE_64x64_FUSED) == (M <= 300) and (nbytes == 0) == (M == 300) and (plan["slices"] > 1) == (M != 300)
+    assert h.one_pass(M, N, K, mode_id, A.shape[0], B.shape[0]) == (M == 1280 and mode == "fp16") and (plan["whole_tiles"] > 0) == (M in (2900, 300))
     workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device="cuda")
     h.set_workspace(workspace, max(nbytes, 256))
     dA, dB, dC_in = to_device(A), to_device(B), to_device(C)
@@ -1160,6 +1162,8 @@ def test_one_pass_over_the_operands_gives_the_bits_of_the_plan(transA, transB, M
     h.set_stream(torch.cuda.current_stream().cuda_stream)
     plan = h.plan_info(M, N, K, ec.MODE_FP16_SPLIT)
     assert plan["shape"] in (ec.SHAPE_256x128_W4, ec.SHAPE_128x128_X2)
+    rows_a, rows_b = M if transA == "N" else K, K if transB == "N" else N
+    assert h.one_pass(M, N, K, ec.MODE_FP16_SPLIT, rows_a + pads[0], rows_b + pads[1])
 
     def operand(cols, rows, pad):
         store = torch.full((cols, rows + pad), float("nan"), device="cuda")
@@ -1173,6 +1177,7 @@ def test_one_pass_over_the_operands_gives_the_bits_of_the_plan(transA, transB, M
     def call(shape, alpha, beta):
         out = C.clone()
         h.set_shape(shape)
+        assert h.one_pass(M, N, K, ec.MODE_FP16_SPLIT, A.shape[1], B.shape[1]) == (shape == ec.SHAPE_AUTO)
         h.sgemm(ops[transA], ops[transB], M, N, K, alpha, A, A.shape[1], B, B.shape[1], beta, out, C.shape[1], ec.MODE_FP16_SPLIT)
         torch.cuda.synchronize()
         return out
@@ -1192,7 +1197,7 @@ def test_one_pass_over_the_operands_gives_the_bits_of_the_plan(transA, transB, M
 
 def test_a_deep_product_is_not_split_first():
     """1024 x 1024 x 32768: the interval in front of the product (ecgemm_set_timing) holds no split pass, whose 0.5 GB the
-    card cannot move in the time; with the shape fixed by the caller it does."""
+    card takes its time to move; with the shape fixed by the caller it does, and is several times as long."""
     import torch
     import paper_2203_03341_amd as ec
     M = N = 1024
@@ -1203,6 +1208,7 @@ def test_a_deep_product_is_not_split_first():
         h = ec.Handle()
         h.set_stream(torch.cuda.current_stream().cuda_stream)
         h.set_shape(shape)
+        assert h.one_pass(M, N, K, ec.MODE_FP16_SPLIT, M, K) == (shape == ec.SHAPE_AUTO)
         for timing in (False, True):
             h.set_timing(timing)
             for _ in range(5):
@@ -1211,7 +1217,7 @@ def test_a_deep_product_is_not_split_first():
         calls, split_ms, _ = h.get_timing()
         split_us[shape] = split_ms * 1e3 / calls
         h.destroy()
-    assert split_us[ec.SHAPE_AUTO] < 40 < 60 < split_us[ec.SHAPE_256x128_W4], split_us
+    assert 2 * split_us[ec.SHAPE_AUTO] < split_us[ec.SHAPE_256x128_W4], split_us
 
 
 @pytest.mark.parametrize("mode", ["fp16", "bf16"])
