@@ -454,8 +454,9 @@ def test_measuring_costs_what_there_is_to_measure():
 
 @pytest.mark.parametrize("transA,transB,pad", [("N", "N", 0), ("T", "T", 0), ("N", "T", 0), ("T", "N", 0), ("N", "T", 1), ("T", "N", 3)])
 def test_measuring_splits_of_every_variant(transA, transB, pad):
-    """Products that need packed operands are measured by their splits: every variant of the split kernel (both storage
-    orders, aligned and not), each of the outcomes, an infinity and a NaN in the last element."""
+    """Products that need packed operands are measured by their splits: both storage orders, aligned (blocks of 256 rows, of
+    single tiles) and not (of 64 rows), each of the outcomes, an infinity and a NaN in the last element.  (The variants for
+    large operands are the next test's.)"""
     import paper_2203_03341_amd as ec
     h = ec.Handle()
     M, N, K = 1060, 1044, 196
@@ -468,15 +469,18 @@ def test_measuring_splits_of_every_variant(transA, transB, pad):
 
 
 @pytest.mark.parametrize("transA,transB,M,N,K,pad", [("T", "N", 2048, 1000, 4132, 0), ("T", "N", 1000, 2050, 4128, 0),
-                                                     ("T", "N", 2048, 2048, 4100, 0), ("N", "T", 4100, 90, 4100, 1)])
+                                                     ("T", "N", 2048, 2048, 4100, 0), ("N", "T", 4100, 90, 4100, 1),
+                                                     ("N", "T", 521, 40, 65940, 0)])
 def test_measuring_splits_of_large_operands(transA, transB, M, N, K, pad):
-    """Aligned operands with k contiguous are measured in blocks of four 64 x 32 tiles from 4096 such tiles on: beside an
-    operand in single tiles on either side, and both; one and two tiles in the last block of a row; then an unaligned
-    operand with r contiguous that is too large to share a launch."""
+    """Operands with k contiguous are measured in blocks of four 64 x 32 tiles from 4096 such tiles on: beside an operand
+    in single tiles on either side, and both; one and two tiles in the last block of a row; then operands with r contiguous
+    whose lines start anywhere: in blocks of 256 rows, from the caches, and of 64, from memory and in a launch of its own."""
     import paper_2203_03341_amd as ec
     h = ec.Handle()
     tiles = lambda rows: (rows + 255) // 256 * 4 * ((K + 31) // 32)
-    assert max(tiles(M), tiles(N)) >= (4096 if pad == 0 else 8192) and (K + 31) // 32 % 4 in (1, 2)
+    assert max(tiles(M), tiles(N)) >= (4096 if transA == "T" else 8192) and (K + 31) // 32 % 4 in (1, 2)
+    if transA == "N":           # four bytes read and two parts written per value, against the memory-side cache
+        assert (M + pad) % 4 != 0 and (8 * M * K > 256 << 20) == (M == 521)
     chosen = [_check_choice_and_bits(h, transA, transB, M, N, K, dist_a, dist_b, 41 + i, pad, last)
               for i, (dist_a, dist_b, last) in enumerate((("urand", "urand", None), (TYPE3, TYPE1, None), ("urand", "urand", np.nan)))]
     assert chosen == ["fp16", "fp16 scaled", "bf16"]
