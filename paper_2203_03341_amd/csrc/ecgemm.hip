@@ -707,12 +707,16 @@ ecgemm_status_t launch_fused(ecgemm_handle_t h, const Plan& pl, ecgemm_op_t tran
 // 1536 x 1088 x 1536 35.8 / 31.1, 8179 x 459 x 676 32.4 / 26.3, 384 x 2112 x 8640 75.3 / 53.4), and in two rounds if the
 // operands are large next to the product (1 / M + 1 / N >= 1 / 800): 40 of them 0.60 to 0.98 (1024 x 1024 x 65536 509 / 437,
 // 512 x 1920 x 21248 184 / 140, 1024 x 2176 x 8448 137 / 134); the nearest beyond that line 1728 x 1728 x 17280 352 / 365
-// and 1344 x 2368 x 20672 496 / 500.  Two rounds of whole tiles where they are short, so that the launch and the fixed cost
-// of a split pass still count, and not so short that the blocks' first loads do, twice: of 32 random ones 224 to 512 deep, 31 took
-// 0.79 to 0.99 of the time (8832 x 576 x 256 NT 27.6 / 21.9, 2304 x 3136 x 320 TN 30.4 / 24.8, 9216 x 704 x 448 TN 38.6 / 38.3)
-// and one longer (3822 x 2033 x 327 TN 38.1 / 39.7).  On both sides of these depths most gain too, but more calls lose: 192
-// deep 0.85 to 1.02, 128 to 178 deep 0.86 to 1.11, 672 to 1000 deep 0.91 to 1.15.  Beyond two rounds, and in deeper ones,
-// splitting every element M / 128 or N / 128 times costs more (up to 1.39).
+// and 1344 x 2368 x 20672 496 / 500.  Of 220 random ones those in three slices or more took 0.51 to 0.985; in two, where
+// the second round is short of blocks for such operands (M N > 3 / 2 blocks (M + N)) and the product more than 20000 deep,
+// 8 of 15 took longer (3264 x 832 x 23232 NN, 364 blocks, 521 / 572, 2944 x 1088 x 34816 NN, 414, 812 / 860): those are left to
+// the plan, and of the other 34 in two slices one took longer (929 x 2827 x 11843 TN 251 / 255), the rest 0.72 to 0.98.
+// Two rounds of whole tiles where they are short, so that the launch and the fixed cost of a split pass still count, and
+// not so short that the blocks' first loads do, twice: of 32 random ones 224 to 512 deep, 31 took 0.79 to 0.99 of the time
+// (8832 x 576 x 256 NT 27.6 / 21.9, 2304 x 3136 x 320 TN 30.4 / 24.8, 9216 x 704 x 448 TN 38.6 / 38.3) and one longer (3822 x
+// 2033 x 327 TN 38.1 / 39.7), and 60 with a second round of 1 to 84 blocks 0.66 to 0.97.  On both sides of these depths most
+// gain too, but more calls lose: 192 deep 0.85 to 1.02, 128 to 178 deep 0.86 to 1.11, 672 to 1000 deep 0.91 to 1.15.  Beyond
+// two rounds, and in deeper ones, splitting every element M / 128 or N / 128 times costs more (up to 1.39).
 struct WidePlan {
   bool use = false;
   int tiles_m = 0, tiles_n = 0, slices = 1;
@@ -730,8 +734,9 @@ WidePlan make_wide_plan(const Plan& pl, int64_t M, int64_t N, int64_t K, ecgemm_
   w.tiles_m = (int)((M + kWideTile - 1) / kWideTile);
   w.tiles_n = (int)((N + kWideTile - 1) / kWideTile);
   const int64_t blocks = tiles * w.slices;
+  const bool short_second_round = w.slices == 2 && K > 20000 && 2 * M * N > 3 * blocks * (M + N);
   w.use = blocks <= kPlanComputeUnits ||
-          (blocks <= 2 * kPlanComputeUnits && (w.slices > 1 ? M * N <= 800 * (M + N) : K >= 224 && K <= 512));
+          (blocks <= 2 * kPlanComputeUnits && (w.slices > 1 ? M * N <= 800 * (M + N) && !short_second_round : K >= 224 && K <= 512));
   return w;
 }
 
