@@ -1389,8 +1389,9 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
   sums.if_fits = kChoiceFp16, sums.if_fits_scaled = kChoiceFp16Scaled, sums.if_not = kChoiceBf16;
   sums.choice = choice;
   if (by_rows) {
-    // Nothing reads packed operands: both FP16 candidates are measured in one launch that writes none, the choice is
-    // another (steps 1 to 3 in two launches instead of five).  The blocks' sums lie where the packed operands would.
+    // Nothing reads packed operands: both FP16 candidates are measured in one launch that writes none, and the choice is
+    // made by the blocks of the product or, where they do not (above), in a launch of its own; five launches otherwise.
+    // The blocks' sums lie where the packed operands would.
     const int rows_per_block = measure_rows_per_block(M, N, K);
     const unsigned blocks_a = (unsigned)((M + rows_per_block - 1) / rows_per_block), blocks_b = (unsigned)((N + rows_per_block - 1) / rows_per_block);
     if (kMeasureSums * sizeof(double) * ((size_t)blocks_a + blocks_b) > ap.packed_bytes)

@@ -57,7 +57,7 @@ template <int KIND, bool DEPTH>
 struct WideOperand {
   static constexpr int NP = parts_of_split(KIND);
   static constexpr int REGION_BYTES = (kWideTile / 32) * 4 * NP * 1024;
-  static_assert(KIND == kSplitFp16Scaled, "the test for ordinary values is the FP16 pair's");
+  static_assert(KIND == kSplitFp16Scaled, "conversions that saturate (MODE.FP16_OVFL) stand in for Splitter's clamps");
 
   const float* tile;      // &X(first row of the tile, first k of the slice), the same for the block
   const float* lane_ptr;  // this lane's part of it: row 4 (t % 32) or t / 8, k = 0
@@ -321,7 +321,6 @@ __global__ void __launch_bounds__(kWideThreads, 1) wide_kernel(const WideParams 
   };
   typedef std::integral_constant<int, 0> set0_t;
   typedef std::integral_constant<int, 1> set1_t;
-  const float corr_scale = METHOD == kMethodFp16Split ? 0x1p-11f : 1.0f;
   for (int pass = 0;; ++pass) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -357,7 +356,7 @@ __global__ void __launch_bounds__(kWideThreads, 1) wide_kernel(const WideParams 
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          acc_main[i][j][v] = acc_main[i][j][v] + acc_corr[i][j][v] * corr_scale;
+          acc_main[i][j][v] = acc_main[i][j][v] + acc_corr[i][j][v] * 0x1p-11f;  // (the residuals carry 2^11)
           largest = __builtin_elementwise_maximum(largest, __builtin_fabsf(acc_main[i][j][v]));
         }
     if (pass == 1) break;
