@@ -295,6 +295,10 @@ Plan plan_with_shape(int64_t M, int64_t N, int64_t K, ecgemm_mode_t mode, ecgemm
 //   plan differs (4 % of random ones with such depths; 60 of them timed): FP16, whose split-first plans the wide kernel
 //   carries out, 7 % slower on average, 0.92 to 1.30 of the time; BF16 beyond 1024 deep 0.92 to 1.16, level on average.
 //   Three for BF16 up to 1024 deep: 20 of these 0.75 to 0.93 with one (2746 x 330 x 622 TN 32.3 us / 24.1).
+//   (In FP16 mode the three chunks stand for what the estimate leaves out, the wide kernel: of 16 problems whose plan is
+//   split first, carried out in one pass, at a depth of 4 n + 1 and one launch at 4 n, the former took 0.77 to 0.95 of the
+//   latter NT, 0.87 on average, and 0.81 to 1.05 TN, 0.96: 467 x 2967 x 712 / 713 NT 25.1 / 19.6 us, 2922 x 453 x 276 / 277
+//   TN 12.7 / 13.3.)
 double split_first_us(const Plan& pl, int64_t M, int64_t N, int64_t K, ecgemm_mode_t mode) {
   const double operand_mb = 4.0 * ((double)M + (double)N) * (double)K / 1e6;
   // (beyond 8.5 us the pass runs at the memory's pace: 8 or 10 bytes moved per element)
@@ -426,12 +430,12 @@ ecgemm_status_t hip_fail(ecgemm_handle_t h, hipError_t e, const char* where) {
 
 // Operands with k contiguous: one 64 x 32 tile a block, or from 2^12 tiles on (2^23 elements, four blocks per unit)
 // four, kSplitKContiguousDeep: fewer and longer blocks with four times the loads in flight.  Below, single
-// tiles, which spread a small operand over the chip.  Whole calls with single / four tiles throughout, us: FP16
-// 8192 x 512 x 1024 41.0 / 37.8, 1024 x 1024 x 16384 145.2 / 137.0, 4096^3 361.6 / 358.6, 9000 x 1024 x 9000 551 / 531;
-// BF16 1024 x 1024 x 16384 219.2 / 211.8; FP32, which has nothing to convert, 9000 x 512 x 9000 842 / 821; one operand
-// split and multiplied with a kept one, FP16, 512 x 5000 x 9000 202 / 190, and at worst 512 x 2048 x 20000 165.1 / 166.5.
-// The automatic mode's measuring split also leaves a quarter of the sums to add up for the choice: 2048 x 2048 x 4096
-// 135 / 125, 8192^3 2607 / 2552 (its two choices 20 / 11 each).
+// tiles, which spread a small operand over the chip.  Whole calls with single / four tiles throughout, us, TN: FP16
+// 4096^3 345.0 / 341.4, 9000 x 1024 x 9000 533.6 / 514.9; BF16 1024 x 1024 x 16384 214.5 / 204.3; FP32, which has nothing
+// to convert, 9000 x 512 x 9000 841 / 821.  One operand alone: FP16 8192^2 102.8 / 96.8, 5000 x 9000 75.4 / 63.2, 1024 x
+// 65536 109.0 / 99.0, BF16 8192^2 134.4 / 122.7, and at worst FP16 4096 x 8192 40.2 / 41.2, BF16 2048 x 4096 14.3 / 14.7;
+// below the line FP16 2048^2 5.53 / 6.04, BF16 7.99 / 7.74.  The automatic mode's measuring split also leaves a quarter of
+// the sums to add up for the choice: 2048 x 2048 x 4096 137.0 / 124.1, 8192^3 2620 / 2580.
 constexpr int64_t kSplitDeepFrom = 1 << 12;  // in tiles
 
 // Operands with the rows contiguous and aligned, from 256 MiB on, the size of the memory-side cache, are read past it (see

@@ -41,7 +41,8 @@ namespace ecgemm {
 //                   rotation of fused_lds_slot the 64 lanes of a write then go to 64 different places of a bank period).
 //                   Lines on no alignment, or a depth that is no multiple of four, read one value per lane before: 1024^3
 //                   TN with odd leading dimensions FP16 21.0 us / 14.1, BF16 27.0 / 18.1, 512^3 9.7 / 7.7 and 11.5 / 8.9, 300 x
-//                   200 x 77 TT BF16 6.96 / 6.57; aligned operands, FP16 256^3 NN 6.0 / 6.1, 512^3 7.3 / 7.4.
+//                   200 x 77 TT BF16 6.96 / 6.57; aligned operands FP16 256^3 NN 6.2 / 5.9, 512^3 7.5 / 7.2,
+//                   half of which is the split's (FastSplit).
 enum FusedLayout { kFusedRows = 0, kFusedDepth = 1 };
 // Chunks in flight in registers (the loop is unrolled by this: a register ring is indexed statically).  Four and six
 // instead of two measured slower at every size (1024^3: 18.9 and 29.6 against 18.1 us).
@@ -287,8 +288,8 @@ struct FusedOperand {
   __device__ __forceinline__ void deposit_last(const float (&x)[V], int c, char* region) const {
     float v[V];
     complete(x, c, v);
-    // (one write for both paths, unlike deposit_whole: another copy of its two moves the registers of the loop over the
-    // whole chunks, 192 x 1920 x 62912 TT in FP16 mode 334 us with this, 345 with that)
+    // (one write for both paths, unlike deposit_whole, which every chunk goes through: 300 x 200 x 77 TT in BF16 mode 6.44 us
+    // so, 6.57 with two writes; 192 x 1920 x 62912 and the cubes in FP16 mode level)
     unsigned words[V / 2][NP];
     const bool ordinary = split_ordinary<GENERAL>(v, words);
     if (__builtin_amdgcn_ballot_w64(!ordinary) != 0) split_with_care(v, words);

@@ -110,7 +110,8 @@ struct FastSplit {
       if constexpr (KIND == kSplitFp16Scaled) {
         // (the multiply-add in 32 bits and one packed conversion: the form that delivers a half by itself takes 8 cycles
         // where the others take 4, and holds up the matrix instructions of other waves; hence the empty statement.  FP16 calls
-        // with that form / with this one: 1024^3 15.5 / 14.4 us, 512^3 7.5 / 7.35, 256^3 6.2 / 6.0)
+        // with that form / with this one: 1024^3 NN 14.2 / 13.9 us, NT 14.5 / 14.0, TN 13.8 / 13.9, 512^3 7.4 / 7.2, 256^3 6.1 /
+        // 5.9, and behind where blocks walk a long way with little else to do, 192 x 1920 x 62912 NN 308 / 315, NT 319 / 321)
         float r0 = __builtin_fmaf((float)hi[0], -2048.0f, scaled0), r1 = __builtin_fmaf((float)hi[1], -2048.0f, scaled1);
         asm("" : "+v"(r0), "+v"(r1));
         out[1] = __builtin_bit_cast(unsigned, __builtin_convertvector(fused_float2_t{r0, r1}, fused_half2_t));
