@@ -455,12 +455,17 @@ constexpr int64_t kSplitStreamedElems = 1ll << 26;
 // (tile_of_block).  Plain order / runs, us, FP16: k contiguous 2052^2 8.6 / 6.7, 4100^2 24.5 / 21.9, 5000^2 35.4 / 30.7, r
 // contiguous 6.6 / 6.4, 22.7 / 21.3, 32.0 / 30.0; larger operands come from memory, where the runs keep fewer
 // neighbouring pages open at a time: k contiguous 6000^2 54.0 / 56.2, 7000^2 71.1 / 76.4, 9000^2 117.9 / 123.1, 1024 x 65536
-// with ld 65540 101 / 124.  Whole lines keep the plain order (runs cost them up to 7 %), and so do operands with k
-// contiguous of fewer than five single tiles a unit, all of whose blocks are on the chip at once: BF16 160 x 7631 (717 tiles)
-// 4.85 / 5.2, 896 x 2368 with ld 2372 (1036) 5.5 / 5.8, FP16 10385 x 198 (1141) 4.68 / 4.75; from there on BF16 1250 x 2094 (1320)
-// 7.1 / 6.5, FP16 4457 x 1066 (2380) 10.7 / 7.0.
+// with ld 65540 101 / 124.  Whole lines keep the plain order (runs cost the split up to 7 %).
+// With k contiguous the runs are runs of rows, and the product kernel's tiles are dealt to the XCDs in runs too: it finds
+// the parts of many rows in the L2 that wrote them, which shows in the call and not in the split alone (14664 x 151
+// BF16 split 5.8 / 6.0, split and multiplied with a kept 253 columns 25.8 / 20.5, 13600 x 167 FP16 by 93 19.8 / 16.2, 2864 x
+// 808 by 315 26.6 / 24.9).  An operand of few rows and a great depth has its product cut along k instead, and the order
+// only moves its parts away (306 x 6819 FP16 by 332 24.3 / 26.2, 322 x 10125 by 81 25.4 / 28.9, 585 x 3444 BF16 by 340 31.1 /
+// 32.4).  Of 72 such calls of 500 to 1280 tiles the plain order was ahead up to 585 rows (0 to 7 %; level to 2 % behind at
+// 173, 572 and 612) and level or behind from there on (up to 26 %); of 45 calls of more tiles, whose blocks do not all
+// start together, up to 360 rows (0.88 to 1.03, at worst 1.09), and level or behind from there on (0.99 to 1.06).
 constexpr int64_t kSplitCachedBytes = 256ll << 20;
-constexpr int64_t kSplitRunsFrom = 1280;  // in tiles
+constexpr int64_t kSplitRunsRows = 400, kSplitRunsRowsShort = 600, kSplitRunsShort = 1280;  // the latter below the last, in tiles
 
 // Rows contiguous, lines that start anywhere: 64 rows a block (kSplitRContiguous), or 256 (kSplitRContiguousWide) where
 // the operand comes from the caches (from memory, FP16 64 / 256 rows: 9001^2 121 / 126 us, 12001^2 217 / 223; from the
@@ -500,7 +505,7 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
   const int64_t tiles_alone = (Kp / 32) * ((rows + 63) / 64), tiles_together = tiles_alone + (Kp / 32) * ((rows_beside + 63) / 64);
   const bool wide = aligned || (cached && tiles_together >= (rows_beside > 0 ? kSplitWideFromPair : kSplitWideFrom));
   job->variant = k_contiguous ? kSplitKContiguous : wide ? kSplitRContiguousWide : kSplitRContiguous;
-  job->runs = !whole_lines && cached && (!k_contiguous || tiles_alone >= kSplitRunsFrom);
+  job->runs = !whole_lines && cached && (!k_contiguous || rows >= (tiles_alone < kSplitRunsShort ? kSplitRunsRowsShort : kSplitRunsRows));
   // blocks are 64 rows x 32 k, or 256 x 32 (wide), or four tiles along k
   switch (job->variant) {
     case kSplitRContiguousWide: job->fast_tiles = (unsigned)(Rp / 256), job->blocks = (unsigned)(blocks64 / 4); break;

@@ -152,10 +152,12 @@ def test_split_of_large_operands_with_the_depth_contiguous(mode_bf16, rows, dept
 @pytest.mark.parametrize("mode_bf16", [False, True])
 @pytest.mark.parametrize("op,rows,depth,pad", [
     ("N", 1021, 4099, 0), ("N", 1022, 4100, 1), ("N", 1023, 4097, 2), ("N", 3, 40, 1), ("N", 2, 33, 2), ("N", 259, 31, 1),
-    ("T", 70, 3, 0), ("T", 65, 2, 3), ("T", 67, 1, 3), ("T", 131, 203, 2), ("T", 2047, 4101, 0), ("T", 2046, 4103, 3)])
+    ("T", 70, 3, 0), ("T", 65, 2, 3), ("T", 67, 1, 3), ("T", 131, 203, 2), ("T", 2047, 4101, 0), ("T", 2046, 4103, 3),
+    ("T", 599, 333, 1), ("T", 600, 333, 1), ("T", 399, 6001, 2), ("T", 400, 6001, 2)])
 def test_split_of_lines_on_any_alignment(op, rows, depth, pad, mode_bf16):
     """Sources are read 16 bytes at a time wherever their lines start: 0 to 3 values left over at the end of a line, lines
-    shorter than one such read, few blocks and many, in either orientation, NaN behind every line.  Bit for bit."""
+    shorter than one such read, few blocks and many, either side of the row counts from which the XCDs take runs of the
+    blocks, in either orientation, NaN behind every line.  Bit for bit."""
     sr, sc = (rows, depth) if op == "N" else (depth, rows)
     store = si.exp_rand(sr, sc, -30, 20, 11, si.ID_A, ld=sr + pad)
     got = _run(op, store, rows, depth, mode_bf16)
