@@ -480,9 +480,14 @@ constexpr int64_t kSplitWideFrom = 1200, kSplitWideFromPair = 1800;
 
 // X = op(src) is rows x depth.  op == N: X(r, k) = src[r + k * ld]; op == T: X(r, k) = src[k + r * ld].
 // `rows_beside`: of the other operand of the product, which is as deep and is split next to this one; 0 if there is none.
+// `measured`: the split also finds every row's largest exponent and leaves its blocks' sums for the choice.  Rows are then
+// written by many blocks at once, which runs keep within one XCD, and fewer blocks leave fewer sums: whatever comes from the
+// caches takes both, at any size.  Automatic mode, the rules of the other splits / so: runs, 256 x 192 x 15744 TN with ld
+// 15748 82.3 us / 74.5, 64 x 192 x 28096 TT 73.2 / 65.4; blocks of 256 rows, 111 x 107 x 11050 NT 85.2 / 53.0, 218 x 85 x
+// 8885 NN 66.0 / 53.8; of 83 random calls of few rows or columns 0.62 to 1.03 of the time.
 ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, int64_t depth, const float* src, int64_t ld,
                                ecgemm_mode_t mode, void* packed, int log2_prescale, const int* row_log2_scale, SplitJob* job,
-                               int64_t rows_beside) {
+                               int64_t rows_beside, bool measured = false) {
   const int64_t Rp = round_up(rows, kRowPad), Kp = round_up(depth, kDepthPad);
   const int64_t blocks64 = (Kp / 32) * (Rp / 64);
   if (blocks64 > 0x7fffffff) return fail(h, ECGEMM_ERR_INVALID_ARG, "operand has more than 2^42 elements");
@@ -503,9 +508,9 @@ ecgemm_status_t make_split_job(ecgemm_handle_t h, ecgemm_op_t op, int64_t rows, 
   job->row_max = nullptr;
   job->streamed = rows * depth >= kSplitStreamedElems && (split_is_bf16(split_kind_of((int)mode)) ? whole_lines : aligned);  // (kSplitRContiguousWide)
   const int64_t tiles_alone = (Kp / 32) * ((rows + 63) / 64), tiles_together = tiles_alone + (Kp / 32) * ((rows_beside + 63) / 64);
-  const bool wide = aligned || (cached && tiles_together >= (rows_beside > 0 ? kSplitWideFromPair : kSplitWideFrom));
+  const bool wide = aligned || (cached && (measured || tiles_together >= (rows_beside > 0 ? kSplitWideFromPair : kSplitWideFrom)));
   job->variant = k_contiguous ? kSplitKContiguous : wide ? kSplitRContiguousWide : kSplitRContiguous;
-  job->runs = !whole_lines && cached && (!k_contiguous || rows >= (tiles_alone < kSplitRunsShort ? kSplitRunsRowsShort : kSplitRunsRows));
+  job->runs = !whole_lines && cached && (!k_contiguous || measured || rows >= (tiles_alone < kSplitRunsShort ? kSplitRunsRowsShort : kSplitRunsRows));
   // blocks are 64 rows x 32 k, or 256 x 32 (wide), or four tiles along k
   switch (job->variant) {
     case kSplitRContiguousWide: job->fast_tiles = (unsigned)(Rp / 256), job->blocks = (unsigned)(blocks64 / 4); break;
@@ -537,7 +542,10 @@ template <int KIND, bool STATS = false>
 void launch_split_kind(hipStream_t stream, const SplitJob& a, const SplitJob* b) {
   // both operands in one launch up to 2^26 elements in large blocks (a quarter of that in small ones): in one / two
   // launches 1024 x 1024 x 16384 136 / 139 us a call, 2048 x 2048 x 16384 391 / 406
-  if (b != nullptr && (uint64_t)a.blocks + b->blocks <= 8192) {
+  // (measured together, rows contiguous means blocks of 256: an operand that takes others comes from memory)
+  const bool one_launch = b != nullptr && (uint64_t)a.blocks + b->blocks <= 8192 &&
+                          !(STATS && (a.variant == kSplitRContiguous || b->variant == kSplitRContiguous));
+  if (one_launch) {
     const dim3 grid(a.blocks + b->blocks), block(256);
     if (a.variant == kSplitKContiguousDeep || b->variant == kSplitKContiguousDeep)
       hipLaunchKernelGGL((split_pair_kernel<KIND, true, STATS>), grid, block, 0, stream, a, *b);
@@ -1348,9 +1356,9 @@ ecgemm_status_t sgemm_auto(ecgemm_handle_t h, ecgemm_op_t transA, ecgemm_op_t tr
   rows_a.scale = scales_a;
   rows_b.scale = scales_b;
   SplitJob fp16_a, fp16_b, scaled_a, scaled_b, bf16_a, bf16_b;
-  st = make_split_job(h, transA, M, K, A, lda, ECGEMM_MODE_FP16_SPLIT, ws, h->log2_scale_a, nullptr, &fp16_a, N);
+  st = make_split_job(h, transA, M, K, A, lda, ECGEMM_MODE_FP16_SPLIT, ws, h->log2_scale_a, nullptr, &fp16_a, N, true);
   if (st != ECGEMM_OK) return st;
-  st = make_split_job(h, op_b, N, K, B, ldb, ECGEMM_MODE_FP16_SPLIT, ws + ap.fp16.a_bytes, h->log2_scale_b, nullptr, &fp16_b, M);
+  st = make_split_job(h, op_b, N, K, B, ldb, ECGEMM_MODE_FP16_SPLIT, ws + ap.fp16.a_bytes, h->log2_scale_b, nullptr, &fp16_b, M, true);
   if (st != ECGEMM_OK) return st;
   st = make_split_job(h, transA, M, K, A, lda, ECGEMM_MODE_BF16_FULL, ws, h->log2_scale_a, nullptr, &bf16_a, N);
   if (st != ECGEMM_OK) return st;

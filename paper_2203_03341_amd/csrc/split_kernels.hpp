@@ -596,7 +596,7 @@ __global__ void __launch_bounds__(256) split_pair_kernel(const SplitJob a, const
   SplitStats stats;
   // (The order of the branches moves the measuring instance, whose code is larger than the instruction cache: automatic
   // mode, 1024 x 1024 x 16384 NN, wide beside deep, 163.4 us in this order, 164 to 168 in five others.)
-  if (job.variant == kSplitRContiguous) {
+  if (!STATS && job.variant == kSplitRContiguous) {  // (measured, not one of a pair)
     split_block_r_contiguous<KIND, STATS>(job, block, &stats);
   } else if (job.variant == kSplitKContiguous) {
     split_tiles_k_contiguous<KIND, 1, STATS>(job, tile_of_block(job, block), &stats);

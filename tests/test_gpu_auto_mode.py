@@ -454,8 +454,8 @@ def test_measuring_costs_what_there_is_to_measure():
 
 @pytest.mark.parametrize("transA,transB,pad", [("N", "N", 0), ("T", "T", 0), ("N", "T", 0), ("T", "N", 0), ("N", "T", 1), ("T", "N", 3)])
 def test_measuring_splits_of_every_variant(transA, transB, pad):
-    """Products that need packed operands are measured by their splits: both storage orders, aligned (blocks of 256 rows, of
-    single tiles) and not (of 64 rows), each of the outcomes, an infinity and a NaN in the last element.  (The variants for
+    """Products that need packed operands are measured by their splits: both storage orders, aligned and not (blocks of
+    256 rows, of single tiles), each of the outcomes, an infinity and a NaN in the last element.  (The variants for
     large operands are the next test's.)"""
     import paper_2203_03341_amd as ec
     h = ec.Handle()
