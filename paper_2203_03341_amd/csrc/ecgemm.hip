@@ -727,7 +727,10 @@ ecgemm_status_t launch_fused(ecgemm_handle_t h, const Plan& pl, ecgemm_op_t tran
 // and 1344 x 2368 x 20672 496 / 500.  Of 220 random ones those in three slices or more took 0.51 to 0.985; in two, where
 // the second round is short of blocks for such operands (M N > 3 / 2 blocks (M + N)) and the product more than 20000 deep,
 // 8 of 15 took longer (3264 x 832 x 23232 NN, 364 blocks, 521 / 572, 2944 x 1088 x 34816 NN, 414, 812 / 860): those are left to
-// the plan, and of the other 34 in two slices one took longer (929 x 2827 x 11843 TN 251 / 255), the rest 0.72 to 0.98.
+// the plan, and of the other 34 in two slices one took longer (929 x 2827 x 11843 TN 251 / 255), the rest 0.72 to 0.98.  Not
+// so where C is wider than tall and five of six blocks of two rounds are there: of 39 such 23 took 0.87 to 0.98 of the time in
+// one pass (896 x 4224 x 39360 NN 1041 / 903, 1054 x 3028 x 29875 NT 735 / 685), four as long, eight 1.01 to 1.03 and four, of
+// storage order TN, up to 1.08; taller than wide six of seven took 1.01 to 1.08 (4001 x 868 x 36274 TN 856 / 896).
 // Two rounds of whole tiles where they are short, so that the launch and the fixed cost of a split pass still count, and
 // not so short that the blocks' first loads do, twice: of 32 random ones 224 to 512 deep, 31 took 0.79 to 0.99 of the time
 // (8832 x 576 x 256 NT 27.6 / 21.9, 2304 x 3136 x 320 TN 30.4 / 24.8, 9216 x 704 x 448 TN 38.6 / 38.3) and one longer (3822 x
@@ -751,7 +754,7 @@ WidePlan make_wide_plan(const Plan& pl, int64_t M, int64_t N, int64_t K, ecgemm_
   w.tiles_m = (int)((M + kWideTile - 1) / kWideTile);
   w.tiles_n = (int)((N + kWideTile - 1) / kWideTile);
   const int64_t blocks = tiles * w.slices;
-  const bool short_second_round = w.slices == 2 && K > 20000 && 2 * M * N > 3 * blocks * (M + N);
+  const bool short_second_round = w.slices == 2 && K > 20000 && 2 * M * N > 3 * blocks * (M + N) && (M > N || blocks < kPlanComputeUnits * 5 / 3);
   w.use = blocks <= kPlanComputeUnits ||
           (blocks <= 2 * kPlanComputeUnits && (w.slices > 1 ? M * N <= 800 * (M + N) && !short_second_round : K >= 224 && K <= 512));
   return w;

@@ -243,7 +243,8 @@ def test_which_plans_are_carried_out_in_one_pass():
         assert whole(*size) and one_pass(*size) == taken, size
     for size, taken in (((1024, 1024, 65536), True), ((1024, 1024, 32768), True),                     # two rounds of slices,
                         ((1600, 1600, 17280), True), ((1728, 1728, 17280), False),                    # 1 / M + 1 / N at least 1 / 800
-                        ((960, 2944, 27776), False), ((960, 2944, 19968), True)):                     # a second round short of blocks
+                        ((960, 2944, 27776), False), ((960, 2944, 19968), True),                      # a second round short of blocks
+                        ((896, 3840, 39360), False), ((896, 3968, 39360), True), ((3968, 896, 39360), False)):  # by the order of the tiles
         blocks = slices(*size) * -(-size[0] // 128) * -(-size[1] // 128)
         assert slices(*size) > 1 and 256 < blocks <= 512 and one_pass(*size) == taken, (size, blocks)
     assert one_pass(2048, 2048, 512, lda=1 << 21, ldb=1 << 21)
